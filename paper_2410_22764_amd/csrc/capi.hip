@@ -290,6 +290,9 @@ int dfamin_create(int hip_device, uint64_t hbm_budget_bytes, dfamin_ctx** out) {
   dfamin_ctx* ctx = new (std::nothrow) dfamin_ctx;
   if (!ctx) return DFAMIN_E_NOMEM;
   ctx->c.device = hip_device;
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, hip_device) == hipSuccess && cus > 0)
+    ctx->c.cus = (uint32_t)cus;
   ctx->c.budget = hbm_budget_bytes ? hbm_budget_bytes : (uint64_t)(0.9 * (double)free_b);
   if (hipStreamCreateWithFlags(&ctx->c.stream, hipStreamNonBlocking) != hipSuccess) {
     delete ctx;

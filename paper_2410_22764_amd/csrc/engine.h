@@ -130,6 +130,11 @@ class Engine {
   // the handed-back ones in handoff; DFAMIN_E_BAD_DFA / _E_INTERNAL.
   int fused_collect(const std::vector<InstInput>& in, const std::vector<uint32_t>& which,
                     std::vector<InstOutcome>& res, std::vector<uint32_t>& handoff);
+  // One instance by the grid kernel (grid.hip): done = false when it does
+  // not apply or gave up, and the call goes on through the round engine.
+  int grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, uint64_t max_rounds, hipStream_t s,
+               std::vector<InstOutcome>& res, bool& done);
+  bool grid_applies(const InstInput& x, const dfamin_opts& opts, uint32_t* items, uint32_t* wgs) const;
   int ensure(DevBuf& b, size_t bytes);
   int ensure_host(HostBuf& b, size_t bytes);
   // Closure level storage a call may still take: half of the context's
@@ -255,6 +260,10 @@ class Engine {
   // fused kernels: jobs in class order, their results, and where each sits
   DevBuf d_fjobs_;
   HostBuf h_fjobs_, h_fres_;
+  // grid kernel: its barrier words (zero between launches; never part of the
+  // fixed region) and its mapped result
+  DevBuf d_gbar_;
+  HostBuf h_gres_;
   std::vector<uint32_t> fused_pos_;  // per entry of `which`: index in the job array
   // A batch's fused kernels run on their own stream beside the round
   // engine's work (created at the first batch; not in fixed-region mode,
@@ -286,6 +295,7 @@ class Serving;
 class Context {
  public:
   int device = 0;
+  uint32_t cus = 0;  // compute units of the device
   uint64_t budget = 0;
   uint64_t used = 0;
   hipStream_t stream = nullptr;  // internal stream for host-input calls

@@ -15,6 +15,7 @@
 #include "closure.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cstdio>
 #include <cstdlib>
 #include <chrono>
@@ -45,6 +46,29 @@ inline uint64_t mix64(uint64_t z) {
 constexpr uint32_t kDefaultAutoRounds = 8;
 constexpr uint64_t kClearAheadSlots = 1ull << 22;  // 32 MiB: a few microseconds to clear
 constexpr uint32_t kQueueRounds = 8;               // queued signature rounds per graph (even)
+
+// Workgroups of grid kernels in flight per device, over every context and
+// thread of the process: together at most one per CU, so that all of them can
+// be resident at once whatever order the hardware starts them in.
+std::atomic<uint32_t> g_grid_wgs[64];
+struct GridLease {
+  std::atomic<uint32_t>* pool = nullptr;
+  uint32_t wgs = 0;
+  bool take(int device, uint32_t want, uint32_t cus) {
+    if (device < 0 || device >= 64) return false;
+    std::atomic<uint32_t>& p = g_grid_wgs[device];
+    uint32_t v = p.load();
+    do {
+      if (v + want > cus) return false;
+    } while (!p.compare_exchange_weak(v, v + want));
+    pool = &p;
+    wgs = want;
+    return true;
+  }
+  ~GridLease() {
+    if (pool) pool->fetch_sub(wgs);
+  }
+};
 
 }  // namespace
 
@@ -141,6 +165,7 @@ Engine::~Engine() {
                     &d_results_, &d_wgflags_, &d_part_, &d_dense_,
                     &d_djobs_, &d_visit_, &d_bfs_rows_, &d_min_delta_, &d_min_acc_,
                     &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
+  if (d_gbar_.p) (void)hipFree(d_gbar_.p);
   // device buffers of the fixed-region mode belong to the region
   if (!fixed()) {
     for (DevBuf* b : bufs)
@@ -149,7 +174,7 @@ Engine::~Engine() {
       if (b.p) (void)hipFree(b.p);
   }
   HostBuf* hb[] = {&h_ctrl_, &h_flags_, &h_results_, &h_counts_, &h_jobs_, &h_rb_, &h_qdbl_,
-                   &stage_[0].buf, &stage_[1].buf, &h_fjobs_, &h_fres_};
+                   &stage_[0].buf, &stage_[1].buf, &h_fjobs_, &h_fres_, &h_gres_};
   for (HostBuf* b : hb)
     if (b->p) (void)hipHostFree(b->p);
 }
@@ -161,7 +186,7 @@ uint64_t Engine::device_bytes() const {
                           &d_results_, &d_wgflags_, &d_part_, &d_dense_,
                           &d_djobs_, &d_visit_, &d_bfs_rows_, &d_min_delta_, &d_min_acc_,
                           &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
-  uint64_t t = 0;
+  uint64_t t = d_gbar_.cap;
   for (const DevBuf* b : bufs) t += b->cap;
   for (const DevBuf& b : closure_bufs_) t += b.cap;
   return t;
@@ -237,8 +262,10 @@ int Engine::ensure_host(HostBuf& b, size_t bytes) {
 int Engine::set_fixed_region(void* base, size_t cap, size_t host_bytes) {
   if (!base || fixed() || device_bytes() != 0) return DFAMIN_E_INTERNAL;
   HostBuf* hb[] = {&h_ctrl_, &h_flags_, &h_results_, &h_counts_, &h_jobs_, &h_rb_, &h_qdbl_,
-                   &stage_[0].buf, &stage_[1].buf, &h_fjobs_, &h_fres_};
+                   &stage_[0].buf, &stage_[1].buf, &h_fjobs_, &h_fres_, &h_gres_};
   for (HostBuf* b : hb) TRY(ensure_host(*b, host_bytes));
+  TRY(ensure(d_gbar_, sizeof(GridBar)));
+  HIP(hipMemset(d_gbar_.p, 0, sizeof(GridBar)));
   if (!ev_rb_) HIP(hipEventCreateWithFlags(&ev_rb_, hipEventDisableTiming));
   fixed_base_ = static_cast<char*>(base);
   fixed_cap_ = cap;
@@ -1621,6 +1648,178 @@ int Engine::fused_collect(const std::vector<InstInput>& in, const std::vector<ui
   return rc;
 }
 
+// ---------------------------------------------------------- grid kernel
+bool Engine::grid_applies(const InstInput& x, const dfamin_opts& opts, uint32_t* items, uint32_t* wgs) const {
+  // (the knobs and options that concern the round engine's own rounds keep
+  // to it, as for the fused kernels)
+  if (opts.method != DFAMIN_METHOD_SIGNATURE || (opts.flags & DFAMIN_FLAG_QUEUE) || ctx_->tuner.forced >= 0)
+    return false;
+  for (const char* e : {"DFAMIN_HASH_BITS", "DFAMIN_CAS_FIRST", "DFAMIN_NO_LABELS"})
+    if (std::getenv(e)) return false;
+  if (const char* e = std::getenv("DFAMIN_FUSED_MAX_STATES"))
+    if (std::atol(e) <= 0) return false;
+  if (const char* e = std::getenv("DFAMIN_GRID_MAX_STATES"))  // testing: 0 turns the grid kernel off
+    if ((long)x.n > std::atol(e)) return false;
+  if (x.n < kGridMinStates || x.n > kGridMaxStates || !ctx_->cus) return false;
+  if (x.closure != DFAMIN_CLOSURE_ON && x.k > kFusedMaxLetters) return false;
+  // The kernel keeps two closure levels where the round engine stores all of
+  // a doubling instance's; an instance whose levels the round engine could
+  // not hold (it then refines without doubling) stays with it.
+  uint64_t L = floor_log2_u32(x.n);
+  const uint64_t n = x.n;
+  if (fixed()) {
+    const uint64_t own = 27ull * n + (64ull << 10);  // the engine's buffers carved before the levels
+    if (own > fixed_cap_ || 4 * L * n > (fixed_cap_ - own) / 3) return false;
+  } else if (ctx_->used + 2 * 4 * L * n + (256ull + 8ull * x.k) * n > ctx_->budget) {
+    return false;
+  }
+  return grid_shape(x.n, ctx_->cus, items, wgs);
+}
+
+int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, uint64_t max_rounds, hipStream_t s,
+                     std::vector<InstOutcome>& res, bool& done) {
+  done = false;
+  const InstInput& x = in[0];
+  uint32_t items = 0, wgs = 0;
+  if (!grid_applies(x, opts, &items, &wgs)) return DFAMIN_OK;
+  GridLease lease;
+  if (!lease.take(ctx_->device, wgs, ctx_->cus)) return DFAMIN_OK;
+  const size_t n = x.n;
+  const uint32_t S = (uint32_t)((4 * n + 7) & ~size_t(7));  // (a quarter full: few home slots are taken)
+  if (!d_gbar_.p) {
+    TRY(ensure(d_gbar_, sizeof(GridBar)));
+    HIP(hipMemset(d_gbar_.p, 0, sizeof(GridBar)));
+  }
+  DevBuf* words[] = {&d_block_, &d_nb_, &d_act_, &d_act2_};
+  for (DevBuf* b : words) TRY(ensure(*b, n * 4));
+  TRY(ensure(d_table_, (size_t)S * 16));
+  TRY(ensure(d_wgflags_, (size_t)wgs * 8));
+  TRY(ensure_host(h_gres_, sizeof(GridRes)));
+  in_ = in;
+  res.assign(1, InstOutcome{});
+  closure_cursor_ = 0;
+  stage_idle();
+  stage_cur_ = 0;
+  if (nonid_.empty()) nonid_.resize(1);
+  inst_rows_.resize(1);
+  inst_rows_[0].clear();
+  levels_.assign(1, 0);
+  has_closure_.assign(1, 0);
+  auto letter_rows = [&]() {
+    for (uint32_t a : nonid_[0])
+      inst_rows_[0].push_back(reinterpret_cast<uint64_t>(x.delta) + 4ull * a * x.n);
+  };
+  GridJob J{};
+  auto closure_rows = [&]() -> int {
+    TRY(build_closure({0u}, opts, s));
+    TRY(ensure(d_rows_, std::max<size_t>(inst_rows_[0].size(), 1) * 8));
+    TRY(upload(d_rows_.p, inst_rows_[0].data(), inst_rows_[0].size() * 8, s));
+    J.rows = d_rows_.as<uint64_t>();
+    J.nrows = (uint32_t)inst_rows_[0].size();
+    return DFAMIN_OK;
+  };
+  if (x.closure == DFAMIN_CLOSURE_ON) {
+    TRY(validate(s, res));
+    letter_rows();
+    TRY(closure_rows());
+  }
+  if (no_fused) {  // the minimal DFA's buffers, as the round engine leaves them
+    TRY(ensure(d_slot_of_, n * 4));
+    TRY(ensure(d_keep_, n));
+    TRY(ensure(d_rank_, (n + 1) * 4));
+    TRY(ensure(d_rb_, sizeof(Ctrl) + 8));
+    d_ctrl_.p = d_rb_.p;
+    d_ctrl_.cap = sizeof(Ctrl);
+    d_counts_.p = static_cast<char*>(d_rb_.p) + sizeof(Ctrl) + 4;
+    d_counts_.cap = 4;
+    TRY(ensure_host(h_ctrl_, sizeof(Ctrl)));
+    TRY(queue_fill(d_ctrl_.p, 0, sizeof(Ctrl), s));
+    TRY(flush_segs(s));
+  }
+  J.delta = reinterpret_cast<uint64_t>(x.delta);
+  J.accept = reinterpret_cast<uint64_t>(x.accept);
+  J.out = reinterpret_cast<uint64_t>(x.out);
+  J.n = x.n;
+  J.k = x.k;
+  J.q0 = x.q0;
+  J.closure = x.closure;
+  J.levels = floor_log2_u32(x.n);
+  if (opts.max_levels && opts.max_levels < J.levels) J.levels = opts.max_levels;
+  J.auto_rounds = opts.auto_rounds ? opts.auto_rounds : kDefaultAutoRounds;
+  J.max_rounds = (uint32_t)std::min<uint64_t>(max_rounds, 0xFFFFFFFFull);
+  J.S = S;
+  J.blk[0] = d_block_.as<uint32_t>();
+  J.blk[1] = d_nb_.as<uint32_t>();
+  J.lvl[0] = d_act_.as<uint32_t>();
+  J.lvl[1] = d_act2_.as<uint32_t>();
+  J.table[0] = d_table_.as<unsigned long long>();
+  J.table[1] = J.table[0] + S;
+  J.wgw = d_wgflags_.as<uint32_t>();
+  J.bar = d_gbar_.as<GridBar>();
+  J.res = static_cast<GridRes*>(h_gres_.dp);
+  J.no_doubling = J.want_ids = no_fused ? 1u : 0u;
+  J.salt = 0x5DEECE66Dull;
+  if (const char* e = std::getenv("DFAMIN_GRID_HASH_BITS")) {  // testing: weak signature hashes
+    const int bits = std::atoi(e);
+    if (bits >= 1 && bits < 64) J.hash_mask = (1ull << bits) - 1ull;
+  }
+  Profiler& prof = ctx_->prof;
+  GridRes* h = h_gres_.as<GridRes>();
+  while (true) {
+    // records of signatures too long for registers, while they fit
+    const uint32_t letters = J.rows ? J.nrows : x.k;
+    J.rec = nullptr;
+    if (!fixed() && letters > grid_letters_kept(items) && ensure(d_sig_, (size_t)letters * n * 4) == DFAMIN_OK)
+      J.rec = d_sig_.as<uint32_t>();
+    *h = GridRes{};
+    h->status = kGridAborted;
+    prof.begin(s, "grid", 4.0 * x.n * x.k + x.n / 8.0 + 4.0 * x.n);
+    launch_grid(J, items, wgs, s);
+    prof.end(s);
+    HIP(hipGetLastError());
+    HIP(stream_wait(s));
+    prof.collect();
+    if (h->aborted || h->status == kGridAborted) return DFAMIN_OK;  // not all resident: the round engine takes it
+    if (h->status != kFusedHandOff || J.resume || h->doubling || fixed()) break;
+    // AUTO, still splitting after auto_rounds rounds: the closure's letters
+    // join and the kernel goes on from its partition
+    nonid_[0].clear();
+    for (uint32_t a = 0; a < x.k; ++a)
+      if ((h->letters >> a) & 1u) nonid_[0].push_back(a);
+    J.resume = 1;
+    J.cur0 = h->cur;
+    J.count0 = h->num_blocks;
+    J.rounds0 = h->rounds;
+    J.refine0 = h->refine_rounds;
+    TRY(closure_rows());
+  }
+  InstOutcome& o = res[0];
+  switch (h->status) {
+    case kFusedOk: break;
+    case kFusedHandOff: return DFAMIN_OK;
+    case kFusedBad: o.status = DFAMIN_E_BAD_DFA; done = true; return DFAMIN_E_BAD_DFA;
+    default: done = true; return DFAMIN_E_INTERNAL;
+  }
+  done = true;
+  o.num_blocks = h->num_blocks;
+  o.initial_block = h->initial_block;
+  o.refine_rounds = h->refine_rounds;
+  o.rounds_executed = h->refine_rounds + 1;
+  if (h->doubling) {
+    o.closure_levels = h->levels_used;
+    o.closure_letters = h->levels_used + 1;
+  } else if (has_closure_[0]) {
+    o.closure_levels = levels_[0];
+    o.closure_letters = (uint32_t)inst_rows_[0].size();
+  } else if (no_fused) {
+    nonid_[0].clear();
+    for (uint32_t a = 0; a < x.k; ++a)
+      if ((h->letters >> a) & 1u) nonid_[0].push_back(a);
+    letter_rows();
+  }
+  return DFAMIN_OK;
+}
+
 // Small instances are minimized whole by the fused kernels (one workgroup
 // each, every round in LDS), the others by the round engine.  A single
 // small instance is validated inside its kernel; a batch is validated as a
@@ -1632,6 +1831,12 @@ int Engine::run_all(const std::vector<InstInput>& in, const dfamin_opts& opts, h
                     std::vector<InstOutcome>& res) {
   const size_t I = in.size();
   const uint32_t lim = fused_limit(opts);
+  if (I == 1) {
+    bool done = false;
+    const int rc = grid_run(in, opts, opts.max_rounds ? opts.max_rounds : (uint64_t)in[0].n + 1, s, res, done);
+    if (done || rc != DFAMIN_OK) return rc;
+    if (fixed()) reset_fixed_region();  // carved again by the path taken instead
+  }
   std::vector<uint32_t> small, big;
   uint32_t nmax = 0;
   uint64_t N = 0;

@@ -203,6 +203,62 @@ inline int fused_class(uint32_t n) { return n <= 2048 ? 0 : (n <= 8192 ? 1 : 2);
 void launch_fused(const FusedJob* jobs, FusedRes* res, uint32_t njobs, int cls, hipStream_t s,
                   const FusedJob* one = nullptr);
 
+// Whole minimization of one larger instance by a grid of co-resident
+// workgroups (grid.hip).  Every workgroup must be resident at once: callers
+// launch at most one per CU (grid_shape) and keep the sum over their launches
+// in flight within the device's CUs.  A launch whose barrier waits run out
+// reports kGridAborted and has written nothing but scratch (or correct output
+// entries): the instance then takes another path.
+constexpr uint32_t kGridThreads = 1024;
+constexpr uint32_t kGridMaxItems = 8;  // states per thread
+constexpr uint32_t kGridMinStates = 1024;
+constexpr uint32_t kGridMaxStates = 1u << 21;
+struct alignas(128) GridWord {
+  unsigned long long v;
+};
+// All zero between launches (the last workgroup to leave resets it).
+struct GridBar {
+  GridWord root[4];     // rotating barrier words
+  GridWord leaf[8][4];  // arrivals of the workgroups of one residue mod 8
+  alignas(128) uint32_t abort;
+  alignas(128) uint32_t exits;
+};
+struct GridRes {
+  int32_t status;  // kFused*, kGridAborted
+  uint32_t aborted, num_blocks, initial_block, refine_rounds, rounds, levels_used, doubling;
+  uint32_t letters;  // non-identity letters (bit mask)
+  uint32_t cur;      // which of blk[] holds the partition (kFusedHandOff)
+};
+constexpr int32_t kGridAborted = 5;
+struct GridJob {
+  uint64_t delta, accept, out;  // device addresses (letter-major rows, bitmap, n outputs)
+  uint32_t n, k, q0, closure;
+  uint32_t levels, auto_rounds, max_rounds;  // as in FusedJob
+  uint32_t S;                    // table slots, more than n, a multiple of 8
+  uint32_t* blk[2];              // n block ids each
+  uint32_t* lvl[2];              // n entries each: doubling levels, ranks at the end
+  unsigned long long* table[2];  // S slots each, table[1] right behind table[0]
+  uint32_t* rec;                 // signature letters x n words, or null
+  uint32_t* wgw;                 // two words per workgroup
+  GridBar* bar;
+  GridRes* res;  // mapped page-locked host memory
+  // Refine over these rows instead of the non-identity letters (already
+  // validated; no doubling, no hand-off); resume: from the partition in
+  // blk[cur0] with the given counts.
+  const uint64_t* rows;
+  uint32_t nrows, resume, cur0, count0, rounds0, refine0;
+  uint32_t no_doubling;  // hand a doubling instance back after validation
+  uint32_t want_ids;     // leave least-member ids in blk[0]
+  uint64_t salt, hash_mask;  // hash_mask: testing, as Ctrl::hash_mask
+};
+// Signature letters whose blocks a thread keeps in registers between the
+// steps of a round; records (GridJob::rec) serve longer signatures.
+inline uint32_t grid_letters_kept(uint32_t items) { return items >= 8 ? 2u : (items == 4 ? 4u : 8u); }
+// States per thread and workgroups for n states on a device of `cus` CUs;
+// false if that is more than the kernel takes.
+bool grid_shape(uint32_t n, uint32_t cus, uint32_t* items, uint32_t* wgs);
+void launch_grid(const GridJob& J, uint32_t items, uint32_t wgs, hipStream_t s);
+
 // Row-check flag bits.
 constexpr uint32_t kFlagBad = 1u;      // entry >= n
 constexpr uint32_t kFlagNonId = 2u;    // entry != its own index

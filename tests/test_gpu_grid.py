@@ -1,0 +1,158 @@
+"""The grid kernel (one instance by co-resident workgroups) against the CPU
+oracle and the round engine: same partition, round counts and closure levels.
+Sizes sit at the edges of its tiles (1,024 states per workgroup and pass; 1,
+2, 4 and 8 states per thread on 256 CUs)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2410_22764_amd import dfamin, workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = dfamin.dfamin_create(0)
+    yield c
+    c.close()
+
+
+def _both(ctx, d, monkeypatch, **opts):
+    """The call as it is, and with the grid kernel turned off."""
+    print(f"[case] {d.name} n={d.n} k={d.k} {opts}", flush=True)
+    out, res = dfamin.dfamin_minimize(ctx, d, opts or None)
+    monkeypatch.setenv("DFAMIN_GRID_MAX_STATES", "0")
+    out2, res2 = dfamin.dfamin_minimize(ctx, d, opts or None)
+    monkeypatch.delenv("DFAMIN_GRID_MAX_STATES")
+    assert np.array_equal(out, out2)
+    assert res == res2
+    return out, res
+
+
+def _check(ctx, d, monkeypatch, **opts):
+    out, res = _both(ctx, d, monkeypatch, **opts)
+    want, nb = oracle.hopcroft(d.n, d.k, d.delta, d.accept)
+    assert np.array_equal(out, want) and res["num_blocks"] == nb and res["initial_block"] == want[d.q0]
+
+
+def _redundant(n, k, classes, seed):
+    """Every state copies a state of a random automaton."""
+    r = np.random.RandomState(seed)
+    cls = r.permutation(np.concatenate([np.arange(classes), r.randint(0, classes, n - classes)]))
+    members = [np.nonzero(cls == c)[0] for c in range(classes)]
+    base = r.randint(0, classes, (k, classes))
+    rows = np.empty((k, n), np.uint32)
+    for a in range(k):
+        for c in range(classes):
+            m = members[c]
+            rows[a, m] = r.choice(members[base[a, c]], len(m))
+    return W.from_rows(rows, r.rand(classes)[cls] < 0.5, int(r.randint(n)), f"redundant({n},{k},{classes})")
+
+
+@pytest.mark.parametrize("n", [1024, 1025, 2047, 32769, 262144, 262145, 524289, 1048577])
+@pytest.mark.parametrize("k", [2, 5])
+def test_random(ctx, n, k, monkeypatch):
+    _check(ctx, W.random_dfa(n, k, n + k), monkeypatch)
+
+
+@pytest.mark.parametrize("closure", ["auto", "off", "on"])
+@pytest.mark.parametrize("n,k,c", [(1500, 9, 100), (40001, 3, 5000), (300007, 2, 7)])
+def test_redundant(ctx, n, k, c, closure, monkeypatch):
+    _check(ctx, _redundant(n, k, c, n), monkeypatch, closure=closure)
+
+
+@pytest.mark.parametrize("closure", ["auto", "on"])
+@pytest.mark.parametrize("n", [1024, 1025, 30001, 270001])
+def test_chains(ctx, n, closure, monkeypatch):
+    _check(ctx, W.permuted_chain_dfa(n, 3, n), monkeypatch, closure=closure)
+
+
+@pytest.mark.parametrize("opts", [dict(), dict(max_levels=3), dict(auto_rounds=2), dict(closure="off")])
+def test_unary_and_deep(ctx, opts, monkeypatch):
+    _check(ctx, W.fib_dfa(16), monkeypatch, **opts)
+    _check(ctx, W.bitsplitter_dfa(13), monkeypatch, **opts)
+    _check(ctx, W.random_dfa(5000, 1, 3), monkeypatch, **opts)
+
+
+def test_many_letters(ctx, monkeypatch):
+    """Alphabets around the chunks of letters whose loads go out together,
+    the widest the kernel validates, and one too wide for it."""
+    for k in (7, 8, 9, 32, 33):
+        _check(ctx, _redundant(3000, k, 300, k), monkeypatch)
+
+
+def test_degenerate(ctx, monkeypatch):
+    n = 5000
+    ident = np.tile(np.arange(n, dtype=np.uint32), (2, 1))
+    for rows in (ident, (ident + 1) % n):
+        for acc in (np.zeros(n, bool), np.ones(n, bool), np.arange(n) == n - 1, np.arange(n) % 2 == 0):
+            _check(ctx, W.from_rows(rows, acc, 17), monkeypatch)
+
+
+def test_refused_inputs_and_caps(ctx, monkeypatch):
+    d = W.random_dfa(70001, 3, 1)
+    d.delta[2 * d.n + 69999] = d.n
+    for closure in ("auto", "on"):
+        _, res = dfamin.dfamin_minimize(ctx, d, dict(closure=closure), check=False)
+        assert res["rc"] == dfamin.DFAMIN_E_BAD_DFA and res["status"] == dfamin.DFAMIN_E_BAD_DFA
+    c = W.chain_dfa(3000, 2)
+    for cap in (1, 5, 11, 12, 13):
+        got = dfamin.dfamin_minimize(ctx, c, dict(max_rounds=cap), check=False)[1]
+        monkeypatch.setenv("DFAMIN_GRID_MAX_STATES", "0")
+        assert dfamin.dfamin_minimize(ctx, c, dict(max_rounds=cap), check=False)[1] == got
+        monkeypatch.delenv("DFAMIN_GRID_MAX_STATES")
+    _check(ctx, W.random_dfa(70001, 3, 1), monkeypatch)  # the context goes on
+
+
+def test_weak_hashes_are_redone(ctx, monkeypatch):
+    """Few bits of hash: different signatures share one now and then, and
+    the round is redone with another salt; with too few, every salt collides
+    and the call gives up with an error."""
+    d = _redundant(20000, 3, 1200, 5)
+    want, nb = oracle.hopcroft(d.n, d.k, d.delta, d.accept)
+    monkeypatch.setenv("DFAMIN_GRID_HASH_BITS", "20")
+    for _ in range(3):
+        out, res = dfamin.dfamin_minimize(ctx, d)
+        assert np.array_equal(out, want) and res["num_blocks"] == nb
+    monkeypatch.setenv("DFAMIN_GRID_HASH_BITS", "4")
+    assert dfamin.dfamin_minimize(ctx, d, check=False)[1]["rc"] == dfamin.DFAMIN_E_INTERNAL
+    monkeypatch.delenv("DFAMIN_GRID_HASH_BITS")
+    _check(ctx, d, monkeypatch)
+
+
+def test_minimal_dfa(ctx, monkeypatch):
+    for d in (W.random_dfa(30001, 3, 2), _redundant(20001, 2, 3000, 9), W.permuted_chain_dfa(4000, 2, 1),
+              W.bitsplitter_dfa(12)):
+        print(f"[case] minimal {d.name}", flush=True)
+        a = dfamin.dfamin_minimal_dfa(ctx, d)
+        monkeypatch.setenv("DFAMIN_GRID_MAX_STATES", "0")
+        b = dfamin.dfamin_minimal_dfa(ctx, d)
+        monkeypatch.delenv("DFAMIN_GRID_MAX_STATES")
+        assert a[0] == b[0] and a[3] == b[3]
+        assert all(np.array_equal(a[i], b[i]) for i in (1, 2, 4))
+
+
+def test_concurrent_calls(monkeypatch):
+    """Several contexts at once: the workgroups of all grid kernels in flight
+    never exceed the device; calls beyond that take the round engine."""
+    import threading
+    ds = [W.random_dfa(200003, 2, 1), W.permuted_chain_dfa(150001, 2, 2), W.random_dfa(9001, 3, 3),
+          W.fib_dfa(18)]
+    want = [oracle.hopcroft(d.n, d.k, d.delta, d.accept)[0] for d in ds]
+    bad = []
+
+    def work(i):
+        with dfamin.dfamin_create(0) as c:
+            for t in range(6):
+                d = ds[(i + t) % len(ds)]
+                out, _ = dfamin.dfamin_minimize(c, d)
+                if not np.array_equal(out, want[(i + t) % len(ds)]):
+                    bad.append((i, t))
+
+    ts = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not bad
