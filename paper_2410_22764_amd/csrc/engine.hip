@@ -1660,7 +1660,7 @@ bool Engine::grid_applies(const InstInput& x, const dfamin_opts& opts, uint32_t*
     if (std::atol(e) <= 0) return false;
   if (const char* e = std::getenv("DFAMIN_GRID_MAX_STATES"))  // testing: 0 turns the grid kernel off
     if ((long)x.n > std::atol(e)) return false;
-  if (x.n < kGridMinStates || x.n > kGridMaxStates || !ctx_->cus) return false;
+  if (x.n < kGridMinStates || !ctx_->cus) return false;
   if (x.closure != DFAMIN_CLOSURE_ON && x.k > kFusedMaxLetters) return false;
   // The kernel keeps two closure levels where the round engine stores all of
   // a doubling instance's; an instance whose levels the round engine could
@@ -1690,8 +1690,10 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
     TRY(ensure(d_gbar_, sizeof(GridBar)));
     HIP(hipMemset(d_gbar_.p, 0, sizeof(GridBar)));
   }
-  DevBuf* words[] = {&d_block_, &d_nb_, &d_act_, &d_act2_};
-  for (DevBuf* b : words) TRY(ensure(*b, n * 4));
+  TRY(ensure(d_block_, n * 4));
+  TRY(ensure(d_nb_, n * 4));
+  TRY(ensure(d_act_, n * 8));
+  TRY(ensure(d_act2_, n * 8));
   TRY(ensure(d_table_, (size_t)S * 16));
   TRY(ensure(d_wgflags_, (size_t)wgs * 8));
   TRY(ensure_host(h_gres_, sizeof(GridRes)));
@@ -1750,8 +1752,9 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
   J.S = S;
   J.blk[0] = d_block_.as<uint32_t>();
   J.blk[1] = d_nb_.as<uint32_t>();
-  J.lvl[0] = d_act_.as<uint32_t>();
-  J.lvl[1] = d_act2_.as<uint32_t>();
+  J.pr[0] = d_act_.as<uint2>();
+  J.pr[1] = d_act2_.as<uint2>();
+  J.rank = d_act_.as<uint32_t>();
   J.table[0] = d_table_.as<unsigned long long>();
   J.table[1] = J.table[0] + S;
   J.wgw = d_wgflags_.as<uint32_t>();

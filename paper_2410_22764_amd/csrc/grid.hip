@@ -26,9 +26,16 @@
 // accesses (about 1 us each through the coherent part of the memory system)
 // and a grid barrier (measured: 1.2 us for 16 workgroups, 1.5 us for 32, 2.2
 // for 64 on one counter; above 32 arrivals go through eight counters, since a
-// single one costs 28 ns per workgroup).
+// single one costs 28 ns per workgroup).  Per call, against the host-planned
+// rounds (the one-workgroup kernel up to 16,384 states): Fib_20 (17,711
+// states, 15 rounds) 932 -> 184 us; a permuted chain of 300,007 states (19
+// rounds) 1,240 -> 490 us; random, n = 16,384, two letters, 140 -> 81 us; the
+// 2^20-state bit-splitter 5.14 -> 1.95 ms, half of it reading rows and
+// records at 6-8 TB/s from the caches.
 #include "../../include/dfamin.h"
 #include "internal.h"
+
+#include <type_traits>
 
 namespace dfamin {
 
@@ -218,12 +225,31 @@ __device__ __forceinline__ uint32_t grid_insert(unsigned long long* table, uint3
   return 0u;
 }
 
+// A row or id array at a workgroup-uniform address, indexed by 32-bit byte
+// offsets (n <= 2^21 entries): one scalar base and one offset register per
+// load, where 64-bit addresses per lane cost two.
+__device__ __forceinline__ const uint32_t* uniform_ptr(unsigned long long a) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+  return reinterpret_cast<const uint32_t*>(((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ uint32_t at32(const uint32_t* p, uint32_t i) {
+  return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(p) + (i << 2));
+}
+__device__ __forceinline__ uint2 at64(const uint2* p, uint32_t i) {
+  return *reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(p) + (i << 3));
+}
+
 // ITEMS states per thread.  A workgroup owns the kT*ITEMS states from
 // base on, item e of thread t being base + e*kT + t, so workgroup order is
-// state order (the numbering at the end is a prefix over workgroups).
+// state order (the numbering at the end is a prefix over workgroups).  A
+// state's own id, and its successors under up to CH letters (or its successor
+// at the current doubling level), stay in registers from round to round: a
+// group step then starts with the gathers.
 template <int ITEMS>
 __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
-  constexpr int CH = ITEMS >= 8 ? 2 : (ITEMS == 4 ? 4 : 8);  // letters whose loads go out together
+  constexpr int CH = 8 / ITEMS;                           // letters kept in registers
+  constexpr int CL = 8 / ITEMS;  // letters per chunk of longer signatures
   // states are grouped in LDS kPass items at a time, in twice as many slots
   constexpr int kPass = ITEMS < 4 ? ITEMS : 4;
   constexpr uint32_t kLds = 2u * kPass * kT;
@@ -234,8 +260,8 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
   const uint32_t n = J.n, wg = blockIdx.x, G = gridDim.x, S = J.S;
   const uint32_t base = wg * (uint32_t)(kT * ITEMS);
-  const uint32_t* delta = reinterpret_cast<const uint32_t*>(J.delta);
   const uint8_t* acc = reinterpret_cast<const uint8_t*>(J.accept);
+  auto state = [&](int e) { return base + (uint32_t)(e * kT) + tid; };
   GridSync sync{J.bar, G, wg, 0u, s_val};
   unsigned long long sum = 0;
   if (tid == 0) {
@@ -252,34 +278,34 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
   }
   uint32_t cur = J.cur0, count = J.count0, rounds = J.rounds0, refine = J.refine0;
   uint32_t mask = 0;
+  uint32_t own[ITEMS];  // block id | kSingleBit
   if (!J.resume) {
     uint32_t nonid = 0, any = 0;  // any: bit 0 some rejecting state, bit 1 some accepting, bit 2 a bad entry
     if (!J.rows)
       for (uint32_t a0 = 0; a0 < J.k; a0 += CH) {
         uint32_t v[CH][ITEMS];
 #pragma unroll
+        for (int c = 0; c < CH; ++c) {
+          const uint32_t* rp = reinterpret_cast<const uint32_t*>(J.delta) + (size_t)min(a0 + c, J.k - 1u) * n;
+#pragma unroll
+          for (int e = 0; e < ITEMS; ++e) v[c][e] = state(e) < n ? at32(rp, state(e)) : state(e);
+        }
+#pragma unroll
         for (int c = 0; c < CH; ++c)
 #pragma unroll
           for (int e = 0; e < ITEMS; ++e) {
-            const uint32_t q = base + (uint32_t)(e * kT) + tid;
-            v[c][e] = (a0 + c < J.k && q < n) ? delta[(size_t)(a0 + c) * n + q] : q;
-          }
-#pragma unroll
-        for (int c = 0; c < CH; ++c)
-#pragma unroll
-          for (int e = 0; e < ITEMS; ++e) {
-            const uint32_t q = base + (uint32_t)(e * kT) + tid;
-            if (q < n && v[c][e] >= n) any |= 4u;
-            if (v[c][e] != q) nonid |= 1u << ((a0 + c) & 31u);
+            if (state(e) < n && v[c][e] >= n) any |= 4u;
+            if (v[c][e] != state(e)) nonid |= 1u << min(a0 + c, J.k - 1u);
           }
       }
 #pragma unroll
     for (int e = 0; e < ITEMS; ++e) {
-      const uint32_t q = base + (uint32_t)(e * kT) + tid;
+      const uint32_t q = state(e);
+      own[e] = kSingleBit;
       if (q >= n) continue;
-      const uint32_t f = (acc[q >> 3] >> (q & 7u)) & 1u;
-      J.blk[0][q] = f;
-      any |= 1u << f;
+      own[e] = (acc[q >> 3] >> (q & 7u)) & 1u;
+      J.blk[0][q] = own[e];
+      any |= 1u << own[e];
     }
     nonid = or64(nonid);
     any = or64(any);
@@ -292,6 +318,9 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
       J.wgw[2 * wg] = s_or[0];
       J.wgw[2 * wg + 1] = s_or[1];
     }
+  } else {
+#pragma unroll
+    for (int e = 0; e < ITEMS; ++e) own[e] = state(e) < n ? J.blk[cur][state(e)] : kSingleBit;
   }
   int32_t status = sync.wait(0, sum) ? kFusedOk : kGridAborted;
   if (!J.resume && status == kFusedOk) {
@@ -320,121 +349,29 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
   if (dbl && J.no_doubling && status == kFusedOk) status = kFusedHandOff;
   __syncthreads();
   const uint64_t* lrows = J.rows;
-  auto row = [&](uint32_t t) {
-    return reinterpret_cast<const uint32_t*>(list ? (unsigned long long)lrows[t] : s_rows[t]);
-  };
+  auto row = [&](uint32_t t) { return uniform_ptr(list ? (unsigned long long)lrows[t] : s_rows[t]); };
 
-  uint32_t l = 0, used = 0;      // doubling: the level of this round, the highest a splitting round read
-  uint64_t jlen = 0;             // the partition is P_jlen
-  const uint32_t* lv = dbl ? row(0) : nullptr;  // the level this round reads
+  uint32_t l = 0, used = 0;  // doubling: the level of this round, the highest a splitting round read
+  uint64_t jlen = 0;         // the partition is P_jlen
   uint32_t tsel = 0, retries = 0;
   uint64_t salt = J.salt;
-  uint32_t clr[ITEMS];  // slot of the previous round this thread has to clear
+  uint32_t slot[ITEMS], clr[ITEMS];  // this round's slot; the slot of the last round this thread has to clear
 #pragma unroll
   for (int e = 0; e < ITEMS; ++e) clr[e] = kNoSlot;
 
-  while (status == kFusedOk) {
-    if (!list && autom && !dbl && knon >= 2 && rounds == J.auto_rounds) {
-      status = kFusedHandOff;  // still splitting: the host builds its closure letters
-      break;
+  // LDS grouping and the table inserts, from the hashes h on.
+  auto clear_lds = [&]() {
+    uint4* k4 = reinterpret_cast<uint4*>(lkey);
+    uint4* m4 = reinterpret_cast<uint4*>(lmin);
+    uint4* v4 = reinterpret_cast<uint4*>(lval);
+    for (uint32_t i = tid; i < kLds / 2; i += kT) k4[i] = make_uint4(0, 0, 0, 0);
+    for (uint32_t i = tid; i < kLds / 4; i += kT) {
+      m4[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+      v4[i] = make_uint4(0, 0, 0, 0);
     }
-    if (rounds >= J.max_rounds) {
-      status = kFusedRoundCap;
-      break;
-    }
-    const uint32_t* bc = J.blk[cur];
-    uint32_t* bn = J.blk[cur ^ 1u];
+  };
+  auto group = [&](uint64_t (&h)[ITEMS]) {
     unsigned long long* table = J.table[tsel];
-    unsigned long long* old_table = J.table[tsel ^ 1u];
-    uint32_t* lvn = nullptr;  // next level, built beside this round's gathers
-    if (dbl && l < J.levels && (1ull << (l + 1)) <= jlen + (1ull << l) + 1ull) lvn = J.lvl[(l + 1u) & 1u];
-    const uint32_t kp = dbl ? 1u : knon;
-    // more letters than stay in registers: the blocks gathered here are kept
-    // for the comparison in the resolve step
-    uint32_t* rec = kp > (uint32_t)CH ? J.rec : nullptr;
-
-    // ---- group
-    uint32_t own[ITEMS], slot[ITEMS], b[CH][ITEMS];
-    uint64_t h[ITEMS];
-#pragma unroll
-    for (int e = 0; e < ITEMS; ++e) {
-      const uint32_t q = base + (uint32_t)(e * kT) + tid;
-      own[e] = q < n ? bc[q] : kSingleBit;
-      slot[e] = kNoSlot;
-    }
-    // row entries of the first letters, on their way while the LDS table is
-    // cleared; inside the loop the next letters' entries go out before this
-    // chunk's gathers
-    uint32_t s[CH][ITEMS];
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const uint32_t* rp = (uint32_t)c < kp ? (dbl ? lv : row((uint32_t)c)) : nullptr;
-#pragma unroll
-      for (int e = 0; e < ITEMS; ++e) {
-        const uint32_t q = base + (uint32_t)(e * kT) + tid;
-        s[c][e] = (rp && q < n) ? rp[q] : 0u;
-      }
-    }
-    auto clear_lds = [&]() {
-      uint4* k4 = reinterpret_cast<uint4*>(lkey);
-      uint4* m4 = reinterpret_cast<uint4*>(lmin);
-      uint4* v4 = reinterpret_cast<uint4*>(lval);
-      for (uint32_t i = tid; i < kLds / 2; i += kT) k4[i] = make_uint4(0, 0, 0, 0);
-      for (uint32_t i = tid; i < kLds / 4; i += kT) {
-        m4[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
-        v4[i] = make_uint4(0, 0, 0, 0);
-      }
-    };
-    clear_lds();
-#pragma unroll
-    for (int e = 0; e < ITEMS; ++e)
-      if (clr[e] != kNoSlot) old_table[clr[e]] = 0ull;
-#pragma unroll
-    for (int e = 0; e < ITEMS; ++e) h[e] = mix(salt, own[e]);
-    if (dbl) {
-      uint32_t nx[ITEMS];
-#pragma unroll
-      for (int e = 0; e < ITEMS; ++e) {
-        b[0][e] = (own[e] & kSingleBit) ? 0u : bc[s[0][e]] & kIdBits;
-        nx[e] = lvn ? lv[s[0][e]] : 0u;
-      }
-#pragma unroll
-      for (int e = 0; e < ITEMS; ++e) {
-        const uint32_t q = base + (uint32_t)(e * kT) + tid;
-        if (lvn && q < n) lvn[q] = nx[e];
-        h[e] = mix(h[e], b[0][e]);
-      }
-    } else {
-      for (uint32_t t0 = 0; t0 < kp; t0 += CH) {
-        uint32_t sn[CH][ITEMS];
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-          const uint32_t* rp = t0 + CH + c < kp ? row(t0 + CH + c) : nullptr;
-#pragma unroll
-          for (int e = 0; e < ITEMS; ++e)
-            sn[c][e] = (rp && !(own[e] & kSingleBit)) ? rp[base + (uint32_t)(e * kT) + tid] : 0u;
-        }
-#pragma unroll
-        for (int c = 0; c < CH; ++c)
-#pragma unroll
-          for (int e = 0; e < ITEMS; ++e)
-            b[c][e] = (t0 + c < kp && !(own[e] & kSingleBit)) ? bc[s[c][e]] & kIdBits : 0u;
-#pragma unroll
-        for (int c = 0; c < CH; ++c)
-          if (t0 + c < kp) {
-#pragma unroll
-            for (int e = 0; e < ITEMS; ++e) {
-              h[e] = mix(h[e], b[c][e]);
-              if (rec && !(own[e] & kSingleBit))
-                rec[(size_t)(t0 + c) * n + base + (uint32_t)(e * kT) + tid] = b[c][e];
-            }
-          }
-#pragma unroll
-        for (int c = 0; c < CH; ++c)
-#pragma unroll
-          for (int e = 0; e < ITEMS; ++e) s[c][e] = sn[c][e];
-      }
-    }
     // few groups: most inserts join a slot that already has a lower member
     // and the shared bit, and a read then saves the atomic
     const bool read_first = (uint64_t)count * 64u < n;
@@ -448,7 +385,6 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
         }
         __syncthreads();
       }
-      const uint32_t q = base + (uint32_t)(e * kT) + tid;
       const bool act = !(own[e] & kSingleBit);
       uint64_t hh = mix_end(h[e]);
       if (J.hash_mask) hh = mix_end(hh & J.hash_mask);
@@ -470,7 +406,7 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
           if (prev == 0ull || prev == lk) break;
           p = (p + 1u) & (kLds - 1u);
         }
-        atomicMin(&lmin[p], q);
+        atomicMin(&lmin[p], state(e));
         atomicAdd(&lval[p], like ? (uint32_t)__popcll(lm) : 1u);
         lp[e] = p;
       }
@@ -481,91 +417,40 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
         // one insert per local group, by its least member (the only one to
         // read the group's count, which the slot then replaces)
 #pragma unroll
-        for (int i = e - kPass + 1; i <= e; ++i) {
-          const uint32_t x = base + (uint32_t)(i * kT) + tid;
-          if (!(own[i] & kSingleBit) && lmin[lp[i]] == x)
-            lval[lp[i]] = grid_insert(table, S, h[i], x, lval[lp[i]] > 1u, read_first, &s_fault);
-        }
+        for (int i = e - kPass + 1; i <= e; ++i)
+          if (!(own[i] & kSingleBit) && lmin[lp[i]] == state(i))
+            lval[lp[i]] = grid_insert(table, S, h[i], state(i), lval[lp[i]] > 1u, read_first, &s_fault);
         __syncthreads();
 #pragma unroll
-        for (int i = e - kPass + 1; i <= e; ++i)
-          if (!(own[i] & kSingleBit)) slot[i] = lval[lp[i]];
+        for (int i = e - kPass + 1; i <= e; ++i) slot[i] = (own[i] & kSingleBit) ? kNoSlot : lval[lp[i]];
       }
     }
-    if (!sync.wait(0, sum)) {
-      status = kGridAborted;
-      break;
-    }
-
-    // ---- resolve
-    uint32_t leaders = 0, coll = 0;
+  };
+  // Ends the resolve step: new ids (nid) are known; counts leaders, and
+  // after the barrier decides what comes next.  True: another round.
+  uint32_t r[ITEMS];  // the group's least member
+  bool shared[ITEMS];
+  auto read_slots = [&]() {
+    const unsigned long long* table = J.table[tsel];
     unsigned long long w[ITEMS];
 #pragma unroll
     for (int e = 0; e < ITEMS; ++e) w[e] = slot[e] != kNoSlot ? table[slot[e]] : 0ull;
-    uint32_t r[ITEMS];
-    bool chk[ITEMS];
 #pragma unroll
     for (int e = 0; e < ITEMS; ++e) {
-      const uint32_t q = base + (uint32_t)(e * kT) + tid;
-      r[e] = slot[e] != kNoSlot ? (uint32_t)(w[e] >> 1) & kIdBits : q;
-      chk[e] = slot[e] != kNoSlot && r[e] != q;
+      r[e] = slot[e] != kNoSlot ? (uint32_t)(w[e] >> 1) & kIdBits : state(e);
+      shared[e] = (w[e] & 1ull) != 0;
     }
-#pragma unroll
-    for (int e = 0; e < ITEMS; ++e)
-      if (chk[e]) coll |= (uint32_t)(bc[r[e]] != own[e]);
-    if (kp <= (uint32_t)CH) {  // b still holds every successor's block
-      uint32_t o[CH][ITEMS];
-#pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        const uint32_t* rp = (uint32_t)c < kp ? (dbl ? lv : row((uint32_t)c)) : nullptr;
-#pragma unroll
-        for (int e = 0; e < ITEMS; ++e) o[c][e] = (rp && chk[e]) ? rp[r[e]] : 0u;
-      }
-#pragma unroll
-      for (int c = 0; c < CH; ++c)
-#pragma unroll
-        for (int e = 0; e < ITEMS; ++e)
-          if ((uint32_t)c < kp && chk[e]) coll |= (uint32_t)((bc[o[c][e]] & kIdBits) != b[c][e]);
-    } else if (rec) {
-      for (uint32_t t0 = 0; t0 < kp; t0 += CH) {
-        uint32_t x[CH][ITEMS], y[CH][ITEMS];
-#pragma unroll
-        for (int c = 0; c < CH; ++c)
-#pragma unroll
-          for (int e = 0; e < ITEMS; ++e) {
-            const bool on = t0 + c < kp && chk[e];
-            x[c][e] = on ? rec[(size_t)(t0 + c) * n + base + (uint32_t)(e * kT) + tid] : 0u;
-            y[c][e] = on ? rec[(size_t)(t0 + c) * n + r[e]] : 0u;
-          }
-#pragma unroll
-        for (int c = 0; c < CH; ++c)
-#pragma unroll
-          for (int e = 0; e < ITEMS; ++e) coll |= (uint32_t)(x[c][e] != y[c][e]);
-      }
-    } else {  // no room for records: both signatures gathered again
-      for (uint32_t t = 0; t < kp; ++t) {
-        const uint32_t* rp = row(t);
-#pragma unroll
-        for (int e = 0; e < ITEMS; ++e)
-          if (chk[e])
-            coll |= (uint32_t)((bc[rp[r[e]]] & kIdBits) != (bc[rp[base + (uint32_t)(e * kT) + tid]] & kIdBits));
-      }
-    }
+  };
+  auto new_id = [&](int e) {
+    return slot[e] == kNoSlot ? own[e] : (r[e] | (shared[e] ? 0u : kSingleBit));
+  };
+  auto finish = [&](uint32_t coll) {
+    uint32_t leaders = 0;
 #pragma unroll
     for (int e = 0; e < ITEMS; ++e) {
-      const uint32_t q = base + (uint32_t)(e * kT) + tid;
-      clr[e] = kNoSlot;
-      if (q >= n) continue;
-      if (own[e] & kSingleBit) {
-        bn[q] = own[e];
-        ++leaders;
-        continue;
-      }
-      bn[q] = r[e] | ((w[e] & 1ull) ? 0u : kSingleBit);
-      if (r[e] == q) {
-        ++leaders;
-        clr[e] = slot[e];
-      }
+      const bool lead = state(e) < n && r[e] == state(e);
+      leaders += lead ? 1u : 0u;
+      clr[e] = lead ? slot[e] : kNoSlot;
     }
     leaders = sum64(leaders);
     const bool anyc = __any(coll != 0u);
@@ -583,46 +468,274 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
     }
     if (!sync.wait(pay, sum)) {
       status = kGridAborted;
-      break;
+      return false;
     }
     tsel ^= 1u;
     if (sum >> kCollShift) {  // two signatures shared a hash: the same round again
       if (++retries > kMaxSaltRetries) {
         status = kFusedFault;
-        break;
+        return false;
       }
       salt = mix_end(salt + 0x9E3779B97F4A7C15ull);
-      continue;
+      return true;
     }
     retries = 0;
-    const uint32_t cnew = (uint32_t)(sum & kSumMask);
+    return true;
+  };
+  // After a round that was not redone: false when it was the last.
+  auto settle = [&](uint32_t cnew, uint64_t step) {
     ++rounds;
     cur ^= 1u;  // (when nothing split, the same blocks under their least members)
-    if (cnew == count) break;
+#pragma unroll
+    for (int e = 0; e < ITEMS; ++e) own[e] = new_id(e);
+    if (cnew == count) return false;
     ++refine;
     used = max(used, l);
     count = cnew;
-    jlen += dbl ? (1ull << l) : 1ull;
-    if (lvn) {  // built in this round
-      lv = lvn;
-      ++l;
-    }
-    if (count == n) break;
-  }
-  if (status == kFusedOk) {
-    // ---- canonical numbering by least member (J.lvl[0] holds the ranks)
-    uint32_t id[ITEMS];
-    const uint32_t* bc = J.blk[cur];
-    uint32_t* out = reinterpret_cast<uint32_t*>(J.out);
+    jlen += step;
+    return count != n;
+  };
+  auto clear_old = [&]() {
+    unsigned long long* old_table = J.table[tsel ^ 1u];
 #pragma unroll
-    for (int e = 0; e < ITEMS; ++e) {
-      const uint32_t q = base + (uint32_t)(e * kT) + tid;
-      id[e] = q < n ? bc[q] & kIdBits : kIdBits;
+    for (int e = 0; e < ITEMS; ++e)
+      if (clr[e] != kNoSlot) old_table[clr[e]] = 0ull;
+  };
+
+  // Doubling, one letter: pr[] holds (block id, successor at the level the
+  // next round reads) side by side, so a round gathers both the successor's
+  // block and the next level's square in one access.
+  auto doubling_rounds = [&]() {
+    const uint32_t* row0 = row(0);
+    uint32_t sx[ITEMS];  // successor at this round's level
+#pragma unroll
+    for (int e = 0; e < ITEMS; ++e) sx[e] = state(e) < n ? at32(row0, state(e)) : 0u;
+    bool first = true;  // ids still are accept bits in blk[0], the level is the row itself
+    while (true) {
+      if (rounds >= J.max_rounds) {
+        status = kFusedRoundCap;
+        break;
+      }
+      const uint2* pc = J.pr[cur];
+      uint2* pn = J.pr[cur ^ 1u];
+      const bool up = l < J.levels && (1ull << (l + 1)) <= jlen + (1ull << l) + 1ull;  // the next round reads l + 1
+      clear_lds();
+      clear_old();
+      uint32_t bb[ITEMS], nx[ITEMS];
+      uint64_t h[ITEMS];
+      if (first) {
+        const uint32_t* b0 = J.blk[0];
+#pragma unroll
+        for (int e = 0; e < ITEMS; ++e) {
+          bb[e] = at32(b0, sx[e]);
+          nx[e] = at32(row0, sx[e]);
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < ITEMS; ++e) {
+          const uint2 v = at64(pc, sx[e]);
+          bb[e] = v.x & kIdBits;
+          nx[e] = v.y;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < ITEMS; ++e) {
+        if (!up) nx[e] = sx[e];
+        h[e] = mix(mix(salt, own[e]), bb[e]);
+      }
+      group(h);
+      if (!sync.wait(0, sum)) {
+        status = kGridAborted;
+        break;
+      }
+      read_slots();
+      uint32_t coll = 0;
+      uint32_t sr[ITEMS];
+#pragma unroll
+      for (int e = 0; e < ITEMS; ++e) {
+        sr[e] = sx[e];
+        if (r[e] == state(e) || slot[e] == kNoSlot) continue;
+        const uint2 v = first ? make_uint2(at32(J.blk[0], r[e]), at32(row0, r[e])) : at64(pc, r[e]);
+        coll |= (uint32_t)(v.x != own[e]);
+        sr[e] = v.y;
+      }
+#pragma unroll
+      for (int e = 0; e < ITEMS; ++e)
+        if (sr[e] != sx[e]) coll |= (uint32_t)(((first ? at32(J.blk[0], sr[e]) : at64(pc, sr[e]).x) & kIdBits) != bb[e]);
+#pragma unroll
+      for (int e = 0; e < ITEMS; ++e)
+        if (state(e) < n) pn[state(e)] = make_uint2(new_id(e), nx[e]);
+      if (!finish(coll)) break;
+      if (sum >> kCollShift) continue;
+      first = false;
+      if (!settle((uint32_t)(sum & kSumMask), 1ull << l)) break;
+      if (up) ++l;
+#pragma unroll
+      for (int e = 0; e < ITEMS; ++e) sx[e] = nx[e];
     }
+  };
+  // Several letters (or rows).  FIT: at most CH, whose successors and their
+  // blocks stay in registers.
+  auto multi_rounds = [&](auto fitc) {
+    constexpr bool fit = decltype(fitc)::value;
+    const uint32_t kp = knon;
+    uint32_t sc[fit ? CH : 1][ITEMS], b[fit ? CH : 1][ITEMS];
+    if constexpr (fit) {
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        const uint32_t* rp = (uint32_t)c < kp ? row((uint32_t)c) : nullptr;
+#pragma unroll
+        for (int e = 0; e < ITEMS; ++e) sc[c][e] = (rp && state(e) < n) ? at32(rp, state(e)) : 0u;
+      }
+    }
+    // longer signatures: the blocks gathered in the group step are kept for
+    // the comparison in the resolve step
+    uint32_t* rec = fit ? nullptr : J.rec;
+    while (true) {
+      if (!list && autom && knon >= 2 && rounds == J.auto_rounds) {
+        status = kFusedHandOff;  // still splitting: the host builds its closure letters
+        break;
+      }
+      if (rounds >= J.max_rounds) {
+        status = kFusedRoundCap;
+        break;
+      }
+      const uint32_t* bc = J.blk[cur];
+      uint32_t* bn = J.blk[cur ^ 1u];
+      uint64_t h[ITEMS];
+#pragma unroll
+      for (int e = 0; e < ITEMS; ++e) h[e] = mix(salt, own[e]);
+      if constexpr (fit) {
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+          for (int e = 0; e < ITEMS; ++e)
+            b[c][e] = ((uint32_t)c < kp && !(own[e] & kSingleBit)) ? at32(bc, sc[c][e]) & kIdBits : 0u;
+        clear_lds();
+        clear_old();
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+          if ((uint32_t)c < kp) {
+#pragma unroll
+            for (int e = 0; e < ITEMS; ++e) h[e] = mix(h[e], b[c][e]);
+          }
+      } else {
+        // chunks of CL letters; the next chunk's row entries go out before
+        // this chunk's gathers
+        uint32_t s[CL][ITEMS];
+#pragma unroll
+        for (int c = 0; c < CL; ++c) {
+          const uint32_t* rp = row((uint32_t)c);
+#pragma unroll
+          for (int e = 0; e < ITEMS; ++e) s[c][e] = (own[e] & kSingleBit) ? 0u : at32(rp, state(e));
+        }
+        clear_lds();
+        clear_old();
+        for (uint32_t t0 = 0; t0 < kp; t0 += CL) {
+          uint32_t sn[CL][ITEMS], v[CL][ITEMS];
+#pragma unroll
+          for (int c = 0; c < CL; ++c) {
+            const uint32_t* rp = row(min(t0 + CL + c, kp - 1u));
+#pragma unroll
+            for (int e = 0; e < ITEMS; ++e) sn[c][e] = (own[e] & kSingleBit) ? 0u : at32(rp, state(e));
+          }
+#pragma unroll
+          for (int c = 0; c < CL; ++c)
+#pragma unroll
+            for (int e = 0; e < ITEMS; ++e) v[c][e] = (own[e] & kSingleBit) ? 0u : at32(bc, s[c][e]) & kIdBits;
+#pragma unroll
+          for (int c = 0; c < CL; ++c)
+            if (t0 + c < kp) {
+#pragma unroll
+              for (int e = 0; e < ITEMS; ++e) {
+                h[e] = mix(h[e], v[c][e]);
+                if (rec && !(own[e] & kSingleBit)) rec[(size_t)(t0 + c) * n + state(e)] = v[c][e];
+              }
+            }
+#pragma unroll
+          for (int c = 0; c < CL; ++c)
+#pragma unroll
+            for (int e = 0; e < ITEMS; ++e) s[c][e] = sn[c][e];
+        }
+      }
+      group(h);
+      if (!sync.wait(0, sum)) {
+        status = kGridAborted;
+        break;
+      }
+
+      // ---- resolve
+      read_slots();
+      uint32_t coll = 0;
+      bool chk[ITEMS];
+#pragma unroll
+      for (int e = 0; e < ITEMS; ++e) {
+        chk[e] = slot[e] != kNoSlot && r[e] != state(e);
+        if (chk[e]) coll |= (uint32_t)(at32(bc, r[e]) != own[e]);
+      }
+      if constexpr (fit) {
+        uint32_t o[CH][ITEMS];
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+          if ((uint32_t)c < kp) {
+            const uint32_t* rp = row((uint32_t)c);
+#pragma unroll
+            for (int e = 0; e < ITEMS; ++e) o[c][e] = chk[e] ? at32(rp, r[e]) : 0u;
+          }
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+          if ((uint32_t)c < kp) {
+#pragma unroll
+            for (int e = 0; e < ITEMS; ++e)
+              if (chk[e]) coll |= (uint32_t)((at32(bc, o[c][e]) & kIdBits) != b[c][e]);
+          }
+      } else if (rec) {
+        for (uint32_t t0 = 0; t0 < kp; t0 += CL) {
+          uint32_t x[CL][ITEMS], y[CL][ITEMS];
+#pragma unroll
+          for (int c = 0; c < CL; ++c) {
+            const uint32_t* rp = rec + (size_t)min(t0 + c, kp - 1u) * n;
+#pragma unroll
+            for (int e = 0; e < ITEMS; ++e) {
+              x[c][e] = chk[e] ? at32(rp, state(e)) : 0u;
+              y[c][e] = chk[e] ? at32(rp, r[e]) : 0u;
+            }
+          }
+#pragma unroll
+          for (int c = 0; c < CL; ++c)
+#pragma unroll
+            for (int e = 0; e < ITEMS; ++e) coll |= (uint32_t)(x[c][e] != y[c][e]);
+        }
+      } else {  // no room for records: both signatures gathered again
+        for (uint32_t t = 0; t < kp; ++t) {
+          const uint32_t* rp = row(t);
+#pragma unroll
+          for (int e = 0; e < ITEMS; ++e)
+            if (chk[e])
+              coll |= (uint32_t)((at32(bc, at32(rp, r[e])) & kIdBits) != (at32(bc, at32(rp, state(e))) & kIdBits));
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < ITEMS; ++e)
+        if (state(e) < n) bn[state(e)] = new_id(e);
+      if (!finish(coll)) break;
+      if (sum >> kCollShift) continue;
+      if (!settle((uint32_t)(sum & kSumMask), 1ull)) break;
+    }
+  };
+  if (status == kFusedOk) {
+    if (dbl) doubling_rounds();
+    else if (knon <= (uint32_t)CH) multi_rounds(std::true_type{});
+    else multi_rounds(std::false_type{});
+  }
+
+  if (status == kFusedOk) {
+    // ---- canonical numbering by least member (J.rank is free by now)
+    uint32_t* out = reinterpret_cast<uint32_t*>(J.out);
     if (count == n) {
 #pragma unroll
       for (int e = 0; e < ITEMS; ++e) {
-        const uint32_t q = base + (uint32_t)(e * kT) + tid;
+        const uint32_t q = state(e);
         if (q < n) {
           out[q] = q;
           if (J.want_ids) J.blk[0][q] = q;
@@ -638,8 +751,7 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
       unsigned long long m[ITEMS];
 #pragma unroll
       for (int e = 0; e < ITEMS; ++e) {
-        const uint32_t q = base + (uint32_t)(e * kT) + tid;
-        m[e] = __ballot(q < n && id[e] == q);
+        m[e] = __ballot(state(e) < n && (own[e] & kIdBits) == state(e));
         if (lane == 0) s_w[e * kWavesT + wave] = (uint32_t)__popcll(m[e]);
       }
       __syncthreads();
@@ -659,23 +771,21 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
         }
       }
       __syncthreads();
-      uint32_t* rank = J.lvl[0];
+      uint32_t* rank = J.rank;
 #pragma unroll
-      for (int e = 0; e < ITEMS; ++e) {
-        const uint32_t q = base + (uint32_t)(e * kT) + tid;
+      for (int e = 0; e < ITEMS; ++e)
         if ((m[e] >> lane) & 1ull)
-          rank[q] = s_w[e * kWavesT + wave] + (uint32_t)__popcll(m[e] & ((1ull << lane) - 1ull));
-      }
+          rank[state(e)] = s_w[e * kWavesT + wave] + (uint32_t)__popcll(m[e] & ((1ull << lane) - 1ull));
       if (!sync.wait(0, sum)) {
         status = kGridAborted;
       } else {
 #pragma unroll
         for (int e = 0; e < ITEMS; ++e) {
-          const uint32_t q = base + (uint32_t)(e * kT) + tid;
+          const uint32_t q = state(e);
           if (q >= n) continue;
-          const uint32_t c = rank[id[e]];
+          const uint32_t c = at32(rank, own[e] & kIdBits);
           out[q] = c;
-          if (J.want_ids) J.blk[0][q] = id[e];
+          if (J.want_ids) J.blk[0][q] = own[e] & kIdBits;
           if (q == J.q0) J.res->initial_block = c;
         }
       }
@@ -697,6 +807,14 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
 
 }  // namespace
 
+// 1,024 threads and the fewest states per thread that fit the CUs: more
+// workgroups with fewer states each beat fewer barrier arrivals (n = 150,000
+// chain: 314 us with 147 workgroups of one state per thread, 399 with 74 of
+// two), while 512 or 256 threads for small n changed nothing.  Above four
+// states per thread the registers spill, whose dirty lines every barrier has
+// to write back, and the gathers no longer fit the caches: random DFAs of
+// 2^21 states took 790 us against the round engine's 600 (at 2^20: 332
+// against 415), so larger instances stay with the round engine.
 bool grid_shape(uint32_t n, uint32_t cus, uint32_t* items, uint32_t* wgs) {
   uint32_t it = 1;
   while (it <= kGridMaxItems && (uint64_t)it * kGridThreads * cus < n) it *= 2;
@@ -711,8 +829,7 @@ void launch_grid(const GridJob& J, uint32_t items, uint32_t wgs, hipStream_t s) 
   switch (items) {
     case 1: hipLaunchKernelGGL(k_grid<1>, g, b, 0, s, J); break;
     case 2: hipLaunchKernelGGL(k_grid<2>, g, b, 0, s, J); break;
-    case 4: hipLaunchKernelGGL(k_grid<4>, g, b, 0, s, J); break;
-    default: hipLaunchKernelGGL(k_grid<8>, g, b, 0, s, J); break;
+    default: hipLaunchKernelGGL(k_grid<4>, g, b, 0, s, J); break;
   }
 }
 

@@ -210,9 +210,8 @@ void launch_fused(const FusedJob* jobs, FusedRes* res, uint32_t njobs, int cls, 
 // reports kGridAborted and has written nothing but scratch (or correct output
 // entries): the instance then takes another path.
 constexpr uint32_t kGridThreads = 1024;
-constexpr uint32_t kGridMaxItems = 8;  // states per thread
+constexpr uint32_t kGridMaxItems = 4;  // states per thread
 constexpr uint32_t kGridMinStates = 1024;
-constexpr uint32_t kGridMaxStates = 1u << 21;
 struct alignas(128) GridWord {
   unsigned long long v;
 };
@@ -236,7 +235,8 @@ struct GridJob {
   uint32_t levels, auto_rounds, max_rounds;  // as in FusedJob
   uint32_t S;                    // table slots, more than n, a multiple of 8
   uint32_t* blk[2];              // n block ids each
-  uint32_t* lvl[2];              // n entries each: doubling levels, ranks at the end
+  uint2* pr[2];                  // n (block id, successor) pairs each: doubling rounds
+  uint32_t* rank;                // n words, written once the rounds are over (may be pr[0])
   unsigned long long* table[2];  // S slots each, table[1] right behind table[0]
   uint32_t* rec;                 // signature letters x n words, or null
   uint32_t* wgw;                 // two words per workgroup
@@ -253,7 +253,7 @@ struct GridJob {
 };
 // Signature letters whose blocks a thread keeps in registers between the
 // steps of a round; records (GridJob::rec) serve longer signatures.
-inline uint32_t grid_letters_kept(uint32_t items) { return items >= 8 ? 2u : (items == 4 ? 4u : 8u); }
+inline uint32_t grid_letters_kept(uint32_t items) { return 8u / items; }
 // States per thread and workgroups for n states on a device of `cus` CUs;
 // false if that is more than the kernel takes.
 bool grid_shape(uint32_t n, uint32_t cus, uint32_t* items, uint32_t* wgs);
