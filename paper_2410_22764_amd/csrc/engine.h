@@ -134,6 +134,7 @@ class Engine {
   // not apply or gave up, and the call goes on through the round engine.
   int grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, uint64_t max_rounds, hipStream_t s,
                std::vector<InstOutcome>& res, bool& done);
+  int ensure_gbar();
   bool grid_applies(const InstInput& x, const dfamin_opts& opts, uint32_t* items, uint32_t* wgs) const;
   int ensure(DevBuf& b, size_t bytes);
   int ensure_host(HostBuf& b, size_t bytes);

@@ -264,8 +264,7 @@ int Engine::set_fixed_region(void* base, size_t cap, size_t host_bytes) {
   HostBuf* hb[] = {&h_ctrl_, &h_flags_, &h_results_, &h_counts_, &h_jobs_, &h_rb_, &h_qdbl_,
                    &stage_[0].buf, &stage_[1].buf, &h_fjobs_, &h_fres_, &h_gres_};
   for (HostBuf* b : hb) TRY(ensure_host(*b, host_bytes));
-  TRY(ensure(d_gbar_, sizeof(GridBar)));
-  HIP(hipMemset(d_gbar_.p, 0, sizeof(GridBar)));
+  TRY(ensure_gbar());
   if (!ev_rb_) HIP(hipEventCreateWithFlags(&ev_rb_, hipEventDisableTiming));
   fixed_base_ = static_cast<char*>(base);
   fixed_cap_ = cap;
@@ -1477,33 +1476,101 @@ int Engine::minimal_dfa(const dfamin_opts& opts, hipStream_t s, uint32_t nb, uin
   uint32_t* frontier = d_act_.as<uint32_t>();
   uint32_t* next = d_act2_.as<uint32_t>();
   uint32_t* counter = d_counts_.as<uint32_t>();
-  // start: visited = {q0}, frontier = [q0]
   uint32_t* hj = h_jobs_.as<uint32_t>();
-  hj[0] = 1u << (x.q0 & 31u);
-  hj[1] = x.q0;
-  HIP(hipMemsetAsync(visited, 0, words * 4, s));
-  HIP(hipMemcpyAsync(visited + (x.q0 >> 5), &hj[0], 4, hipMemcpyHostToDevice, s));
-  HIP(hipMemcpyAsync(frontier, &hj[1], 4, hipMemcpyHostToDevice, s));
+  // start: visited = {q0}, frontier = [q0]
+  auto start = [&]() -> int {
+    hj[0] = 1u << (x.q0 & 31u);
+    hj[1] = x.q0;
+    TRY(queue_fill(visited, 0, words * 4, s));
+    TRY(flush_segs(s));
+    TRY(upload(visited + (x.q0 >> 5), &hj[0], 4, s));
+    return upload(frontier, &hj[1], 4, s);
+  };
   // the rows followed: the non-identity letters, then their closure levels
   std::vector<uint64_t> rows = inst_rows_[0];
   bool closure_used = has_closure_[0] != 0;
   auto upload_rows = [&]() -> int {
     TRY(ensure(d_bfs_rows_, std::max<size_t>(rows.size(), 1) * 8));
-    if (!rows.empty())
-      HIP(hipMemcpyAsync(d_bfs_rows_.p, rows.data(), rows.size() * 8, hipMemcpyHostToDevice, s));
-    return DFAMIN_OK;
+    return rows.empty() ? DFAMIN_OK : upload(d_bfs_rows_.p, rows.data(), rows.size() * 8, s);
   };
   TRY(upload_rows());
   uint32_t fcount = 1, reached = 1, levels = 0;
-  while (fcount) {
-    if (levels == kBfsLevelsBeforeClosure && !closure_used && !nonid_[0].empty()) {
-      // a long path: closure letters (words over Sigma) shorten it
-      TRY(build_closure({0u}, opts, s));
-      rows = inst_rows_[0];
-      closure_used = true;
-      TRY(upload_rows());
+  // a long path: closure letters (words over Sigma) shorten it
+  auto join_closure = [&]() -> int {
+    TRY(build_closure({0u}, opts, s));
+    rows = inst_rows_[0];
+    closure_used = true;
+    return upload_rows();
+  };
+  const bool may_join = !closure_used && !nonid_[0].empty();
+  bool by_grid = false;
+  {
+    // Levels on the device (k_bfs_grid), in one launch, or two where the
+    // closure's rows join in between.  128 workgroups: a frontier of a
+    // quarter million states still has two per thread, and a barrier of
+    // twice as many costs 3 us more a level.
+    const uint32_t wgs = std::min<uint32_t>({128u, ctx_->cus, (n + kGridThreads - 1) / kGridThreads});
+    GridLease lease;
+    const char* knob = std::getenv("DFAMIN_GRID_MAX_STATES");
+    if (wgs && !(knob && std::atol(knob) <= 0) && lease.take(ctx_->device, wgs, ctx_->cus)) {
+      TRY(ensure_gbar());
+      TRY(ensure_host(h_gres_, sizeof(GridRes)));
+      TRY(ensure(d_qdbl_, 256));
+      BfsJob B{};
+      B.seed = 1;
+      B.q0 = x.q0;
+      B.words = words;
+      B.list[0] = frontier;
+      B.list[1] = next;
+      B.visited = visited;
+      B.counter = d_qdbl_.as<uint32_t>();
+      B.bar = d_gbar_.as<GridBar>();
+      B.res = static_cast<GridRes*>(h_gres_.dp);
+      B.fcount = B.reached = 1;
+      GridRes* h = h_gres_.as<GridRes>();
+      while (true) {
+        B.rows = d_bfs_rows_.as<uint64_t>();
+        B.nrows = (uint32_t)rows.size();
+        B.max_levels = may_join && !closure_used ? kBfsLevelsBeforeClosure : 0xffffffffu;
+        *h = GridRes{};
+        h->status = kGridAborted;
+        prof.begin(s, "bfs_level", 4.0 * n * (1.0 + 3.0 * rows.size()));
+        launch_bfs_grid(B, wgs, s);
+        prof.end(s);
+        HIP(hipGetLastError());
+        HIP(stream_wait(s));
+        stage_idle();
+        prof.collect();
+        by_grid = !h->aborted && h->status == kFusedOk;
+        if (!by_grid || !h->num_blocks) break;
+        B.fcount = h->num_blocks;
+        B.levels = h->rounds;
+        B.reached = h->refine_rounds;
+        B.cur = h->cur;
+        B.seed = 0;
+        TRY(join_closure());
+      }
+      reached = h->refine_rounds;
+      levels = h->rounds;
     }
-    HIP(hipMemsetAsync(counter, 0, 4, s));
+  }
+  if (!by_grid) {
+    if (levels || reached != 1) {  // gave up: from the start, level by level
+      levels = 0;
+      reached = 1;
+      if (closure_used && may_join) {
+        rows.clear();
+        for (uint32_t a : nonid_[0]) rows.push_back(reinterpret_cast<uint64_t>(x.delta) + 4ull * a * n);
+        closure_used = false;
+        TRY(upload_rows());
+      }
+    }
+    TRY(start());
+  }
+  while (!by_grid && fcount) {
+    if (levels == kBfsLevelsBeforeClosure && !closure_used && !nonid_[0].empty()) TRY(join_closure());
+    TRY(queue_fill(counter, 0, 4, s));
+    TRY(flush_segs(s));
     prof.begin(s, "bfs_level", 4.0 * fcount * (1.0 + 3.0 * rows.size()));
     launch_bfs_level(d_bfs_rows_.as<uint64_t>(), (uint32_t)rows.size(), frontier, fcount, visited, next,
                      counter, s);
@@ -1511,6 +1578,7 @@ int Engine::minimal_dfa(const dfamin_opts& opts, hipStream_t s, uint32_t nb, uin
     HIP(hipGetLastError());
     HIP(hipMemcpyAsync(&hj[2], counter, 4, hipMemcpyDeviceToHost, s));
     HIP(stream_wait(s));
+    stage_idle();
     prof.collect();
     fcount = hj[2];
     reached += fcount;
@@ -1521,7 +1589,8 @@ int Engine::minimal_dfa(const dfamin_opts& opts, hipStream_t s, uint32_t nb, uin
   uint32_t* sel = d_nb_.as<uint32_t>();
   uint32_t* rid = d_rank_.as<uint32_t>();
   uint32_t* rep = d_slot_of_.as<uint32_t>();
-  HIP(hipMemsetAsync(sel, 0xff, (size_t)nb * 4, s));
+  TRY(queue_fill(sel, 0xff, (size_t)nb * 4, s));
+  TRY(flush_segs(s));
   TRY(ensure(d_status_, ((size_t)scan_tiles(nb, scan_items_for(nb)) + 1) * 8));
   prof.begin(s, "quotient", (double)n * 12.0 + (double)nb * (16.0 + 8.0 * k));
   launch_quotient(n, k, nb, x.delta, x.accept, d_block_.as<uint32_t>(), x.out, visited, sel, rid, rep,
@@ -1676,6 +1745,13 @@ bool Engine::grid_applies(const InstInput& x, const dfamin_opts& opts, uint32_t*
   return grid_shape(x.n, ctx_->cus, items, wgs);
 }
 
+int Engine::ensure_gbar() {
+  if (d_gbar_.p) return DFAMIN_OK;
+  TRY(ensure(d_gbar_, sizeof(GridBar)));
+  HIP(hipMemset(d_gbar_.p, 0, sizeof(GridBar)));
+  return check_hip(hipDeviceSynchronize());  // (set-up, once per engine: calls come on any stream)
+}
+
 int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, uint64_t max_rounds, hipStream_t s,
                      std::vector<InstOutcome>& res, bool& done) {
   done = false;
@@ -1686,10 +1762,7 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
   if (!lease.take(ctx_->device, wgs, ctx_->cus)) return DFAMIN_OK;
   const size_t n = x.n;
   const uint32_t S = (uint32_t)((4 * n + 7) & ~size_t(7));  // (a quarter full: few home slots are taken)
-  if (!d_gbar_.p) {
-    TRY(ensure(d_gbar_, sizeof(GridBar)));
-    HIP(hipMemset(d_gbar_.p, 0, sizeof(GridBar)));
-  }
+  TRY(ensure_gbar());
   TRY(ensure(d_block_, n * 4));
   TRY(ensure(d_nb_, n * 4));
   TRY(ensure(d_act_, n * 8));
