@@ -1636,9 +1636,9 @@ int Engine::fused_issue(const std::vector<InstInput>& in, const std::vector<uint
   // jobs grouped by size class, largest class first
   FusedJob* hj = h_fjobs_.as<FusedJob>();
   fused_pos_.assign(F, 0);
-  uint32_t at = 0, start[4] = {0, 0, 0, 0};
+  uint32_t at = 0, start[kFusedClasses] = {};
   double bytes = 0;
-  for (int cls = 2; cls >= 0; --cls) {
+  for (int cls = kFusedClasses - 1; cls >= 0; --cls) {
     start[cls] = at;
     for (size_t w = 0; w < F; ++w) {
       const InstInput& x = in[which[w]];
@@ -1662,7 +1662,6 @@ int Engine::fused_issue(const std::vector<InstInput>& in, const std::vector<uint
       bytes += 4.0 * x.n * x.k + x.n / 8.0 + 4.0 * x.n;
     }
   }
-  start[3] = at;
   // The kernels write their results straight into the mapped page-locked
   // buffer the host reads after its wait; one job travels as a kernel
   // argument, so a single small instance costs one launch and no copies.
@@ -1673,8 +1672,8 @@ int Engine::fused_issue(const std::vector<InstInput>& in, const std::vector<uint
   if (F == 1) {
     launch_fused(nullptr, res, 1, fused_class(hj[0].n), s, &hj[0]);
   } else {
-    for (int cls = 2; cls >= 0; --cls) {
-      const uint32_t b = start[cls], e = cls == 0 ? start[3] : start[cls - 1];
+    for (int cls = kFusedClasses - 1; cls >= 0; --cls) {
+      const uint32_t b = start[cls], e = cls == 0 ? at : start[cls - 1];
       launch_fused(d_fjobs_.as<FusedJob>() + b, res + b, e - b, cls, s);
     }
   }

@@ -25,6 +25,8 @@
 #include "../../include/dfamin.h"
 #include "internal.h"
 
+#include <type_traits>
+
 namespace dfamin {
 
 namespace {
@@ -63,58 +65,73 @@ __device__ __forceinline__ uint32_t mix_final(uint32_t h) {
   return h ^ (h >> 16);
 }
 
-// The grouping table is probed a bucket of kBucket consecutive slots at a
-// time (one 16-byte LDS read): a state looks for its group among the
-// bucket's occupied slots and otherwise claims the bucket's first empty
-// slot, moving on to the next bucket only when one is full.  A wave then
-// waits for few probe steps, where single-slot linear probing at this load
-// factor lets one lane of the wave run through a long cluster.
-constexpr uint32_t kBucket = 4;
-// states of a thread whose successors are loaded together (one or two
-// signature letters)
-constexpr int kChunk = 4;
+// Grouping by minimum.  A round's states all throw (hash fragment, state id)
+// words at a table with one LDS minimum each -- no answer is waited for --
+// and read their slot back after a barrier: where the fragment is theirs the
+// slot holds their group's least member, which is confirmed on the full
+// signature; a state whose slot went to a smaller fragment (or whose
+// confirmation fails) throws again at another slot.  At 16,384 states, of
+// which most form groups of their own, three throws place all but a few
+// hundred, about 12 us; claiming slots with a compare-and-swap and probing on,
+// one answer after another, took 38 us of a 46 us round.
+//
+// Slot word: bits 31..17 a 15-bit fragment, bits 16..1 the state id, bit 0
+// set once another member has found the slot's state (after the throws, so
+// that it does not take part in the minimum).
+constexpr uint32_t kEmpty = 0xFFFFFFFFu;
+constexpr uint32_t kThrows = 6;  // per hash of the signatures; then a new one
 
-// Slot word: bits 31..16 a 16-bit fragment of the signature hash, bits
-// 15..1 the least state id + 1 of the group, bit 0 set once a second state
-// joined it (0 = empty slot).
-constexpr uint32_t kFragShift = 16;
-constexpr uint32_t kIdMask = 0x7FFFu;  // (word >> 1) & kIdMask = least id + 1
-constexpr uint32_t kShared = 1u;
-// blk[q]: bits 13..0 the block id (least member), bit 15 set when that block
-// is a single state, which can never split again: such a state skips the
-// grouping of later rounds and stays its own block.
-constexpr uint16_t kSingle = 0x8000u;
-constexpr uint16_t kBlkMask = 0x3FFFu;
+// row[i] through a uniform base and a 32-bit offset register
+__device__ __forceinline__ uint32_t ld(const uint32_t* __restrict__ row, uint32_t i) {
+  return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(row) + (i << 2));
+}
 
 template <int MAXN, int NT>
-__global__ void __launch_bounds__(NT) k_fused(const FusedJob* __restrict__ jobs, FusedRes* __restrict__ res,
+__global__ void __launch_bounds__(NT, 4) k_fused(const FusedJob* __restrict__ jobs, FusedRes* __restrict__ res,
                                               uint32_t njobs, FusedJob one) {
-  static_assert(MAXN % NT == 0 && MAXN <= (1 << 14) && (MAXN / NT) % kChunk == 0, "fused tile: ids fit 14 bits");
-  static_assert(MAXN / NT <= 32, "accept bits of a thread's states fit one word");
-  static_assert(((3u * MAXN) / 2u - 64u) % kBucket == 0, "table of whole buckets");
   constexpr int ITEMS = MAXN / NT;
   constexpr uint32_t NW = NT / 64;
-  // table slots: load factor at most 2/3; 64 slots fewer than 1.5 MAXN
-  // leave room for the shared words in 160 KB at MAXN = 16,384
-  constexpr uint32_t SMAX = (3u * MAXN) / 2u - 64u;
-  __shared__ uint16_t blk[MAXN];   // block id (least member) per state
-  __shared__ uint16_t lvl[MAXN];   // doubling: the closure level a^(2^built)
-  __shared__ __align__(16) uint32_t slot[SMAX];  // grouping table (buckets of kBucket slots); ranks at the end
-  __shared__ uint32_t sh[64];      // 0 bad, 1 non-identity letters, 2 min F, 3 min Q\F,
-                                   // 4/5 leaders (alternate rounds), 6 fault, 32.. wave totals
+  constexpr int LC = ITEMS >= 8 ? 1 : 8 / ITEMS;  // letters gathered together
+  static_assert(MAXN % NT == 0 && MAXN <= (1 << 16), "state ids are 16-bit in LDS");
+  static_assert(ITEMS <= 32, "a bit per state of a thread");
+  // table slots: 128 fewer than 1.5 MAXN leave room for the shared words in
+  // 160 KB at MAXN = 16,384
+  constexpr uint32_t SMAX = (3u * MAXN) / 2u - 128u;
+  static_assert(SMAX >= ITEMS * NW + MAXN / 2, "wave counts and 16-bit ranks fit the table");
+  // One struct, the 16-bit arrays first: an LDS access reaches 64 KB from its
+  // base register by an immediate offset, so a thread's states cost no
+  // address register each.
+  struct Lds {
+    uint16_t blk[MAXN];  // block id (least member) per state
+    uint16_t lvl[MAXN];  // doubling: the closure level a^(2^built); else labels
+    uint32_t sh[64];     // 0 bad, 1 non-identity letters, 2 min F, 3 min Q\F, 4/5 leaders (alternate
+                         // rounds), 8..10 states left after a throw
+    uint32_t slot[SMAX]; // grouping table; numbering scratch between rounds
+  };
+  __shared__ __align__(16) Lds lds;
+  uint16_t* const blk = lds.blk;
+  uint16_t* const lvl = lds.lvl;
+  uint32_t* const sh = lds.sh;
+  uint32_t* const slot = lds.slot;
   const uint32_t j = blockIdx.x;
   if (j >= njobs) return;
-  const FusedJob J = jobs ? jobs[j] : one;  // one job may come as an argument
+  // One job may come as an argument.  (Two statements: a pointer to either
+  // would put the job's fields, and every row address made from them, into
+  // vector registers.)
+  FusedJob J = one;
+  if (jobs) J = jobs[j];
   const uint32_t n = J.n, k = J.k, tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
   const uint32_t* __restrict__ delta = reinterpret_cast<const uint32_t*>(J.delta);
   const uint8_t* __restrict__ acc = reinterpret_cast<const uint8_t*>(J.accept);
+  auto state = [&](int i) { return tid + (uint32_t)i * NT; };
   FusedRes R{};
   if (tid == 0) {
     sh[0] = 0;
     sh[1] = 0;
     sh[2] = kNone;
     sh[3] = kNone;
-    sh[4] = sh[5] = sh[6] = 0;
+    sh[4] = sh[5] = 0;
+    sh[8] = sh[9] = sh[10] = 0;
   }
   __syncthreads();
 
@@ -122,36 +139,37 @@ __global__ void __launch_bounds__(NT) k_fused(const FusedJob* __restrict__ jobs,
   // Thread tid owns states tid + i*NT, i < ITEMS (n <= MAXN); its loads of
   // one row go out together, so each row costs one memory latency.
   uint32_t fbits = 0;  // accept bit of owned state i in bit i
+  uint32_t live = 0;   // bit i: owned state i exists and its block may still split
   {
     uint32_t bad = 0, nonid = 0;
-    for (uint32_t a = 0; a < k; ++a) {
-      const uint32_t* __restrict__ row = delta + (size_t)a * n;
-      uint32_t v[ITEMS];
+    for (uint32_t a = 0; a < k; a += LC) {
+      uint32_t v[LC][ITEMS];
 #pragma unroll
-      for (int i = 0; i < ITEMS; ++i) {
-        const uint32_t q = tid + (uint32_t)i * NT;
-        v[i] = q < n ? row[q] : q;
-      }
-      uint32_t d = 0;
+      for (int c = 0; c < LC; ++c) {
+        const uint32_t* __restrict__ row = delta + (size_t)min(a + c, k - 1u) * n;
 #pragma unroll
-      for (int i = 0; i < ITEMS; ++i) {
-        const uint32_t q = tid + (uint32_t)i * NT;
-        bad |= (uint32_t)(q < n && v[i] >= n);
-        d |= (uint32_t)(v[i] != q);
+        for (int i = 0; i < ITEMS; ++i) v[c][i] = state(i) < n ? ld(row + i * NT, tid) : state(i);
       }
-      if (d) nonid |= 1u << a;
+#pragma unroll
+      for (int c = 0; c < LC; ++c) {
+        uint32_t d = 0;
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+          bad |= (uint32_t)(state(i) < n && v[c][i] >= n);
+          d |= (uint32_t)(v[c][i] != state(i));
+        }
+        if (d) nonid |= 1u << min(a + c, k - 1u);
+      }
     }
     uint8_t ab[ITEMS];
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-      const uint32_t q = tid + (uint32_t)i * NT;
-      ab[i] = q < n ? acc[q >> 3] : 0u;
-    }
+    for (int i = 0; i < ITEMS; ++i) ab[i] = state(i) < n ? acc[state(i) >> 3] : 0u;
     uint32_t mf = kNone, mn = kNone;
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
-      const uint32_t q = tid + (uint32_t)i * NT;
+      const uint32_t q = state(i);
       if (q >= n) continue;
+      live |= 1u << i;
       if ((ab[i] >> (q & 7)) & 1u) {
         mf = min(mf, q);
         fbits |= 1u << i;
@@ -178,76 +196,74 @@ __global__ void __launch_bounds__(NT) k_fused(const FusedJob* __restrict__ jobs,
     }
     return;
   }
-  const uint32_t mask = sh[1];
+  auto uniform = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane(v); };
+  const uint32_t mask = uniform(sh[1]);
   const uint32_t knon = __popc(mask);
   const bool autom = J.closure == DFAMIN_CLOSURE_AUTO;
   const bool dbl = autom && knon == 1;
-  const uint32_t minF = sh[2], minN = sh[3];
-  // the first two non-identity letters
-  const uint32_t l0 = mask ? (uint32_t)__ffs(mask) - 1u : 0u;
-  const uint32_t m1 = mask & (mask - 1u);
-  const uint32_t l1 = m1 ? (uint32_t)__ffs(m1) - 1u : 0u;
+  const uint32_t minF = uniform(sh[2]), minN = uniform(sh[3]);
+  const uint32_t* __restrict__ rowA = delta + (size_t)(mask ? __ffs(mask) - 1 : 0) * n;  // the doubling letter
   // ---- initial partition {F, Q\F}; ids are least members (Section 3.2)
   uint32_t count = (minF < n ? 1u : 0u) + (minN < n ? 1u : 0u);
 #pragma unroll
   for (int i = 0; i < ITEMS; ++i) {
-    const uint32_t q = tid + (uint32_t)i * NT;
-    if (q >= n) continue;
+    if (!((live >> i) & 1u)) continue;
     const bool f = (fbits >> i) & 1u;
-    blk[q] = (uint16_t)(f ? minF : minN);
+    blk[state(i)] = (uint16_t)(f ? minF : minN);
     // a doubling instance keeps its closure level in lvl[]; any other
     // starts with its accept bit there, the exact label of its class
-    lvl[q] = dbl ? (uint16_t)delta[(size_t)l0 * n + q] : (uint16_t)f;
+    lvl[state(i)] = dbl ? (uint16_t)ld(rowA + i * NT, tid) : (uint16_t)f;
   }
-  // > n slots, so an empty one always exists
-  const uint32_t S = min(SMAX, max(64u, (n + n / 2u + kBucket - 1u) & ~(kBucket - 1u)));
-  const uint32_t NB = S / kBucket;  // < 2^16: the bucket comes from the low half of the hash,
-                                    // the fragment from the high half
+  // slots of a hash round: up to eight per state (a small instance's throws
+  // then nearly all hit), 1.5 per state at MAXN
+  const uint32_t S = min(SMAX, max(64u, 8u * n));
   uint32_t rounds = 0, refine = 0, built = 0, used = 0;
   uint64_t jlen = 0;  // this partition is P_jlen (states agree on words of length <= jlen)
   // Exact-key rounds: while the signature in labels of lw bits each (block
   // numbers 0..B-1, or the accept bit in the first round) fits in
-  // floor(log2 S) bits, it is itself the slot index: no hashing, no
-  // comparison of signatures.  lvl[] then holds each state's label.
+  // floor(log2 S) bits, it is itself the slot index: one throw, no fragment,
+  // no comparison of signatures.  lvl[] then holds each state's label.
   const uint32_t lgS = 31u - (uint32_t)__clz(S);
   uint32_t lw = 1;
-  // a direct round needs 2^bits table slots and n 16-bit keys behind them
-  auto fits_direct = [&](uint32_t bits) {
-    return !dbl && bits <= lgS && bits <= 14u && (4u << bits) + 2u * n <= 4u * SMAX;
-  };
-  bool direct_next = fits_direct((knon + 1u) * lw);
-  // rank of each block's least member among the least members (states in
-  // order), into slot[p] for every state p
-  auto rank_leaders = [&]() {
-    const uint32_t base = tid * (uint32_t)ITEMS;
-    uint32_t c = 0;
+  auto fits_direct = [&](uint32_t bits) { return !dbl && bits <= lgS; };
+  bool direct = fits_direct((knon + 1u) * lw);
+  uint32_t was = live;  // live at the start of the round
+  // Number of least members below state(i), for each owned i that is one
+  // (states in order): wave counts in element order, then a scan by wave 0.
+  auto rank_leaders = [&](uint32_t (&rk)[ITEMS], uint32_t& lead) {
+    lead = 0;
+    unsigned long long m[ITEMS];
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
-      const uint32_t p = base + (uint32_t)i;
-      if (p < n && (blk[p] & kBlkMask) == p) ++c;
+      const bool is = state(i) < n && blk[state(i)] == state(i);
+      m[i] = __ballot(is);
+      lead |= (is ? 1u : 0u) << i;
+      if (lane == 0) slot[i * NW + wave] = (uint32_t)__popcll(m[i]);
     }
-    const uint32_t incl = wave_incl_scan(c);
-    if (lane == 63) sh[32 + wave] = incl;
     __syncthreads();
-    uint32_t off = 0;
-    for (uint32_t w = 0; w < wave; ++w) off += sh[32 + w];
-    uint32_t r = off + incl - c;
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-      const uint32_t p = base + (uint32_t)i;
-      if (p < n) {
-        slot[p] = r;
-        if ((blk[p] & kBlkMask) == p) ++r;
+    if (wave == 0) {
+      uint32_t run = 0;
+      for (uint32_t c0 = 0; c0 < ITEMS * NW; c0 += 64) {
+        const uint32_t c = c0 + lane, x = c < ITEMS * NW ? slot[c] : 0u;
+        const uint32_t incl = wave_incl_scan(x);
+        if (c < ITEMS * NW) slot[c] = run + incl - x;
+        run += __shfl(incl, 63);
       }
     }
     __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+      rk[i] = slot[i * NW + wave] + (uint32_t)__popcll(m[i] & ((1ull << lane) - 1ull));
   };
   int32_t status = kFusedOk;
   __syncthreads();
 
-  // ---- rounds
+  // ---- rounds (a copy of the loop for doubling instances: less to keep in
+  // registers than in one loop for both)
+  auto run = [&](auto dblc) {
+  constexpr bool DBL = decltype(dblc)::value;
   while (true) {
-    if (autom && !dbl && knon >= 2 && rounds == J.auto_rounds) {
+    if (!DBL && autom && knon >= 2 && rounds == J.auto_rounds) {
       status = kFusedHandOff;  // still splitting: its closure letters come from the round engine
       break;
     }
@@ -256,277 +272,245 @@ __global__ void __launch_bounds__(NT) k_fused(const FusedJob* __restrict__ jobs,
       break;
     }
     uint32_t l = 0;
-    if (dbl) {
+    if constexpr (DBL) {
       l = 63u - (uint32_t)__clzll(jlen + 1ull);
       if (l > J.levels) l = J.levels;
       for (; built < l; ++built) {  // level built+1 = level built, squared
         uint16_t nxt[ITEMS];
 #pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-          const uint32_t q = tid + (uint32_t)i * NT;
-          if (q < n) nxt[i] = lvl[lvl[q]];
-        }
+        for (int i = 0; i < ITEMS; ++i)
+          if (state(i) < n) nxt[i] = lvl[lvl[state(i)]];
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-          const uint32_t q = tid + (uint32_t)i * NT;
-          if (q < n) lvl[q] = nxt[i];
-        }
+        for (int i = 0; i < ITEMS; ++i)
+          if (state(i) < n) lvl[state(i)] = nxt[i];
         __syncthreads();
       }
     }
-    const bool direct = direct_next;
-    const uint32_t T = direct ? 1u << ((knon + 1u) * lw) : S;  // slots this round uses
-    for (uint32_t s = tid; s < T; s += NT) slot[s] = 0;
-    if (tid == 0) sh[4 + (rounds & 1u)] = 0;
-    __syncthreads();
-
-    // group: each state joins the slot of its signature; the slot keeps the
-    // group's least state (a hash fragment match is always confirmed on the
-    // full signature)
-    // a direct round keeps each state's key behind the table, 16 bits each
-    uint16_t* const keyat = reinterpret_cast<uint16_t*>(slot + T);
-    if (direct) {
-      // with one or two signature letters the successors of kChunk states
-      // of the thread are loaded together, as in the hash rounds
-      const bool pre = knon <= 2u;
-#pragma unroll 1
-      for (int c0 = 0; c0 < ITEMS; c0 += kChunk) {
-      uint32_t pf[kChunk];
-      if (pre) {
+    // key[i]: the exact key or the signature's hash; once the state has its
+    // group, its new id (least member)
+    uint32_t key[ITEMS];
+    const uint32_t T = !DBL && direct ? 1u << ((knon + 1u) * lw) : S;  // slots of this round
+    // few groups: most throws would lose to a word already there, and a
+    // read, which many lanes share, then saves the serialized minimum
+    const bool read_first = count * 8u < n;
+    uint32_t todo = live;
+    // Successors of the states to place, LC letters at a time (their loads
+    // go out together; small tiles have few per letter).
+    auto for_letters = [&](auto use) {
+      for (uint32_t mm = mask; mm;) {
+        uint32_t s[LC][ITEMS], cnt = 0;
 #pragma unroll
-        for (int i = 0; i < kChunk; ++i) {
-          const uint32_t q = tid + (uint32_t)(c0 + i) * NT;
-          pf[i] = 0;
-          if (q < n && knon > 0u) {
-            pf[i] = delta[(size_t)l0 * n + q];
-            if (knon > 1u) pf[i] |= delta[(size_t)l1 * n + q] << 16;
-          }
+        for (int c = 0; c < LC; ++c) {
+          if (!mm) break;
+          const uint32_t* row = delta + (size_t)(__ffs(mm) - 1) * n;
+          mm &= mm - 1u;
+          ++cnt;
+#pragma unroll
+          for (int i = 0; i < ITEMS; ++i) s[c][i] = ((todo >> i) & 1u) ? ld(row + i * NT, tid) : 0u;
         }
+        use(s, cnt);
       }
+    };
+    for (uint32_t hashes = 0; ; ++hashes) {
+      if (!DBL && direct) {
+        const uint16_t* lab = lvl;
 #pragma unroll
-      for (int i = 0; i < kChunk; ++i) {
-        const uint32_t q = tid + (uint32_t)(c0 + i) * NT;
-        if (q >= n || (blk[q] & kSingle)) continue;
-        uint32_t key = lvl[q];
-        if (pre) {
-          if (knon > 0u) key |= (uint32_t)lvl[pf[i] & 0xFFFFu] << lw;
-          if (knon > 1u) key |= (uint32_t)lvl[pf[i] >> 16] << (2u * lw);
-        } else {
+        for (int i = 0; i < ITEMS; ++i) key[i] = state(i) < n ? lab[state(i)] : 0u;
+        {
           uint32_t at = lw;
-          for (uint32_t mm = mask; mm; mm &= mm - 1u, at += lw)
-            key |= (uint32_t)lvl[delta[(size_t)(__ffs(mm) - 1) * n + q]] << at;
-        }
-        keyat[q] = (uint16_t)key;
-        const uint32_t want = (q + 1u) << 1;
-        uint32_t v = slot[key];
-        if (v == 0) {
-          v = atomicCAS(&slot[key], 0u, want);
-          if (v == 0) continue;  // a new group
-        }
-        if (((v >> 1) & kIdMask) - 1u > q) atomicMin(&slot[key], want | kShared);
-        else if (!(v & kShared)) atomicOr(&slot[key], kShared);
-      }
-      }
-    } else {
-    // (a plain instance keeps each state's slot in lvl[], which only
-    // doubling instances use; a doubling instance finds it again below).
-    // With one or two signature letters, the successors of kChunk states of
-    // the thread are loaded together first, packed two to a word.
-    const bool pre = !dbl && knon <= 2u;
-#pragma unroll 1
-    for (int c0 = 0; c0 < ITEMS; c0 += kChunk) {
-    uint32_t pf[kChunk];
-    if (pre) {
+          for_letters([&](const uint32_t (&s)[LC][ITEMS], uint32_t cnt) {
 #pragma unroll
-      for (int i = 0; i < kChunk; ++i) {
-        const uint32_t q = tid + (uint32_t)(c0 + i) * NT;
-        pf[i] = 0;
-        if (q < n && knon > 0u) {
-          pf[i] = delta[(size_t)l0 * n + q];
-          if (knon > 1u) pf[i] |= delta[(size_t)l1 * n + q] << 16;
-        }
-      }
-    }
+            for (int c = 0; c < LC; ++c) {
+              if ((uint32_t)c >= cnt) break;
 #pragma unroll
-    for (int i = 0; i < kChunk; ++i) {
-      const uint32_t q = tid + (uint32_t)(c0 + i) * NT;
-      if (q >= n || (blk[q] & kSingle)) continue;
-      const uint32_t own = blk[q];
-      uint32_t h = mix_step(0x6A09E667u, own);
-      if (dbl) {
-        h = mix_step(h, blk[lvl[q]] & kBlkMask);
-      } else if (pre) {
-        if (knon > 0u) h = mix_step(h, blk[pf[i] & 0xFFFFu] & kBlkMask);
-        if (knon > 1u) h = mix_step(h, blk[pf[i] >> 16] & kBlkMask);
+              for (int i = 0; i < ITEMS; ++i) key[i] |= (uint32_t)lab[s[c][i]] << at;
+              at += lw;
+            }
+          });
+        }
       } else {
-        for (uint32_t mm = mask; mm; mm &= mm - 1u) {
-          const uint32_t a = (uint32_t)__ffs(mm) - 1u;
-          h = mix_step(h, blk[delta[(size_t)a * n + q]] & kBlkMask);
-        }
-      }
-      h = mix_final(h);
-      const uint32_t frag = h >> kFragShift;
-      const uint32_t want = (frag << kFragShift) | ((q + 1u) << 1);
-      // the full signature of r equals that of q
-      auto same_as = [&](uint32_t r) {
-        if (blk[r] != own) return false;
-        if (dbl) return (blk[lvl[r]] & kBlkMask) == (blk[lvl[q]] & kBlkMask);
-        if (pre) {
-          bool eq = true;
-          if (knon > 0u)
-            eq = (blk[delta[(size_t)l0 * n + r]] & kBlkMask) == (blk[pf[i] & 0xFFFFu] & kBlkMask);
-          if (knon > 1u)
-            eq = eq && (blk[delta[(size_t)l1 * n + r]] & kBlkMask) == (blk[pf[i] >> 16] & kBlkMask);
-          return eq;
-        }
-        for (uint32_t mm = mask; mm; mm &= mm - 1u) {
-          const uint32_t a = (uint32_t)__ffs(mm) - 1u;
-          if ((blk[delta[(size_t)a * n + r]] & kBlkMask) != (blk[delta[(size_t)a * n + q]] & kBlkMask))
-            return false;
-        }
-        return true;
-      };
-      uint32_t b = (((h & 0xFFFFu) * NB) >> 16);
-      uint32_t pos = 0;
-      for (uint32_t steps = 0;; ++steps) {
-        if (steps >= (kBucket + 1u) * NB) {  // cannot happen (S > n); bounded all the same
-          sh[6] = 1;
-          break;
-        }
-        const uint4 w0 = *reinterpret_cast<const uint4*>(&slot[b * kBucket]);
-        const uint32_t w[kBucket] = {w0.x, w0.y, w0.z, w0.w};
-        uint32_t cand = 0, empties = 0;
+        const uint32_t seed = 0x6A09E667u + hashes * 0x9E3779B9u;
 #pragma unroll
-        for (int j = 0; j < (int)kBucket; ++j) {
-          if (w[j] == 0) empties |= 1u << j;
-          else if ((w[j] >> kFragShift) == frag) cand |= 1u << j;
+        for (int i = 0; i < ITEMS; ++i)
+          if ((todo >> i) & 1u) key[i] = mix_step(seed, blk[state(i)]);
+        if constexpr (DBL) {
+#pragma unroll
+          for (int i = 0; i < ITEMS; ++i)
+            if ((todo >> i) & 1u) key[i] = mix_step(key[i], blk[lvl[state(i)]]);
+        } else {
+          for_letters([&](const uint32_t (&s)[LC][ITEMS], uint32_t cnt) {
+#pragma unroll
+            for (int c = 0; c < LC; ++c) {
+              if ((uint32_t)c >= cnt) break;
+#pragma unroll
+              for (int i = 0; i < ITEMS; ++i)
+                if ((todo >> i) & 1u) key[i] = mix_step(key[i], blk[s[c][i]]);
+            }
+          });
         }
-        int hit = -1;
-        for (; cand; cand &= cand - 1u) {  // fragment matches, confirmed on the full signature
-          const int j = __ffs(cand) - 1;
-          // (an occupied slot changes only to a lower member of its group)
-          if (same_as(((slot[b * kBucket + (uint32_t)j] >> 1) & kIdMask) - 1u)) {
-            hit = j;
-            break;
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i)
+          if ((todo >> i) & 1u) key[i] = mix_final(key[i]);
+      }
+      bool left = true;
+      for (uint32_t t = 0; left && t < kThrows; ++t) {
+        for (uint32_t x = tid; x < T / 4u; x += NT)
+          reinterpret_cast<uint4*>(slot)[x] = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
+        if (tid < (T & 3u)) slot[(T & ~3u) + tid] = kEmpty;
+        __syncthreads();
+        // this throw's slot and fragment
+        // (the multiplier is made opaque in each of the three steps: the
+        // compiler would otherwise keep every state's slot and fragment from
+        // one step to the next, and spill)
+        uint32_t mul = 0x9E3779B1u + 0x3C6EF372u * t;  // odd: a bijection of h
+        asm volatile("" : "+s"(mul));
+        auto aim = [&](uint32_t h, uint32_t& pos, uint32_t& frag) {
+          if (!DBL && direct) {
+            pos = h;
+            frag = 0;
+          } else {
+            uint32_t y = h * mul;
+            y ^= y >> 16;
+            frag = min(y >> 17, 0x7FFEu);
+            pos = ((y & 0x1FFFFu) * T) >> 17;  // (T < 2^15)
           }
-        }
-        const int empty = empties ? __ffs(empties) - 1 : -1;
-        if (hit >= 0) {  // the group exists: mark it shared and keep its least member
-          pos = b * kBucket + (uint32_t)hit;
-          const uint32_t v = slot[pos];
-          if (((v >> 1) & kIdMask) - 1u > q) atomicMin(&slot[pos], want | kShared);  // same fragment
-          else if (!(v & kShared)) atomicOr(&slot[pos], kShared);
-          break;
-        }
-        if (empty >= 0) {  // claim the bucket's first empty slot; if another state
-                           // took it first, read the bucket again
-          pos = b * kBucket + (uint32_t)empty;
-          if (atomicCAS(&slot[pos], 0u, want) == 0u) break;
-          continue;
-        }
-        b = (b + 1u == NB) ? 0u : b + 1u;
-      }
-      if (!dbl) lvl[q] = (uint16_t)pos;
-    }
-    }
-    }
-    __syncthreads();
-    // new id = the group's least member (with the single-state mark);
-    // count the groups
-    uint32_t leaders = 0;
-    if (direct) {
-#pragma unroll 1
-      for (int i = 0; i < ITEMS; ++i) {
-        const uint32_t q = tid + (uint32_t)i * NT;
-        if (q >= n) continue;
-        if (blk[q] & kSingle) {
-          ++leaders;
-          continue;
-        }
-        const uint32_t v = slot[keyat[q]];
-        const uint32_t nb = ((v >> 1) & kIdMask) - 1u;
-        blk[q] = (uint16_t)(nb | ((v & kShared) ? 0u : kSingle));
-        leaders += (uint32_t)(nb == q);
-      }
-    } else if (!dbl) {
-#pragma unroll 1
-      for (int i = 0; i < ITEMS; ++i) {
-        const uint32_t q = tid + (uint32_t)i * NT;
-        if (q >= n) continue;
-        if (blk[q] & kSingle) {
-          ++leaders;
-          continue;
-        }
-        const uint32_t v = slot[lvl[q]];
-        const uint32_t nb = ((v >> 1) & kIdMask) - 1u;
-        blk[q] = (uint16_t)(nb | ((v & kShared) ? 0u : kSingle));
-        leaders += (uint32_t)(nb == q);
-      }
-    } else {
-      // the slot of each state's signature (own block, block of its level
-      // successor), found again by the same probe; blocks change only
-      // after every state has found its slot
-      uint16_t nbs[ITEMS];
+        };
 #pragma unroll
-      for (int i = 0; i < ITEMS; ++i) {
-        const uint32_t q = tid + (uint32_t)i * NT;
-        nbs[i] = 0;
-        if (q >= n || (blk[q] & kSingle)) continue;
-        const uint32_t own = blk[q], succ = blk[lvl[q]] & kBlkMask;
-        const uint32_t h = mix_final(mix_step(mix_step(0x6A09E667u, own), succ));
-        const uint32_t frag = h >> kFragShift;
-        uint32_t b = (((h & 0xFFFFu) * NB) >> 16);
-        for (uint32_t probes = 0; probes < S; ++probes) {
-          const uint32_t v = slot[b * kBucket + (probes % kBucket)];
-          if (v && (v >> kFragShift) == frag) {
-            const uint32_t r = ((v >> 1) & kIdMask) - 1u;
-            if (blk[r] == own && (blk[lvl[r]] & kBlkMask) == succ) {
-              nbs[i] = (uint16_t)(r | ((v & kShared) ? 0u : kSingle));
-              break;
+        for (int i = 0; i < ITEMS; ++i) {
+          if (!((todo >> i) & 1u)) continue;
+          uint32_t pos, frag;
+          aim(key[i], pos, frag);
+          const uint32_t word = (frag << 17) | (state(i) << 1);
+          if (!read_first || slot[pos] > word) atomicMin(&slot[pos], word);
+        }
+        __syncthreads();
+        asm volatile("" : "+s"(mul));
+        uint32_t reps = 0, cand = 0;  // owned states that are their slot's least member; that found one
+        uint32_t rep[ITEMS];
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+          rep[i] = 0;
+          if (!((todo >> i) & 1u)) continue;
+          uint32_t pos, frag;
+          aim(key[i], pos, frag);
+          const uint32_t v = slot[pos];
+          if ((v >> 17) != frag) continue;
+          rep[i] = (v >> 1) & 0xFFFFu;
+          if (rep[i] == state(i)) reps |= 1u << i;
+          else cand |= 1u << i;
+        }
+        // Confirmed on the full signature, a letter at a time for half the
+        // thread's states together (state by state, each one's row loads
+        // waited for, took 13 us of a 16,384-state round; now 5).
+        if ((DBL || !direct) && __any(cand != 0u)) {
+#pragma unroll
+          for (int i = 0; i < ITEMS; ++i)
+            if (((cand >> i) & 1u) && blk[rep[i]] != blk[state(i)]) cand &= ~(1u << i);
+          if constexpr (DBL) {
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i)
+              if (((cand >> i) & 1u) && blk[lvl[rep[i]]] != blk[lvl[state(i)]]) cand &= ~(1u << i);
+          } else {
+            constexpr int HALF = (ITEMS + 1) / 2;
+            for (uint32_t mm = mask; mm; mm &= mm - 1u) {
+              const uint32_t* row = delta + (size_t)(__ffs(mm) - 1) * n;
+#pragma unroll
+              for (int i0 = 0; i0 < ITEMS; i0 += HALF) {
+                uint32_t a[HALF], b[HALF];
+#pragma unroll
+                for (int i = 0; i < HALF; ++i) {
+                  const bool on = i0 + i < ITEMS && ((cand >> (i0 + i)) & 1u);
+                  a[i] = on ? ld(row, rep[i0 + i]) : 0u;
+                  b[i] = on ? ld(row + (i0 + i) * NT, tid) : 0u;
+                }
+#pragma unroll
+                for (int i = 0; i < HALF; ++i)
+                  if (blk[a[i]] != blk[b[i]]) cand &= ~(1u << (i0 + i));
+              }
             }
           }
-          if (probes % kBucket == kBucket - 1u) b = (b + 1u == NB) ? 0u : b + 1u;
         }
-      }
-      __syncthreads();
+        asm volatile("" : "+s"(mul));
 #pragma unroll
-      for (int i = 0; i < ITEMS; ++i) {
-        const uint32_t q = tid + (uint32_t)i * NT;
-        if (q >= n) continue;
-        if (blk[q] & kSingle) {
-          ++leaders;
-          continue;
+        for (int i = 0; i < ITEMS; ++i) {
+          if (!((cand >> i) & 1u)) continue;
+          uint32_t pos, frag;
+          aim(key[i], pos, frag);
+          if (!(slot[pos] & 1u)) atomicOr(&slot[pos], 1u);
+          key[i] = rep[i];
         }
-        blk[q] = nbs[i];
-        leaders += (uint32_t)((nbs[i] & kBlkMask) == q);
+        todo &= ~cand;
+        __syncthreads();
+        asm volatile("" : "+s"(mul));
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+          if (!((reps >> i) & 1u)) continue;
+          uint32_t pos, frag;
+          aim(key[i], pos, frag);
+          if (!(slot[pos] & 1u)) live &= ~(1u << i);  // alone: this block can never split
+          key[i] = state(i);
+        }
+        todo &= ~reps;
+        // (a word of its own per throw, cleared two throws ahead)
+        if (__any(todo != 0u) && lane == 0) sh[8 + t % 3u] = 1u;
+        __syncthreads();
+        left = uniform(sh[8 + t % 3u]) != 0u;
+        if (tid == 0) sh[8 + (t + 2u) % 3u] = 0u;
+      }
+      if (!left) break;
+      // signatures that share a whole hash: another one separates them.  (Every
+      // state finds its group in the end; the bound is only a backstop.)
+      if (hashes >= 64u) {
+        status = kFusedFault;
+        break;
       }
     }
+    if (status != kFusedOk) break;
+    // new id = the group's least member; count the groups.  (A state that was
+    // alone before this round keeps its own id.)
+    uint32_t leaders = 0;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+      const uint32_t q = state(i);
+      if (q >= n) continue;
+      if ((was >> i) & 1u) blk[q] = (uint16_t)key[i];
+      leaders += (uint32_t)(((was >> i) & 1u) ? key[i] == q : 1u);
+    }
+    was = live;
     leaders = wave_sum(leaders);
     if (lane == 0) atomicAdd(&sh[4 + (rounds & 1u)], leaders);
     __syncthreads();
-    const uint32_t cnew = sh[4 + (rounds & 1u)];
+    const uint32_t cnew = uniform(sh[4 + (rounds & 1u)]);
+    if (tid == 0) sh[4 + ((rounds + 1u) & 1u)] = 0;
     ++rounds;
-    if (sh[6]) {
-      status = kFusedFault;
-      break;
-    }
     if (cnew == count) break;  // no block split: stable
     ++refine;
     used = max(used, l);  // the highest level a splitting round read
     count = cnew;
-    jlen += dbl ? (1ull << l) : 1ull;
+    jlen += DBL ? (1ull << l) : 1ull;
     if (count == n) break;  // every block a singleton: stable without another round
     // the next round's labels: block numbers, if its signature fits
     const uint32_t wn = max(1u, 32u - (uint32_t)__clz(count - 1u));
-    direct_next = fits_direct((knon + 1u) * wn);
-    if (direct_next) {
-      rank_leaders();
-      for (uint32_t q = tid; q < n; q += NT) lvl[q] = (uint16_t)slot[blk[q] & kBlkMask];
+    if (!DBL) direct = fits_direct((knon + 1u) * wn);
+    if (!DBL && direct) {
+      uint32_t rk[ITEMS], lead;
+      rank_leaders(rk, lead);
+      uint16_t* ranks = reinterpret_cast<uint16_t*>(slot + ITEMS * NW);
+#pragma unroll
+      for (int i = 0; i < ITEMS; ++i)
+        if ((lead >> i) & 1u) ranks[state(i)] = (uint16_t)rk[i];
       __syncthreads();
+#pragma unroll
+      for (int i = 0; i < ITEMS; ++i)
+        if (state(i) < n) lvl[state(i)] = ranks[blk[state(i)]];
       lw = wn;
     }
+    __syncthreads();
   }
+  };
+  if (dbl) run(std::true_type{});
+  else run(std::false_type{});
   if (status != kFusedOk) {
     if (tid == 0) {
       R.status = status;
@@ -535,20 +519,34 @@ __global__ void __launch_bounds__(NT) k_fused(const FusedJob* __restrict__ jobs,
     return;
   }
 
-  // ---- canonical numbering: out[q] = rank of q's block's least member
-  rank_leaders();
+  // ---- canonical numbering: out[q] = rank of q's block's least member.
+  // The ranks take the least members' place in blk[] once every thread has
+  // its states' ids.
+  uint32_t id[ITEMS];
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) id[i] = state(i) < n ? blk[state(i)] : 0u;
+  const uint32_t id0 = blk[J.q0];
+  {
+    uint32_t rk[ITEMS], lead;
+    rank_leaders(rk, lead);  // (its barriers come before the writes below)
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+      if ((lead >> i) & 1u) blk[state(i)] = (uint16_t)rk[i];
+  }
+  __syncthreads();
   uint32_t* __restrict__ out = reinterpret_cast<uint32_t*>(J.out);
-  for (uint32_t q = tid; q < n; q += NT) out[q] = slot[blk[q] & kBlkMask];
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i)
+    if (state(i) < n) out[state(i)] = blk[id[i]];
   if (tid == 0) {
     R.status = kFusedOk;
     R.num_blocks = count;
-    R.initial_block = slot[blk[J.q0] & kBlkMask];
+    R.initial_block = blk[id0];
     R.refine_rounds = refine;
     R.levels_used = used;
     R.doubling = dbl ? 1u : 0u;
     res[j] = R;
   }
-  (void)NW;
 }
 
 }  // namespace
@@ -561,12 +559,23 @@ void launch_fused(const FusedJob* jobs, FusedRes* res, uint32_t njobs, int cls, 
     jobs = nullptr;
     njobs = 1;
   }
+  // Threads per class: as many as the states can use.  512 threads of four
+  // states beat 256 of eight (2,000 instances of up to 2,048 states: 380
+  // against 404 us a call), 1,024 of eight 512 of sixteen (up to 8,192: 632
+  // against 656).  One instance alone takes 1,024 threads from 513 states on
+  // (2,000 states, two letters: 43 us a call, with 256 threads 63).
+  const dim3 g(njobs);
   switch (cls) {
-    case 0: hipLaunchKernelGGL((k_fused<2048, 256>), dim3(njobs), dim3(256), 0, s, jobs, res, njobs, arg); break;
-    case 1: hipLaunchKernelGGL((k_fused<8192, 512>), dim3(njobs), dim3(512), 0, s, jobs, res, njobs, arg); break;
-    default:
-      hipLaunchKernelGGL((k_fused<16384, 1024>), dim3(njobs), dim3(1024), 0, s, jobs, res, njobs, arg);
+    case 0: hipLaunchKernelGGL((k_fused<512, 256>), g, dim3(256), 0, s, jobs, res, njobs, arg); break;
+    case 1:
+      if (one) hipLaunchKernelGGL((k_fused<2048, 1024>), g, dim3(1024), 0, s, jobs, res, njobs, arg);
+      else hipLaunchKernelGGL((k_fused<2048, 512>), g, dim3(512), 0, s, jobs, res, njobs, arg);
       break;
+    case 2:
+      if (one && one->n <= 4096) hipLaunchKernelGGL((k_fused<4096, 1024>), g, dim3(1024), 0, s, jobs, res, njobs, arg);
+      else hipLaunchKernelGGL((k_fused<8192, 1024>), g, dim3(1024), 0, s, jobs, res, njobs, arg);
+      break;
+    default: hipLaunchKernelGGL((k_fused<16384, 1024>), g, dim3(1024), 0, s, jobs, res, njobs, arg); break;
   }
 }
 

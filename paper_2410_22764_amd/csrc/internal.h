@@ -195,9 +195,11 @@ constexpr int32_t kFusedRoundCap = 3;  // max_rounds reached
 constexpr int32_t kFusedFault = 4;     // a bounded probe ran out (never expected)
 constexpr uint32_t kFusedMaxStates = 16384;
 constexpr uint32_t kFusedMaxLetters = 32;
-// size class of a fused instance: 0 up to 2,048 states (256 threads),
-// 1 up to 8,192 (512 threads), 2 up to 16,384 (1,024 threads, 160 KB of LDS)
-inline int fused_class(uint32_t n) { return n <= 2048 ? 0 : (n <= 8192 ? 1 : 2); }
+// size class of a fused instance: 0 up to 512 states (256 threads), 1 up to
+// 2,048 (512), 2 up to 8,192 (1,024), 3 up to 16,384 (1,024 threads, 160 KB
+// of LDS)
+constexpr int kFusedClasses = 4;
+inline int fused_class(uint32_t n) { return n <= 512 ? 0 : (n <= 2048 ? 1 : (n <= 8192 ? 2 : 3)); }
 // one (nullable): a single job passed by value (jobs is then ignored and
 // njobs taken as 1).  res may be mapped page-locked host memory.
 void launch_fused(const FusedJob* jobs, FusedRes* res, uint32_t njobs, int cls, hipStream_t s,
@@ -211,7 +213,10 @@ void launch_fused(const FusedJob* jobs, FusedRes* res, uint32_t njobs, int cls, 
 // entries): the instance then takes another path.
 constexpr uint32_t kGridThreads = 1024;
 constexpr uint32_t kGridMaxItems = 4;  // states per thread
-constexpr uint32_t kGridMinStates = 1024;
+// Below, one workgroup is faster (random, two letters: 4,000 states 56 us
+// against 79, 6,000 65 against 70, 8,192 76 against 79; chains 100 / 116,
+// 139 / 123, 157 / 130).
+constexpr uint32_t kGridMinStates = 6145;
 struct alignas(128) GridWord {
   unsigned long long v;
 };

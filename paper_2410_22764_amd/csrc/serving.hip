@@ -769,8 +769,8 @@ struct Serving::Impl {
     std::vector<FusedJob>& jobs = fb.jobs;
     jobs.assign(F, FusedJob{});
     fb.pos.assign(F, 0);
-    uint32_t at = 0, start[4] = {0, 0, 0, 0};
-    for (int cls = 2; cls >= 0; --cls) {
+    uint32_t at = 0, start[kFusedClasses] = {};
+    for (int cls = kFusedClasses - 1; cls >= 0; --cls) {
       start[cls] = at;
       for (size_t w = 0; w < F; ++w) {
         Resident* r = fb.fs[w];
@@ -792,8 +792,7 @@ struct Serving::Impl {
         fb.pos[w] = at++;
       }
     }
-    start[3] = at;
-    if ((F > 1 && !grow(s_fjobs, F * sizeof(FusedJob))) || !grow_host(h_fres, F * sizeof(FusedRes)))
+      if ((F > 1 && !grow(s_fjobs, F * sizeof(FusedJob))) || !grow_host(h_fres, F * sizeof(FusedRes)))
       return DFAMIN_E_NOMEM;
     for (Resident* r : fb.fs) {
       if (r->uploaded) continue;
@@ -812,8 +811,8 @@ struct Serving::Impl {
       if (hipMemcpyAsync(s_fjobs.p, jobs.data(), F * sizeof(FusedJob), hipMemcpyHostToDevice, fstream) !=
           hipSuccess)
         return DFAMIN_E_DEVICE;
-      for (int cls = 2; cls >= 0; --cls) {
-        const uint32_t b = start[cls], e = cls == 0 ? start[3] : start[cls - 1];
+      for (int cls = kFusedClasses - 1; cls >= 0; --cls) {
+        const uint32_t b = start[cls], e = cls == 0 ? at : start[cls - 1];
         launch_fused(s_fjobs.as<FusedJob>() + b, res + b, e - b, cls, fstream);
       }
     }

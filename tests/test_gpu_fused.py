@@ -246,3 +246,22 @@ def test_many_small_instances_in_one_batch(ctx, monkeypatch):
     for d, o in zip(ds[::25], outs[::25]):
         want, _ = oracle.hopcroft(d.n, d.k, d.delta, d.accept)
         assert np.array_equal(o, want), d.name
+
+
+@pytest.mark.parametrize("n", [511, 512, 513, 4095, 4096, 4097, 6144])
+def test_tile_edges_alone_and_batched(ctx, monkeypatch, n):
+    """Sizes at the edges of the tiles (512, 2,048, 4,096, 8,192 states; a
+    single instance and a batch use different ones), inputs whose groups are
+    mostly single states, mostly large, and one letter's doubling."""
+    from paper_2410_22764_amd import dfamin
+    r = np.random.RandomState(n)
+    cls = r.randint(0, n // 9, n)
+    lift = W.from_rows(np.stack([r.permutation(n)[np.searchsorted(np.sort(cls), cls)] for _ in range(3)]),
+                       r.rand(n // 9)[cls] < 0.5, int(r.randint(n)), f"coarse({n})")
+    ds = [W.random_dfa(n, k, n + k) for k in (1, 2, 3, 9)] + [W.permuted_chain_dfa(n, 2, n), lift]
+    for d in ds:
+        out, res = both(ctx, d, "auto", monkeypatch)
+        oracle_check(d, out, res)
+    outs, results = dfamin.dfamin_minimize_batch(ctx, ds, "auto")
+    for d, out, res in zip(ds, outs, results):
+        oracle_check(d, out, res)
