@@ -122,11 +122,12 @@ int ensure(Context& c, dfamin::DevBuf& b, size_t bytes) {
   size_t want = (bytes + bytes / 8 + 4095) & ~size_t(4095);
   if (c.used + want > c.budget) {
     want = (bytes + 4095) & ~size_t(4095);
-    if (c.used + want > c.budget) return DFAMIN_E_NOMEM;
+    if (c.used + want > c.budget) return c.engine.release_big() ? ensure(c, b, bytes) : DFAMIN_E_NOMEM;
   }
   if (hipMalloc(&b.p, want) != hipSuccess) {
     b.p = nullptr;
     (void)hipGetLastError();
+    if (c.engine.release_big()) return ensure(c, b, bytes);
     return DFAMIN_E_NOMEM;
   }
   b.cap = want;

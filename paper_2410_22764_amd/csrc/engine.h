@@ -124,8 +124,11 @@ class Engine {
   uint32_t fused_limit(const dfamin_opts& opts) const;
   // Queues the fused kernels for the instances `which` of `in`; they write
   // their results into h_fres_ (mapped, read after the stream has drained).
+  // nonid (nullable): the instances' non-identity letters when they are
+  // validated already.  Instances above kFusedMaxStates go to `sbig`.
   int fused_issue(const std::vector<InstInput>& in, const std::vector<uint32_t>& which,
-                  const dfamin_opts& opts, uint64_t max_rounds, hipStream_t s);
+                  const dfamin_opts& opts, uint64_t max_rounds, hipStream_t s,
+                  const std::vector<std::vector<uint32_t>>* nonid = nullptr, hipStream_t sbig = nullptr);
   // Results of fused_issue's instances: res entries of the finished ones,
   // the handed-back ones in handoff; DFAMIN_E_BAD_DFA / _E_INTERNAL.
   int fused_collect(const std::vector<InstInput>& in, const std::vector<uint32_t>& which,
@@ -270,9 +273,16 @@ class Engine {
   // engine's work (created at the first batch; not in fixed-region mode,
   // which creates nothing after set-up): fused_ready_ on the caller's
   // stream after validation, fused_done_ behind the results' copy.
-  hipStream_t fused_stream_ = nullptr;
-  hipEvent_t fused_ready_ = nullptr, fused_done_ = nullptr;
+  // The larger ones among them (launch_fused_big) have a stream of their own:
+  // the small ones need not wait for the longest.
+  hipStream_t fused_stream_ = nullptr, big_stream_ = nullptr;
+  hipEvent_t fused_ready_ = nullptr, fused_done_ = nullptr, big_done_ = nullptr;
+  DevBuf d_fbig_;                     // their scratch
+  std::vector<uint32_t> big_order_;   // longest first
+  bool big_busy_ = false;             // d_fbig_ is in use by this call
+  bool no_big_ = false;               // this call does without
  public:
+  bool release_big();  // true: d_fbig_ was given back
   // Set by callers that read the round engine's buffers after run() (the
   // minimal DFA): every instance then goes through the round engine.
   bool no_fused = false;

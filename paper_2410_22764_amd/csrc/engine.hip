@@ -45,6 +45,13 @@ inline uint64_t mix64(uint64_t z) {
 
 constexpr uint32_t kDefaultAutoRounds = 8;
 constexpr uint64_t kClearAheadSlots = 1ull << 22;  // 32 MiB: a few microseconds to clear
+// Larger instances of a batch take one workgroup each (launch_fused_big) when
+// together they have at least this many times the states of the largest: an
+// instance alone on its CU takes longer (65,536 states, two letters: 1.1 ms)
+// than a few of them in the round engine (16: 0.6 ms; 64: 1.3 against 1.2 ms;
+// 256: 4.0 against 2.2 ms; 30,000 states: even at 16, 0.74 against 0.47 ms at
+// 64).
+constexpr uint64_t kBigMinRatio = 48;
 constexpr uint32_t kQueueRounds = 8;               // queued signature rounds per graph (even)
 
 // Workgroups of grid kernels in flight per device, over every context and
@@ -154,6 +161,11 @@ Engine::~Engine() {
     (void)hipStreamSynchronize(fused_stream_);
     (void)hipStreamDestroy(fused_stream_);
   }
+  if (big_stream_) {
+    (void)hipStreamSynchronize(big_stream_);
+    (void)hipStreamDestroy(big_stream_);
+  }
+  if (big_done_) (void)hipEventDestroy(big_done_);
   if (fused_ready_) (void)hipEventDestroy(fused_ready_);
   if (fused_done_) (void)hipEventDestroy(fused_done_);
   if (graph_exec_) (void)hipGraphExecDestroy(graph_exec_);
@@ -164,7 +176,7 @@ Engine::~Engine() {
                     &d_keep_, &d_rank_, &d_sig_, &d_table_, &d_status_, &d_changed_, &d_rb_,
                     &d_results_, &d_wgflags_, &d_part_, &d_dense_,
                     &d_djobs_, &d_visit_, &d_bfs_rows_, &d_min_delta_, &d_min_acc_,
-                    &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
+                    &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_fbig_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
   if (d_gbar_.p) (void)hipFree(d_gbar_.p);
   // device buffers of the fixed-region mode belong to the region
   if (!fixed()) {
@@ -185,7 +197,7 @@ uint64_t Engine::device_bytes() const {
                           &d_keep_, &d_rank_, &d_sig_, &d_table_, &d_status_, &d_changed_, &d_rb_,
                           &d_results_, &d_wgflags_, &d_part_, &d_dense_,
                           &d_djobs_, &d_visit_, &d_bfs_rows_, &d_min_delta_, &d_min_acc_,
-                          &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
+                          &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_fbig_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
   uint64_t t = d_gbar_.cap;
   for (const DevBuf* b : bufs) t += b->cap;
   for (const DevBuf& b : closure_bufs_) t += b.cap;
@@ -222,17 +234,28 @@ int Engine::ensure(DevBuf& b, size_t bytes) {
   }
   if (ctx_->used + want > ctx_->budget) {
     want = (bytes + 4095) & ~size_t(4095);
-    if (ctx_->used + want > ctx_->budget) return DFAMIN_E_NOMEM;
+    if (ctx_->used + want > ctx_->budget) return &b != &d_fbig_ && release_big() ? ensure(b, bytes) : DFAMIN_E_NOMEM;
   }
   hipError_t e = hipMalloc(&b.p, want);
   if (e != hipSuccess) {
     b.p = nullptr;
     (void)hipGetLastError();
+    if (e == hipErrorOutOfMemory && &b != &d_fbig_ && release_big()) return ensure(b, bytes);
     return e == hipErrorOutOfMemory ? DFAMIN_E_NOMEM : check_hip(e);
   }
   b.cap = want;
   ctx_->used += want;
   return DFAMIN_OK;
+}
+
+// Gives back the scratch of a batch's larger instances, which is kept from
+// call to call only while nothing else needs the budget.
+bool Engine::release_big() {
+  if (big_busy_ || fixed() || !d_fbig_.p) return false;
+  (void)hipFree(d_fbig_.p);
+  ctx_->used -= d_fbig_.cap;
+  d_fbig_ = DevBuf{};
+  return true;
 }
 
 int Engine::ensure_host(HostBuf& b, size_t bytes) {
@@ -279,7 +302,7 @@ void Engine::reset_fixed_region() {
                     &d_results_, &d_wgflags_, &d_part_, &d_dense_,
                     &d_djobs_, &d_visit_, &d_bfs_rows_, &d_min_delta_, &d_min_acc_,
                     &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_ctrl_, &d_refine_, &d_counts_,
-                    &d_fjobs_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
+                    &d_fjobs_, &d_fbig_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
   for (DevBuf* b : bufs) *b = DevBuf{};
   closure_bufs_.clear();
   fixed_off_ = 0;
@@ -287,7 +310,9 @@ void Engine::reset_fixed_region() {
 
 uint64_t Engine::closure_cap() const {
   if (fixed()) return fixed_cap_ > fixed_off_ ? (fixed_cap_ - fixed_off_) / 3 : 0;
-  return ctx_->budget > ctx_->used ? (ctx_->budget - ctx_->used) / 2 : 0;
+  // (d_fbig_ is given up before anything else fails for it)
+  const uint64_t used = ctx_->used - d_fbig_.cap;
+  return ctx_->budget > used ? (ctx_->budget - used) / 2 : 0;
 }
 
 int Engine::upload(void* dst, const void* src, size_t bytes, hipStream_t s) {
@@ -1628,56 +1653,92 @@ uint32_t Engine::fused_limit(const dfamin_opts& opts) const {
 }
 
 int Engine::fused_issue(const std::vector<InstInput>& in, const std::vector<uint32_t>& which,
-                        const dfamin_opts& opts, uint64_t max_rounds, hipStream_t s) {
+                        const dfamin_opts& opts, uint64_t max_rounds, hipStream_t s,
+                        const std::vector<std::vector<uint32_t>>* nonid, hipStream_t sbig) {
   const size_t F = which.size();
-  if (F > 1) TRY(ensure(d_fjobs_, F * sizeof(FusedJob)));
+  if (F > 1 || in[which[0]].n > kFusedMaxStates) TRY(ensure(d_fjobs_, F * sizeof(FusedJob)));
   TRY(ensure_host(h_fjobs_, F * sizeof(FusedJob)));
   TRY(ensure_host(h_fres_, F * sizeof(FusedRes)));
   // jobs grouped by size class, largest class first
   FusedJob* hj = h_fjobs_.as<FusedJob>();
   fused_pos_.assign(F, 0);
-  uint32_t at = 0, start[kFusedClasses] = {};
+  uint32_t at = 0, start[kFusedClasses + 1] = {};
   double bytes = 0;
-  for (int cls = kFusedClasses - 1; cls >= 0; --cls) {
-    start[cls] = at;
-    for (size_t w = 0; w < F; ++w) {
-      const InstInput& x = in[which[w]];
-      if (fused_class(x.n) != cls) continue;
-      FusedJob& J = hj[at];
-      J.delta = reinterpret_cast<uint64_t>(x.delta);
-      J.accept = reinterpret_cast<uint64_t>(x.accept);
-      J.out = reinterpret_cast<uint64_t>(x.out);
-      J.n = x.n;
-      J.k = x.k;
-      J.q0 = x.q0;
-      J.closure = x.closure;
-      uint32_t L = floor_log2_u32(x.n);
-      if (opts.max_levels && opts.max_levels < L) L = opts.max_levels;
-      J.levels = L;
-      J.auto_rounds = opts.auto_rounds ? opts.auto_rounds : kDefaultAutoRounds;
-      J.max_rounds = (uint32_t)std::min<uint64_t>(max_rounds, 0xFFFFFFFFull);
-      J.pad = 0;
-      fused_pos_[w] = at++;
-      // transitions read once for validation, accept bits, the output write
-      bytes += 4.0 * x.n * x.k + x.n / 8.0 + 4.0 * x.n;
+  uint64_t scratch = reinterpret_cast<uint64_t>(d_fbig_.p);  // (run_all sized it)
+  auto add = [&](size_t w) {
+    const InstInput& x = in[which[w]];
+    FusedJob& J = hj[at];
+    J.delta = reinterpret_cast<uint64_t>(x.delta);
+    J.accept = reinterpret_cast<uint64_t>(x.accept);
+    J.out = reinterpret_cast<uint64_t>(x.out);
+    J.n = x.n;
+    J.k = x.k;
+    J.q0 = x.q0;
+    J.closure = x.closure;
+    uint32_t L = floor_log2_u32(x.n);
+    if (opts.max_levels && opts.max_levels < L) L = opts.max_levels;
+    J.levels = L;
+    J.auto_rounds = opts.auto_rounds ? opts.auto_rounds : kDefaultAutoRounds;
+    J.max_rounds = (uint32_t)std::min<uint64_t>(max_rounds, 0xFFFFFFFFull);
+    J.validated = nonid ? 1u : 0u;
+    J.mask = 0;
+    if (nonid)
+      for (uint32_t a : (*nonid)[which[w]]) J.mask |= 1u << a;
+    J.pad = 0;
+    J.scratch = 0;
+    if (x.n > kFusedMaxStates) {
+      J.scratch = scratch;
+      scratch += fused_big_scratch(x.n, x.k);
     }
+    fused_pos_[w] = at++;
+    // transitions read once, accept bits, the output write
+    bytes += 4.0 * x.n * x.k + x.n / 8.0 + 4.0 * x.n;
+  };
+  // the larger ones longest first: doubling instances (one round per level),
+  // then by transitions
+  big_order_.clear();
+  for (size_t w = 0; w < F; ++w)
+    if (in[which[w]].n > kFusedMaxStates) big_order_.push_back((uint32_t)w);
+  auto cost = [&](uint32_t w) {
+    const InstInput& x = in[which[w]];
+    const bool unary = nonid && x.closure == DFAMIN_CLOSURE_AUTO && (*nonid)[which[w]].size() == 1;
+    return (unary ? 1ull << 40 : 0ull) + (uint64_t)x.n * (unary ? 1u : x.k);
+  };
+  std::sort(big_order_.begin(), big_order_.end(), [&](uint32_t a, uint32_t b) { return cost(a) > cost(b); });
+  for (uint32_t w : big_order_) add(w);
+  const uint32_t nbig = at;
+  for (int cls = kFusedClasses - 1; cls >= 0; --cls) {
+    start[cls + 1] = at;
+    for (size_t w = 0; w < F; ++w)
+      if (in[which[w]].n <= kFusedMaxStates && fused_class(in[which[w]].n) == cls) add(w);
   }
+  start[0] = at;
   // The kernels write their results straight into the mapped page-locked
   // buffer the host reads after its wait; one job travels as a kernel
   // argument, so a single small instance costs one launch and no copies.
   FusedRes* res = static_cast<FusedRes*>(h_fres_.dp);
-  if (F > 1) launch_copy_bytes(d_fjobs_.p, h_fjobs_.dp, F * sizeof(FusedJob), s);
   Profiler& prof = ctx_->prof;
-  prof.begin(s, "fused", bytes);
-  if (F == 1) {
+  if (F == 1 && !nbig) {
+    prof.begin(s, "fused", bytes);
     launch_fused(nullptr, res, 1, fused_class(hj[0].n), s, &hj[0]);
-  } else {
-    for (int cls = kFusedClasses - 1; cls >= 0; --cls) {
-      const uint32_t b = start[cls], e = cls == 0 ? at : start[cls - 1];
-      launch_fused(d_fjobs_.as<FusedJob>() + b, res + b, e - b, cls, s);
-    }
+    prof.end(s);
+    return check_hip(hipGetLastError());
   }
-  prof.end(s);
+  FusedJob* dj = d_fjobs_.as<FusedJob>();
+  if (nbig) {
+    const hipStream_t bs = sbig ? sbig : s;
+    launch_copy_bytes(dj, h_fjobs_.dp, nbig * sizeof(FusedJob), bs);
+    prof.begin(bs, "fused_big", 0.0);
+    launch_fused_big(dj, res, nbig, bs);
+    prof.end(bs);
+  }
+  if (at > nbig) {
+    launch_copy_bytes(dj + nbig, static_cast<const FusedJob*>(h_fjobs_.dp) + nbig, (at - nbig) * sizeof(FusedJob), s);
+    prof.begin(s, "fused", bytes);
+    for (int cls = kFusedClasses - 1; cls >= 0; --cls)
+      launch_fused(dj + start[cls + 1], res + start[cls + 1], start[cls] - start[cls + 1], cls, s);
+    prof.end(s);
+  }
   return check_hip(hipGetLastError());
 }
 
@@ -1738,7 +1799,7 @@ bool Engine::grid_applies(const InstInput& x, const dfamin_opts& opts, uint32_t*
   if (fixed()) {
     const uint64_t own = 27ull * n + (64ull << 10);  // the engine's buffers carved before the levels
     if (own > fixed_cap_ || 4 * L * n > (fixed_cap_ - own) / 3) return false;
-  } else if (ctx_->used + 2 * 4 * L * n + (256ull + 8ull * x.k) * n > ctx_->budget) {
+  } else if (ctx_->used - d_fbig_.cap + 2 * 4 * L * n + (256ull + 8ull * x.k) * n > ctx_->budget) {
     return false;
   }
   return grid_shape(x.n, ctx_->cus, items, wgs);
@@ -1922,6 +1983,28 @@ int Engine::run_all(const std::vector<InstInput>& in, const dfamin_opts& opts, h
                     (in[i].closure == DFAMIN_CLOSURE_AUTO || in[i].closure == DFAMIN_CLOSURE_OFF);
     (ok ? small : big).push_back((uint32_t)i);
   }
+  // Many instances of up to kFusedBigStates states: one workgroup each, too
+  // (kBigMinRatio), while their scratch fits the budget.
+  bool bigs = false;
+  if (I > 1 && N < kMaxStates && lim == kFusedMaxStates && !fixed() && !no_big_ && ctx_->tuner.forced < 0 &&
+      !std::getenv("DFAMIN_NO_LABELS")) {
+    uint64_t bytes = 0, states = 0, most = 0;
+    std::vector<uint32_t> mid, rest;
+    for (uint32_t i : big) {
+      const bool ok = in[i].n <= kFusedBigStates && in[i].k <= kFusedMaxLetters &&
+                      (in[i].closure == DFAMIN_CLOSURE_AUTO || in[i].closure == DFAMIN_CLOSURE_OFF);
+      (ok ? mid : rest).push_back(i);
+      if (!ok) continue;
+      bytes += fused_big_scratch(in[i].n, in[i].k);
+      states += in[i].n;
+      most = std::max<uint64_t>(most, in[i].n);
+    }
+    if (!mid.empty() && states >= kBigMinRatio * most && ensure(d_fbig_, bytes) == DFAMIN_OK) {
+      bigs = big_busy_ = true;
+      small.insert(small.end(), mid.begin(), mid.end());
+      big.swap(rest);
+    }
+  }
   if (small.empty() || N >= kMaxStates) return run_path(in, opts, s, res);
   const uint64_t max_rounds = opts.max_rounds ? opts.max_rounds : (uint64_t)nmax + 1;
   res.assign(I, InstOutcome{});
@@ -1972,13 +2055,23 @@ int Engine::run_all(const std::vector<InstInput>& in, const dfamin_opts& opts, h
   // With larger instances in the call, the fused kernels run on their own
   // stream beside the round engine's rounds (whose host syncs leave the GPU
   // idle now and then), after this call's validation.
-  hipStream_t fs = s;
+  hipStream_t fs = s, bs = s;
+  if (bigs && !ctx_->prof.enabled()) {
+    if (!big_stream_) {
+      HIP(hipStreamCreateWithFlags(&big_stream_, hipStreamNonBlocking));
+      HIP(hipEventCreateWithFlags(&big_done_, hipEventDisableTiming));
+    }
+    if (!fused_ready_) HIP(hipEventCreateWithFlags(&fused_ready_, hipEventDisableTiming));
+    HIP(hipEventRecord(fused_ready_, s));
+    HIP(hipStreamWaitEvent(big_stream_, fused_ready_, 0));
+    bs = big_stream_;
+  }
   // (with kernel timing on, everything stays on one stream: the profiler
   // collects a launch's events after that stream's waits)
   if (!big.empty() && !fixed() && !ctx_->prof.enabled()) {
     if (!fused_stream_) {
       HIP(hipStreamCreateWithFlags(&fused_stream_, hipStreamNonBlocking));
-      HIP(hipEventCreateWithFlags(&fused_ready_, hipEventDisableTiming));
+      if (!fused_ready_) HIP(hipEventCreateWithFlags(&fused_ready_, hipEventDisableTiming));
       HIP(hipEventCreateWithFlags(&fused_done_, hipEventDisableTiming));
     }
     HIP(hipEventRecord(fused_ready_, s));
@@ -1986,8 +2079,9 @@ int Engine::run_all(const std::vector<InstInput>& in, const dfamin_opts& opts, h
     fs = fused_stream_;
   }
   const double t_pre = us_since(t0);
-  int frc = fused_issue(in, small, opts, max_rounds, fs);
+  int frc = fused_issue(in, small, opts, max_rounds, fs, &nonid_all, bs);
   if (frc == DFAMIN_OK && fs != s) frc = check_hip(hipEventRecord(fused_done_, fs));
+  if (frc == DFAMIN_OK && bs != s) frc = check_hip(hipEventRecord(big_done_, bs));
   const double t_fused = us_since(t0);
   if (frc == DFAMIN_OK && !big.empty()) frc = run_subset(big, nonid_all);
   if (trace)
@@ -1995,11 +2089,14 @@ int Engine::run_all(const std::vector<InstInput>& in, const dfamin_opts& opts, h
                  "fused issued %.0f, round engine done %.0f\n", I, small.size(), t_valid, t_pre, t_fused,
                  us_since(t0));
   if (frc != DFAMIN_OK) {
-    if (fs != s && !ctx_->device_lost) (void)hipStreamSynchronize(fs);  // nothing of the call left queued
+    // nothing of the call left queued
+    if (fs != s && !ctx_->device_lost) (void)hipStreamSynchronize(fs);
+    if (bs != s && !ctx_->device_lost) (void)hipStreamSynchronize(bs);
     return frc;
   }
   HIP(stream_wait(s));
-  if (fs != s) HIP(hipEventSynchronize(fused_done_));
+  if (fs != s) HIP(event_wait(fused_done_));
+  if (bs != s) HIP(event_wait(big_done_));
   ctx_->prof.collect();
   TRY(fused_collect(in, small, res, handoff));
   if (!handoff.empty()) TRY(run_subset(handoff, nonid_all));
@@ -2009,7 +2106,14 @@ int Engine::run_all(const std::vector<InstInput>& in, const dfamin_opts& opts, h
 int Engine::run(const std::vector<InstInput>& in, const dfamin_opts& opts, hipStream_t s,
                 std::vector<InstOutcome>& res) {
   if (fixed()) reset_fixed_region();
-  const int rc = run_all(in, opts, s, res);
+  int rc = run_all(in, opts, s, res);
+  big_busy_ = false;
+  if (rc == DFAMIN_E_NOMEM && release_big()) {  // the rest did not fit beside d_fbig_
+    (void)hipStreamSynchronize(s);
+    no_big_ = true;
+    rc = run_all(in, opts, s, res);
+    no_big_ = false;
+  }
   // A call that stops early may leave work queued behind its last wait (the
   // next round's level passes and table clear): let it finish before the
   // buffers are handed to another call.

@@ -141,8 +141,8 @@ __global__ void __launch_bounds__(NT, 4) k_fused(const FusedJob* __restrict__ jo
   uint32_t fbits = 0;  // accept bit of owned state i in bit i
   uint32_t live = 0;   // bit i: owned state i exists and its block may still split
   {
-    uint32_t bad = 0, nonid = 0;
-    for (uint32_t a = 0; a < k; a += LC) {
+    uint32_t bad = 0, nonid = J.validated ? J.mask : 0u;
+    for (uint32_t a = 0; a < (J.validated ? 0u : k); a += LC) {
       uint32_t v[LC][ITEMS];
 #pragma unroll
       for (int c = 0; c < LC; ++c) {
@@ -549,6 +549,530 @@ __global__ void __launch_bounds__(NT, 4) k_fused(const FusedJob* __restrict__ jo
   }
 }
 
+// Larger instances of a batch (16,384 < n <= 65,536), one workgroup each: the
+// same rounds and the same grouping by minimum, with the block ids (16-bit)
+// and the table sharing the LDS -- 30,000 slots at 20,000 states, 7,700 at
+// 65,536 -- and hashes, new ids and lists in global scratch that stays in the
+// caches.  Where a round may form more groups than the table takes, its
+// states are first sorted into slices of the hash (all members of a group
+// share one), and each throw takes one more slice along with what the last
+// throw left.  Bound: LDS operations and the row reads of each round, on as
+// many CUs as there are instances; a round of the round engine moves the same
+// states through device atomics (27 G/s) and a dozen launches instead.  A
+// random instance of 65,536 states and two letters takes 1.1 ms (six rounds
+// of 40 us hashing and, in three, 150 us of throws), 256 of them 2.2 ms
+// (round engine: 4.0), 512 chains of that size 6.2 ms (22.9); a batch of 1,272
+// instances up to 65,536 states went from 10.2 to 3.6 ms.
+constexpr uint32_t kBigThreads = 1024, kBigWaves = kBigThreads / 64;
+constexpr uint32_t kBigLds = 40960 - 64;  // 32-bit words
+constexpr uint32_t kSlices = 16;
+constexpr uint32_t kAlone = 0x10000u;     // new-id word: a block of one state
+constexpr int kBigChunk = 8;              // states of a thread whose loads go out together
+
+__global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __restrict__ jobs,
+                                                              FusedRes* __restrict__ res, uint32_t njobs) {
+  __shared__ __align__(16) uint32_t lds[kBigLds];
+  // words 0..63: 0 bad, 1 letters, 2 min F, 3 min Q\F, 4/5 leaders, 6/7 list lengths
+  uint32_t* const sh = lds;
+  uint32_t* const hist = lds + 64;                      // per wave and slice: counts, then list positions
+  uint32_t* const first = hist + kBigWaves * kSlices;   // start of each slice, and the end
+  uint16_t* const blk = reinterpret_cast<uint16_t*>(lds + 64 + kBigWaves * kSlices + 32);
+  const uint32_t j = blockIdx.x;
+  if (j >= njobs) return;
+  const FusedJob J = jobs[j];
+  const uint32_t n = J.n, k = J.k, tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  const uint32_t blkw = ((n + 7u) / 8u) * 4u;  // words of blk[], 16-byte multiple
+  uint32_t* const slot = lds + 64 + kBigWaves * kSlices + 32 + blkw;
+  const uint32_t S = kBigLds - (64 + kBigWaves * kSlices + 32) - blkw;  // below 2^15
+  const uint32_t* __restrict__ delta = reinterpret_cast<const uint32_t*>(J.delta);
+  const uint8_t* __restrict__ acc = reinterpret_cast<const uint8_t*>(J.accept);
+  // scratch: hash and new id per state, the sorted list, two leftover lists
+  // ((hash, state) pairs), two levels, the signatures
+  const uint32_t n4 = (n + 3u) & ~3u;
+  uint32_t* H = reinterpret_cast<uint32_t*>(J.scratch);
+  uint32_t* NB = H + n4;
+  uint2* L = reinterpret_cast<uint2*>(NB + n4);
+  uint2* LO[2] = {L + n4, L + 2 * n4};
+  uint16_t* LV[2] = {reinterpret_cast<uint16_t*>(L + 3 * n4), reinterpret_cast<uint16_t*>(L + 3 * n4) + n4};
+  // Signatures as 16-bit block ids, eight to a record of 16 bytes: what a
+  // confirmation compares, two reads instead of two per letter.
+  uint4* REC = reinterpret_cast<uint4*>(LV[1] + n4);
+  const uint32_t iters = (n + kBigThreads - 1) / kBigThreads;  // at most 64
+  auto uniform = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane(v); };
+  FusedRes R{};
+  if (tid < 64) sh[tid] = tid == 2 || tid == 3 ? kNone : 0u;
+  __syncthreads();
+
+  unsigned long long live = 0;  // bit i: state tid + i*1024 exists and its block may still split
+  {
+    uint32_t bad = 0, nonid = 0;
+    if (J.validated) {
+      nonid = J.mask;
+    } else {
+      for (uint32_t a = 0; a < k; ++a) {
+        const uint32_t* __restrict__ row = delta + (size_t)a * n;
+        uint32_t d = 0;
+        for (uint32_t i0 = 0; i0 < iters; i0 += kBigChunk) {
+          uint32_t v[kBigChunk];
+#pragma unroll
+          for (int i = 0; i < kBigChunk; ++i) {
+            const uint32_t q = tid + (i0 + i) * kBigThreads;
+            v[i] = q < n ? ld(row, q) : q;
+          }
+#pragma unroll
+          for (int i = 0; i < kBigChunk; ++i) {
+            const uint32_t q = tid + (i0 + i) * kBigThreads;
+            bad |= (uint32_t)(q < n && v[i] >= n);
+            d |= (uint32_t)(v[i] != q);
+          }
+        }
+        if (d) nonid |= 1u << a;
+      }
+    }
+    uint32_t mf = kNone, mn = kNone;
+    for (uint32_t i = 0; i < iters; ++i) {
+      const uint32_t q = tid + i * kBigThreads;
+      if (q >= n) break;
+      live |= 1ull << i;
+      if ((acc[q >> 3] >> (q & 7)) & 1u) mf = min(mf, q);
+      else mn = min(mn, q);
+    }
+    bad = wave_or(bad);
+    nonid = wave_or(nonid);
+    mf = wave_min(mf);
+    mn = wave_min(mn);
+    if (lane == 0) {
+      if (bad) atomicOr(&sh[0], 1u);
+      if (nonid) atomicOr(&sh[1], nonid);
+      atomicMin(&sh[2], mf);
+      atomicMin(&sh[3], mn);
+    }
+  }
+  __syncthreads();
+  if (sh[0]) {
+    if (tid == 0) {
+      R.status = kFusedBad;
+      res[j] = R;
+    }
+    return;
+  }
+  const uint32_t mask = uniform(sh[1]), knon = __popc(mask);
+  const bool autom = J.closure == DFAMIN_CLOSURE_AUTO;
+  const bool dbl = autom && knon == 1;
+  const uint32_t minF = uniform(sh[2]), minN = uniform(sh[3]);
+  uint32_t count = (minF < n ? 1u : 0u) + (minN < n ? 1u : 0u);
+  {
+    const uint32_t* __restrict__ rowA = delta + (size_t)(mask ? __ffs(mask) - 1 : 0) * n;
+    for (uint32_t i = 0; i < iters; ++i) {
+      const uint32_t q = tid + i * kBigThreads;
+      if (q >= n) break;
+      blk[q] = (uint16_t)(((acc[q >> 3] >> (q & 7)) & 1u) ? minF : minN);
+      if (dbl) LV[0][q] = (uint16_t)ld(rowA, q);
+    }
+  }
+  uint32_t rounds = 0, refine = 0, used = 0, l = 0, alive = n;
+  uint64_t jlen = 0;
+  int32_t status = kFusedOk;
+  __syncthreads();
+
+  while (true) {
+    if (autom && !dbl && knon >= 2 && rounds == J.auto_rounds) {
+      status = kFusedHandOff;
+      break;
+    }
+    if (rounds >= J.max_rounds) {
+      status = kFusedRoundCap;
+      break;
+    }
+    const uint16_t* lv = LV[l & 1u];
+    uint16_t* lvn = nullptr;  // the next round's level, squared beside this round's hashes
+    if (dbl && l < J.levels && (1ull << (l + 1)) <= jlen + (1ull << l) + 1ull) lvn = LV[(l + 1u) & 1u];
+    // the first round's signatures (accept bits) index the table themselves
+    const bool direct = !dbl && rounds == 0 && knon + 1u <= 31u - (uint32_t)__clz(S);
+    // groups this round may form: as many as states left to place, but a
+    // doubling round at most about squares its blocks, and from few blocks
+    // forms far fewer (a guess: too low costs throws, nothing else)
+    const uint32_t est = direct ? 1u : (dbl ? (uint32_t)min((uint64_t)alive, 4ull * count) : alive);
+    const uint32_t P = est <= S + S / 2u ? 1u : min(kSlices, (uint32_t)((10ull * est + 7ull * S - 1) / (7ull * S)));
+    const bool read_first = count * 8u < n;
+    const uint32_t seed0 = 0x6A09E667u;
+    auto slice = [&](uint32_t h) { return ((h >> 16) * P) >> 16; };
+    auto aim_at = [&](uint32_t h, uint32_t mul, uint32_t& pos, uint32_t& frag) {
+      uint32_t y = h * mul;
+      y ^= y >> 16;
+      frag = min(y >> 17, 0x7FFEu);
+      pos = ((y & 0x1FFFFu) * S) >> 17;
+    };
+    auto hash_one = [&](uint32_t q, uint32_t seed) {  // (a rehash: rare)
+      uint32_t h = mix_step(seed, blk[q]);
+      for (uint32_t mm = mask; mm; mm &= mm - 1u) h = mix_step(h, blk[ld(delta + (size_t)(__ffs(mm) - 1) * n, q)]);
+      return mix_final(h);
+    };
+    if (P > 1 && tid < kBigWaves * kSlices) hist[tid] = 0;
+    if (P == 1)
+      for (uint32_t x = tid; x < S; x += kBigThreads) slot[x] = kEmpty;
+    if (tid < 2) sh[6 + tid] = 0;
+    __syncthreads();
+    // ---- hashes (and the next level).  A doubling signature's two ids are
+    // its exact 32-bit key, which the hash only permutes.  With one slice the
+    // first throw happens right here.
+    const uint32_t recs = (knon + 8u) / 8u;  // records per signature
+    auto throw_at = [&](uint32_t h, uint32_t q, uint32_t mul) {
+      uint32_t pos = h, frag = 0;
+      if (!direct) aim_at(h, mul, pos, frag);
+      const uint32_t word = (frag << 17) | (q << 1);
+      if (!read_first || slot[pos] > word) atomicMin(&slot[pos], word);
+    };
+    for (uint32_t i0 = 0; i0 < iters; i0 += kBigChunk) {
+      uint32_t h[kBigChunk], s[kBigChunk];
+      const uint32_t bits = (uint32_t)(live >> i0) & ((1u << kBigChunk) - 1u);
+      if (dbl) {
+        uint32_t nx[kBigChunk];
+#pragma unroll
+        for (int i = 0; i < kBigChunk; ++i) {
+          const uint32_t q = tid + (i0 + i) * kBigThreads;
+          s[i] = q < n ? lv[q] : 0u;
+        }
+#pragma unroll
+        for (int i = 0; i < kBigChunk; ++i) nx[i] = lvn ? lv[s[i]] : 0u;
+#pragma unroll
+        for (int i = 0; i < kBigChunk; ++i) {
+          const uint32_t q = tid + (i0 + i) * kBigThreads;
+          if (lvn && q < n) lvn[q] = (uint16_t)nx[i];
+          h[i] = mix_final((((q < n ? (uint32_t)blk[q] : 0u) << 16) | blk[s[i]]) * 0x9E3779B1u);
+        }
+      } else {
+        uint32_t w[kBigChunk];  // two ids of the record being filled
+        uint32_t at = 1;
+#pragma unroll
+        for (int i = 0; i < kBigChunk; ++i) {
+          const uint32_t q = tid + (i0 + i) * kBigThreads;
+          w[i] = q < n ? (uint32_t)blk[q] : 0u;
+          h[i] = direct ? (uint32_t)(w[i] == minF) : mix_step(seed0, w[i]);
+        }
+        for (uint32_t mm = mask; mm; mm &= mm - 1u, ++at) {
+          const uint32_t* row = delta + (size_t)(__ffs(mm) - 1) * n;
+#pragma unroll
+          for (int i = 0; i < kBigChunk; ++i)
+            s[i] = ((bits >> i) & 1u) ? ld(row, tid + (i0 + i) * kBigThreads) : 0u;
+#pragma unroll
+          for (int i = 0; i < kBigChunk; ++i) {
+            const uint32_t b = blk[s[i]];
+            h[i] = direct ? h[i] | ((uint32_t)(b == minF) << at) : mix_step(h[i], b);
+            w[i] |= b << (16u * (at & 1u));
+          }
+          // (letter pairs go out as they fill: word at/2 of the state's records)
+          if (!direct && ((at & 1u) || !(mm & (mm - 1u)))) {
+#pragma unroll
+            for (int i = 0; i < kBigChunk; ++i) {
+              if ((bits >> i) & 1u)
+                reinterpret_cast<uint32_t*>(REC)[(size_t)(tid + (i0 + i) * kBigThreads) * (4u * recs) + (at >> 1)] = w[i];
+              w[i] = 0;
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < kBigChunk; ++i) {
+        if (!((bits >> i) & 1u)) continue;
+        if (!direct && !dbl) h[i] = mix_final(h[i]);
+        H[tid + (i0 + i) * kBigThreads] = h[i];
+        if (P > 1) atomicAdd(&hist[wave * kSlices + slice(h[i])], 1u);
+        else throw_at(h[i], tid + (i0 + i) * kBigThreads, 0x9E3779B1u);
+      }
+    }
+    __syncthreads();
+    if (P > 1) {
+      // list positions: slice by slice, wave by wave
+      if (tid < 64) {
+        uint32_t run = 0;
+        for (uint32_t c0 = 0; c0 < kBigWaves * kSlices; c0 += 64) {
+          const uint32_t c = c0 + lane;  // (slice, wave) in list order
+          uint32_t& cell = hist[(c % kBigWaves) * kSlices + c / kBigWaves];
+          const uint32_t x = cell, incl = wave_incl_scan(x);
+          cell = run + incl - x;
+          if (c % kBigWaves == 0) first[c / kBigWaves] = run + incl - x;
+          run += __shfl(incl, 63);
+        }
+        if (lane == 0) first[kSlices] = run;
+      }
+      __syncthreads();
+      for (uint32_t i0 = 0; i0 < iters; i0 += kBigChunk) {
+        const uint32_t bits = (uint32_t)(live >> i0) & ((1u << kBigChunk) - 1u);
+        uint32_t h[kBigChunk];
+#pragma unroll
+        for (int i = 0; i < kBigChunk; ++i) h[i] = ((bits >> i) & 1u) ? H[tid + (i0 + i) * kBigThreads] : 0u;
+#pragma unroll
+        for (int i = 0; i < kBigChunk; ++i)
+          if ((bits >> i) & 1u)
+            L[atomicAdd(&hist[wave * kSlices + slice(h[i])], 1u)] = make_uint2(h[i], tid + (i0 + i) * kBigThreads);
+      }
+      __syncthreads();
+    }
+    // ---- throws
+    uint32_t next = 0, left = 0, lo = 0, idle = 0, rehash = 0;  // next: slices thrown so far
+    while (next < P || left) {
+      // entries of this throw: what is left, then the next slice (or, with
+      // one slice, every live state in order)
+      const bool order = P == 1 && next == 0;
+      uint32_t b0 = 0, add = 0;
+      if (P > 1 && next < P) {
+        b0 = uniform(first[next]);
+        add = uniform(next + 1 < kSlices ? first[next + 1] : first[kSlices]) - b0;
+      }
+      const uint32_t total = order ? n : left + add;
+      const uint2* old = LO[lo];
+      uint2* fresh = LO[lo ^ 1u];
+      auto entry = [&](uint32_t x) -> uint2 {
+        if (order) return make_uint2(H[x], x);
+        return x < left ? old[x] : L[b0 + x - left];
+      };
+      auto valid = [&](uint32_t x, uint32_t i) { return x < total && (!order || ((live >> i) & 1u)); };
+      const uint32_t mul = 0x9E3779B1u + 0x3C6EF372u * (next + idle);  // odd: a bijection of h
+      auto aim = [&](uint32_t h, uint32_t& pos, uint32_t& frag) {
+        if (direct) {
+          pos = h;
+          frag = 0;
+        } else {
+          aim_at(h, mul, pos, frag);
+        }
+      };
+      if (!order)
+        for (uint32_t x = tid; x < S; x += kBigThreads) slot[x] = kEmpty;
+      if (tid == 0) sh[6 + (lo ^ 1u)] = 0;
+      __syncthreads();
+      const uint32_t its = (total + kBigThreads - 1) / kBigThreads;
+      constexpr int UT = 8, U = 4;
+      if (!order) {
+        for (uint32_t i0 = 0; i0 < its; i0 += UT) {
+          uint2 e[UT];
+#pragma unroll
+          for (int i = 0; i < UT; ++i) {
+            const uint32_t x = tid + (i0 + i) * kBigThreads;
+            e[i] = x < total ? entry(x) : make_uint2(0, kNone);
+          }
+#pragma unroll
+          for (int i = 0; i < UT; ++i)
+            if (e[i].y != kNone) throw_at(e[i].x, e[i].y, mul);
+        }
+        __syncthreads();
+      }
+      unsigned long long reps = 0;
+      for (uint32_t i0 = 0; i0 < its; i0 += U) {
+        uint2 e[U];
+        uint32_t rep[U], cand = 0, todo = 0;
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+          const uint32_t x = tid + (i0 + i) * kBigThreads;
+          e[i] = valid(x, i0 + i) ? entry(x) : make_uint2(0, kNone);
+        }
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+          rep[i] = 0;
+          if (e[i].y == kNone) continue;
+          todo |= 1u << i;
+          uint32_t pos, frag;
+          aim(e[i].x, pos, frag);
+          const uint32_t v = slot[pos];
+          if ((v >> 17) != frag) continue;
+          rep[i] = (v >> 1) & 0xFFFFu;
+          if (rep[i] == e[i].y) {
+            reps |= 1ull << (i0 + i);
+            todo &= ~(1u << i);
+          } else {
+            cand |= 1u << i;
+          }
+        }
+        if (!direct && __any(cand != 0u)) {
+          if (dbl) {  // the hash is the signature
+            uint32_t a[U];
+#pragma unroll
+            for (int i = 0; i < U; ++i) a[i] = ((cand >> i) & 1u) ? H[rep[i]] : e[i].x;
+#pragma unroll
+            for (int i = 0; i < U; ++i)
+              if (a[i] != e[i].x) cand &= ~(1u << i);
+          } else if (!knon) {
+#pragma unroll
+            for (int i = 0; i < U; ++i)
+              if (((cand >> i) & 1u) && blk[rep[i]] != blk[e[i].y]) cand &= ~(1u << i);
+          } else {
+            for (uint32_t r = 0; r < recs; ++r) {
+              uint4 a[U], b[U];
+#pragma unroll
+              for (int i = 0; i < U; ++i) {
+                const bool on = (cand >> i) & 1u;
+                a[i] = REC[(size_t)(on ? rep[i] : 0u) * recs + r];
+                b[i] = REC[(size_t)(on ? e[i].y : 0u) * recs + r];
+              }
+              // (ids beyond the signature's last are never written: not compared)
+              const uint32_t ids = min(8u, knon + 1u - 8u * r);
+#pragma unroll
+              for (int i = 0; i < U; ++i) {
+                bool same = a[i].x == b[i].x || ids == 0u;
+                if (ids > 2u) same = same && a[i].y == b[i].y;
+                if (ids > 4u) same = same && a[i].z == b[i].z;
+                if (ids > 6u) same = same && a[i].w == b[i].w;
+                if (!same) cand &= ~(1u << i);
+              }
+            }
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+          if (!((cand >> i) & 1u)) continue;
+          uint32_t pos, frag;
+          aim(e[i].x, pos, frag);
+          if (!(slot[pos] & 1u)) atomicOr(&slot[pos], 1u);
+          NB[e[i].y] = rep[i];
+        }
+        todo &= ~cand;
+        // what is left joins the next throw's list
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+          const bool go = (todo >> i) & 1u;
+          const unsigned long long m = __ballot(go);
+          if (!m) continue;
+          uint32_t p = 0;
+          if (lane == (uint32_t)__builtin_ctzll(m)) p = atomicAdd(&sh[6 + (lo ^ 1u)], (uint32_t)__popcll(m));
+          p = __shfl(p, __builtin_ctzll(m));
+          if (go) fresh[p + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = e[i];
+        }
+      }
+      __syncthreads();
+      for (unsigned long long b = reps; b; b &= b - 1ull) {  // alone unless a member marked the slot
+        const uint2 e = entry(tid + (uint32_t)__builtin_ctzll(b) * kBigThreads);
+        uint32_t pos, frag;
+        aim(e.x, pos, frag);
+        NB[e.y] = e.y | ((slot[pos] & 1u) ? 0u : kAlone);
+      }
+      left = uniform(sh[6 + (lo ^ 1u)]);
+      lo ^= 1u;
+      if (next < P) ++next;
+      else ++idle;
+      __syncthreads();
+      if (idle > 4096u) {  // (each throw places at least one group: a backstop)
+        status = kFusedFault;
+        break;
+      }
+      if (!dbl && left && next >= P && (idle & 7u) == 7u) {
+        // signatures that share a whole hash: another one separates them
+        ++rehash;
+        for (uint32_t x = tid; x < left; x += kBigThreads) {
+          const uint32_t q = LO[lo][x].y;
+          LO[lo][x].x = hash_one(q, seed0 + rehash * 0x9E3779B9u);
+        }
+        __syncthreads();
+      }
+    }
+    if (status != kFusedOk) break;
+    // ---- new ids; groups counted
+    uint32_t leaders = 0, stay = 0;
+    for (uint32_t i0 = 0; i0 < iters; i0 += kBigChunk) {
+      uint32_t v[kBigChunk];
+#pragma unroll
+      for (int i = 0; i < kBigChunk; ++i)
+        v[i] = ((live >> (i0 + i)) & 1ull) ? NB[tid + (i0 + i) * kBigThreads] : kNone;
+#pragma unroll
+      for (int i = 0; i < kBigChunk; ++i) {
+        const uint32_t q = tid + (i0 + i) * kBigThreads;
+        if (q >= n) continue;
+        if (v[i] == kNone) {  // alone before this round
+          ++leaders;
+          continue;
+        }
+        blk[q] = (uint16_t)v[i];
+        leaders += (uint32_t)((v[i] & 0xFFFFu) == q);
+        if (v[i] & kAlone) live &= ~(1ull << (i0 + i));
+        else ++stay;
+      }
+    }
+    leaders = wave_sum(leaders);
+    stay = wave_sum(stay);
+    if (lane == 0) {
+      atomicAdd(&sh[4], leaders);
+      atomicAdd(&sh[5], stay);
+    }
+    __syncthreads();
+    const uint32_t cnew = uniform(sh[4]);
+    alive = uniform(sh[5]);
+    __syncthreads();
+    if (tid < 2) sh[4 + tid] = 0;
+    ++rounds;
+    if (cnew == count) break;  // no block split: stable
+    ++refine;
+    used = max(used, l);
+    count = cnew;
+    jlen += dbl ? (1ull << l) : 1ull;
+    if (lvn) ++l;
+    if (count == n) break;
+  }
+  if (status != kFusedOk) {
+    if (tid == 0) {
+      R.status = status;
+      res[j] = R;
+    }
+    return;
+  }
+
+  // ---- canonical numbering: the least members' ranks (in NB) by wave
+  // counts in state order
+  __syncthreads();
+  for (uint32_t i = 0; i < iters; ++i) {
+    const uint32_t q = tid + i * kBigThreads;
+    const unsigned long long m = __ballot(q < n && blk[q] == q);
+    if (lane == 0) slot[i * kBigWaves + wave] = (uint32_t)__popcll(m);
+  }
+  __syncthreads();
+  if (wave == 0) {
+    uint32_t run = 0;
+    for (uint32_t c0 = 0; c0 < iters * kBigWaves; c0 += 64) {
+      const uint32_t c = c0 + lane, x = c < iters * kBigWaves ? slot[c] : 0u;
+      const uint32_t incl = wave_incl_scan(x);
+      if (c < iters * kBigWaves) slot[c] = run + incl - x;
+      run += __shfl(incl, 63);
+    }
+  }
+  __syncthreads();
+  // (each thread keeps its own states' ids in NB while the ranks replace the
+  // least members' entries of blk[])
+  const uint32_t id0 = blk[J.q0];
+  for (uint32_t i = 0; i < iters; ++i) {
+    const uint32_t q = tid + i * kBigThreads;
+    if (q < n) NB[q] = blk[q];
+  }
+  __syncthreads();
+  for (uint32_t i = 0; i < iters; ++i) {
+    const uint32_t q = tid + i * kBigThreads;
+    const bool lead = q < n && blk[q] == q;  // (only this thread writes blk[q])
+    const unsigned long long m = __ballot(lead);
+    if (lead) blk[q] = (uint16_t)(slot[i * kBigWaves + wave] + (uint32_t)__popcll(m & ((1ull << lane) - 1ull)));
+  }
+  __syncthreads();
+  uint32_t* __restrict__ out = reinterpret_cast<uint32_t*>(J.out);
+  for (uint32_t i0 = 0; i0 < iters; i0 += kBigChunk) {
+    uint32_t v[kBigChunk];
+#pragma unroll
+    for (int i = 0; i < kBigChunk; ++i) {
+      const uint32_t q = tid + (i0 + i) * kBigThreads;
+      v[i] = q < n ? NB[q] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < kBigChunk; ++i) {
+      const uint32_t q = tid + (i0 + i) * kBigThreads;
+      if (q < n) out[q] = blk[v[i]];
+    }
+  }
+  if (tid == 0) {
+    R.status = kFusedOk;
+    R.num_blocks = count;
+    R.initial_block = blk[id0];
+    R.refine_rounds = refine;
+    R.levels_used = used;
+    R.doubling = dbl ? 1u : 0u;
+    res[j] = R;
+  }
+}
+
 }  // namespace
 
 void launch_fused(const FusedJob* jobs, FusedRes* res, uint32_t njobs, int cls, hipStream_t s,
@@ -577,6 +1101,11 @@ void launch_fused(const FusedJob* jobs, FusedRes* res, uint32_t njobs, int cls, 
       break;
     default: hipLaunchKernelGGL((k_fused<16384, 1024>), g, dim3(1024), 0, s, jobs, res, njobs, arg); break;
   }
+}
+
+void launch_fused_big(const FusedJob* jobs, FusedRes* res, uint32_t njobs, hipStream_t s) {
+  if (!njobs) return;
+  hipLaunchKernelGGL(k_fused_big, dim3(njobs), dim3(kBigThreads), 0, s, jobs, res, njobs);
 }
 
 }  // namespace dfamin

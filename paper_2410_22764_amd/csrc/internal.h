@@ -179,7 +179,10 @@ struct FusedJob {
   uint32_t auto_rounds;  // AUTO: rounds after which an instance with >= 2 non-identity letters
                          // that is still splitting is handed back to the round engine
   uint32_t max_rounds;   // round cap
+  uint32_t validated;    // 1: every entry is known to be below n, and mask holds the
+  uint32_t mask;         // non-identity letters
   uint32_t pad;
+  uint64_t scratch;      // fused_big_scratch(n, k) bytes, 16-byte aligned (launch_fused_big only)
 };
 struct FusedRes {
   int32_t status;  // kFused*
@@ -202,6 +205,13 @@ constexpr int kFusedClasses = 4;
 inline int fused_class(uint32_t n) { return n <= 512 ? 0 : (n <= 2048 ? 1 : (n <= 8192 ? 2 : 3)); }
 // one (nullable): a single job passed by value (jobs is then ignored and
 // njobs taken as 1).  res may be mapped page-locked host memory.
+// Instances of a batch above kFusedMaxStates and up to kFusedBigStates
+// states, one workgroup each (the other conditions as above).
+constexpr uint32_t kFusedBigStates = 65536;
+inline uint64_t fused_big_scratch(uint32_t n, uint32_t k) {
+  return (((uint64_t)n + 3) & ~3ull) * (36 + 16 * (((uint64_t)k + 8) / 8)) + 64;
+}
+void launch_fused_big(const FusedJob* jobs, FusedRes* res, uint32_t njobs, hipStream_t s);
 void launch_fused(const FusedJob* jobs, FusedRes* res, uint32_t njobs, int cls, hipStream_t s,
                   const FusedJob* one = nullptr);
 

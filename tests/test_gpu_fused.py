@@ -265,3 +265,85 @@ def test_tile_edges_alone_and_batched(ctx, monkeypatch, n):
     outs, results = dfamin.dfamin_minimize_batch(ctx, ds, "auto")
     for d, out, res in zip(ds, outs, results):
         oracle_check(d, out, res)
+
+
+def _copies(n, k, classes, seed):
+    """Every state copies a state of a random automaton of `classes` states."""
+    r = np.random.RandomState(seed)
+    cls = r.permutation(np.concatenate([np.arange(classes), r.randint(0, classes, n - classes)]))
+    order = np.argsort(cls, kind="stable")
+    size = np.bincount(cls, minlength=classes)
+    start = np.cumsum(size) - size
+    base = r.randint(0, classes, (k, classes))
+    rows = np.stack([order[start[base[a][cls]] + (r.rand(n) * size[base[a][cls]]).astype(np.int64)] for a in range(k)])
+    return W.from_rows(rows, r.rand(classes)[cls] < 0.5, int(r.randint(n)), f"copies({n},{k},{classes})")
+
+
+def test_larger_instances_of_a_batch(ctx, monkeypatch):
+    """16,384 < n <= 65,536 in a batch: one workgroup each, with one throw or
+    several slices per round, against the round engine's result for each
+    instance alone and the oracle."""
+    from paper_2410_22764_amd import dfamin
+    ds = [W.random_dfa(n, k, n + k) for n in (16385, 24577, 32768, 40001, 65535, 65536) for k in (1, 2, 5, 6, 7, 8)]
+    ds += [W.random_dfa(20011, 11, 1), W.random_dfa(65536, 32, 2)]
+    ds += [W.permuted_chain_dfa(n, 2 + n % 3, n) for n in (16385, 33333, 65536)]
+    ds += [_copies(n, k, c, n) for n, k, c in ((16390, 2, 4000), (50021, 3, 20), (65536, 2, 9000), (65521, 6, 40000))]
+    ds += [W.fib_dfa(21), W.bitsplitter_dfa(15), W.bitsplitter_dfa(16), shift_dfa(17000, (1, 2), "shift")]
+    n = 30000  # degenerate: nothing accepting, everything, identity letters only
+    ident = np.tile(np.arange(n, dtype=np.uint32), (2, 1))
+    ds += [W.from_rows(ident, np.arange(n) % 2 == 0, 5), W.from_rows((ident + 1) % n, np.zeros(n, bool), 5),
+           W.from_rows((ident + 1) % n, np.ones(n, bool), 5)]
+    ds += [W.random_dfa(60000, 4, s) for s in range(24)]  # enough states for this path
+    ds += [W.random_dfa(500, 3, 1), W.random_dfa(9000, 2, 1), W.random_dfa(100003, 2, 1)]
+    for opts in (dict(), dict(closure="off", max_rounds=0), dict(max_levels=2, auto_rounds=3)):
+        if opts.get("closure") == "off":  # (plain rounds only: leave the deep ones out)
+            use = [d for d in ds if not d.name.startswith(("permuted", "Fib", "shift"))]
+        else:
+            use = [d for d in ds if opts.get("max_levels") != 2 or not d.name.startswith(("permuted", "Fib", "shift"))]
+        print(f"[case] {len(use)} instances, {opts}", flush=True)
+        outs, got = dfamin.dfamin_minimize_batch(ctx, use, opts or "auto")
+        mid = [d.n for d in use if 16384 < d.n <= 65536]
+        assert sum(mid) >= 48 * max(mid)
+        monkeypatch.setenv("DFAMIN_FUSED_MAX_STATES", "0")
+        for d, a, ra in zip(use, outs, got):
+            b, rb = dfamin.dfamin_minimize(ctx, d, opts or "auto")
+            assert np.array_equal(a, b) and ra == rb, (d.name, ra, rb)
+        monkeypatch.delenv("DFAMIN_FUSED_MAX_STATES")
+        if not opts:
+            for d, out, res in zip(use, outs, got):
+                oracle_check(d, out, res)
+    # a bad entry anywhere leaves every output alone; a round cap is reported
+    bad = W.random_dfa(40000, 2, 9)
+    bad.delta[3] = bad.n
+    rs = dfamin.dfamin_minimize_batch(ctx, ds + [bad], "auto", check=False)[1]
+    assert rs[-1]["status"] == dfamin.DFAMIN_E_BAD_DFA and rs[0]["rc"] == dfamin.DFAMIN_E_BAD_DFA
+    assert dfamin.dfamin_minimize_batch(ctx, ds, dict(max_rounds=2), check=False)[1][0]["rc"] == dfamin.DFAMIN_E_INTERNAL
+
+
+def test_larger_instances_give_way_to_the_budget(monkeypatch):
+    """Their scratch costs no call its memory: wherever a batch and a larger
+    call after it fit a context's budget without them, they fit with them."""
+    from paper_2410_22764_amd import dfamin
+    ds = [W.random_dfa(20000, 2, s) for s in range(60)] + [shift_dfa(17000, (1, 2), "shift"), W.random_dfa(70000, 2, 1)]
+    last = W.random_dfa(1000000, 4, 1)
+    seen = set()
+    for mib in (1024, 256, 192, 160, 128, 112, 96, 80, 64, 48, 24):
+        ends = []
+        for limit in ("16383", None):
+            print(f"[case] budget {mib} MiB, limit {limit}", flush=True)
+            if limit:
+                monkeypatch.setenv("DFAMIN_FUSED_MAX_STATES", limit)
+            else:
+                monkeypatch.delenv("DFAMIN_FUSED_MAX_STATES")
+            with dfamin.dfamin_create(0, mib << 20) as c:
+                outs, got = dfamin.dfamin_minimize_batch(c, ds, "auto", check=False)
+                one, alone = dfamin.dfamin_minimize(c, last, "auto", check=False)
+            ends.append((outs, got, one, alone))
+        (o0, g0, q0, a0), (o1, g1, q1, a1) = ends
+        ok = dfamin.DFAMIN_OK
+        if g0[0]["rc"] == ok:
+            assert all(np.array_equal(a, b) for a, b in zip(o0, o1)) and [r["rc"] for r in g1] == [ok] * len(ds), mib
+        if a0["rc"] == ok:
+            assert a1["rc"] == ok and np.array_equal(q0, q1), mib
+        seen.add((g0[0]["rc"], a0["rc"]))
+    assert len(seen) > 1, seen
