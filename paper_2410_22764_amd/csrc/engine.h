@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <string>
 #include <array>
 #include <map>
@@ -13,6 +14,23 @@
 #include "internal.h"
 
 namespace dfamin {
+
+// Workgroups of grid kernels in flight per device, over every context and
+// thread of the process: together at most one per CU, so that all of them can
+// be resident at once whatever order the hardware starts them in.
+struct GridLease {
+  std::atomic<uint32_t>* pool = nullptr;
+  uint32_t wgs = 0;
+  GridLease() = default;
+  GridLease(const GridLease&) = delete;
+  GridLease& operator=(const GridLease&) = delete;
+  bool take(int device, uint32_t want, uint32_t cus);
+  void give() {
+    if (pool) pool->fetch_sub(wgs);
+    pool = nullptr;
+  }
+  ~GridLease() { give(); }
+};
 
 // A device buffer that only grows; its bytes count against the context budget.
 struct DevBuf {

@@ -54,30 +54,26 @@ constexpr uint64_t kClearAheadSlots = 1ull << 22;  // 32 MiB: a few microseconds
 constexpr uint64_t kBigMinRatio = 48;
 constexpr uint32_t kQueueRounds = 8;               // queued signature rounds per graph (even)
 
-// Workgroups of grid kernels in flight per device, over every context and
-// thread of the process: together at most one per CU, so that all of them can
-// be resident at once whatever order the hardware starts them in.
-std::atomic<uint32_t> g_grid_wgs[64];
-struct GridLease {
-  std::atomic<uint32_t>* pool = nullptr;
-  uint32_t wgs = 0;
-  bool take(int device, uint32_t want, uint32_t cus) {
-    if (device < 0 || device >= 64) return false;
-    std::atomic<uint32_t>& p = g_grid_wgs[device];
-    uint32_t v = p.load();
-    do {
-      if (v + want > cus) return false;
-    } while (!p.compare_exchange_weak(v, v + want));
-    pool = &p;
-    wgs = want;
-    return true;
-  }
-  ~GridLease() {
-    if (pool) pool->fetch_sub(wgs);
-  }
-};
-
 }  // namespace
+
+namespace {
+std::atomic<uint32_t> g_grid_wgs[64];
+}
+
+bool GridLease::take(int device, uint32_t want, uint32_t cus) {
+  if (pool || device < 0 || device >= 64) return false;
+  std::atomic<uint32_t>& p = g_grid_wgs[device];
+  // (a launch spreads over eight dies with CUs of their own, so its share of
+  // each is what counts: an eighth, rounded up)
+  want = std::min((want + 7u) & ~7u, std::max(want, cus));
+  uint32_t v = p.load();
+  do {
+    if (v + want > cus) return false;
+  } while (!p.compare_exchange_weak(v, v + want));
+  pool = &p;
+  wgs = want;
+  return true;
+}
 
 // ------------------------------------------------------------------ Profiler
 Profiler::~Profiler() {

@@ -11,6 +11,10 @@
 //      on the device join at the next step, so their work overlaps;
 //   3. retires every request whose round split nothing: canonical numbering
 //      of its states only (segmented scan), copy-out, buffers released.
+// Requests of up to 524,288 states (closure OFF or AUTO) seldom get that far:
+// up to 16,384 states they run as batches of the fused kernel, above that one
+// by one on the grid kernel, both on streams of their own beside the resident
+// set, which takes what those kernels hand back.
 // Instances never interact: block ids are global state ids, so a request's
 // result is the same alone and in any mix.
 #include "serving.h"
@@ -41,6 +45,20 @@ constexpr uint32_t kSlots = 4096;               // resident requests at most
 constexpr uint64_t kDefaultArenaStates = 1ull << 26;
 constexpr uint32_t kDefaultAutoRounds = 8;
 constexpr size_t kMaxQueue = 1u << 16;
+// Grid kernels in flight at most.  Streams share a few hardware queues, and a
+// kernel holds up whatever stands behind it in its queue: of the 64 requests
+// below, uploads and small batches waited out other requests' kernels with
+// four lanes or eight (3.4 ms; two 3.1, one 3.6).
+constexpr uint32_t kLanes = 2;
+// Workgroups a request's grid kernel takes at most, so that both lanes fit the
+// CUs: up to 524,288 states at four per thread.  Larger requests are bound by
+// bandwidth, and the resident set's rounds, which take them all together, are
+// as fast (128 requests of up to 2^20 states: 42 ms both ways; with lanes that
+// take the whole chip for the largest, 38 against 32).
+constexpr uint32_t kLaneWgs = 128;
+// Rounds after which a lane hands its request over to the resident set, where
+// a cancellation takes effect between rounds (AUTO needs fewer).
+constexpr uint32_t kLaneRounds = 64;
 
 inline uint32_t ceil_log2_u64(uint64_t x) {
   uint32_t b = 0;
@@ -258,7 +276,8 @@ struct Resident {
   void* d_out = nullptr;
   void* d_sig = nullptr;
   std::vector<std::pair<void*, size_t>> closure_bufs;  // closure level storage
-  size_t sz_delta = 0, sz_accept = 0, sz_out = 0, sz_sig = 0;
+  size_t sz_delta = 0, sz_accept = 0,  // (0: the bitmap is the end of d_delta's block)
+         sz_out = 0, sz_sig = 0;
   std::vector<uint32_t> nonid;
   std::vector<uint64_t> rows;
   uint32_t rounds = 0;
@@ -353,6 +372,19 @@ struct Serving::Impl {
   std::vector<Resident*> fpend;  // small requests waiting for the next batch
   hipStream_t fstream = nullptr;
   hipEvent_t fev = nullptr;
+  // Larger requests run one per lane on the grid kernel (launch_lane)
+  struct Lane {
+    hipStream_t stream = nullptr;
+    hipEvent_t ev = nullptr;
+    void* bar = nullptr;  // GridBar, all zero between launches
+    HostBuf res;          // GridRes
+    GridLease lease;      // held while a request is in flight
+    Resident* r = nullptr;
+    void* scratch = nullptr;
+    size_t sz_scratch = 0;
+  };
+  Lane lanes[kLanes];
+  std::deque<Resident*> gpend;  // requests waiting for a lane
   uint32_t* h_last() { return reinterpret_cast<uint32_t*>(static_cast<char*>(h_ctrl.p) + sizeof(Ctrl)); }
 
   void shutdown() {
@@ -364,6 +396,7 @@ struct Serving::Impl {
     if (worker.joinable()) worker.join();
     // a fused batch may still be copying outputs into requests' buffers:
     // let it finish before their waiters wake
+    drain_lanes();
     if (fstream) (void)hipStreamSynchronize(fstream);
     if (std::getenv("DFAMIN_TRACE"))
       std::fprintf(stderr, "[dfamin] serving: %llu iterations, %llu joined; join %.0f us, rounds %.0f us\n",
@@ -435,13 +468,25 @@ struct Serving::Impl {
   void free_device() {
     if (ustream) (void)hipStreamSynchronize(ustream);  // uploads still reading host staging
     if (fstream) (void)hipStreamSynchronize(fstream);  // a fused batch still running
+    drain_lanes();
     staged.clear();
     fpend.clear();
+    gpend.clear();
     fb.fs.clear();
     fb.live = false;
     for (Resident* r : slots)
       if (r) release_resident(r);
     slots.clear();
+    for (Lane& l : lanes) {
+      if (l.bar) (void)hipFree(l.bar);
+      if (l.res.p) (void)hipHostFree(l.res.p);
+      if (l.ev) (void)hipEventDestroy(l.ev);
+      if (l.stream) (void)hipStreamDestroy(l.stream);
+      l.bar = nullptr;
+      l.res = HostBuf{};
+      l.ev = nullptr;
+      l.stream = nullptr;
+    }
     void** ps[] = {&d_block, &d_inst_of, &d_act, &d_act2, &d_slot_of, &d_nb, &d_keep, &d_rank,
                    &d_status, &d_table, &d_desc, &d_rows, &d_changed, &d_refine, &d_dead,
                    &d_minF, &d_minN, &d_ctrl, &d_results, &d_totals};
@@ -516,7 +561,7 @@ struct Serving::Impl {
   void release_resident(Resident* r) {
     if (r->up) free_events.push_back(r->up);
     pool.free(r->d_delta, r->sz_delta);
-    pool.free(r->d_accept, r->sz_accept);
+    if (r->sz_accept) pool.free(r->d_accept, r->sz_accept);
     pool.free(r->d_out, r->sz_out);
     pool.free(r->d_sig, r->sz_sig);
     for (auto& cb : r->closure_bufs) pool.free(cb.first, cb.second);
@@ -526,11 +571,24 @@ struct Serving::Impl {
     delete r;
   }
 
+  // Transitions and accept bits in one block, and one copy (about 10 us
+  // each on the device's side), wherever that takes no more memory than two.
+  static bool one_block(const Request& q) {
+    return DevicePool::size_class(q.delta_bytes() + q.accept_bytes()) <=
+           DevicePool::size_class(q.delta_bytes()) + DevicePool::size_class(q.accept_bytes());
+  }
+  bool put_inputs(Resident* r, hipStream_t s) {
+    r->uploaded = true;
+    return hipMemcpyAsync(r->d_delta, r->req->delta(), r->sz_delta, hipMemcpyHostToDevice, s) == hipSuccess &&
+           (!r->sz_accept || hipMemcpyAsync(r->d_accept, r->req->accept(), r->sz_accept, hipMemcpyHostToDevice,
+                                            s) == hipSuccess);
+  }
   // Device bytes a request needs besides the fixed per-state buffers.
   static size_t footprint(const Request& q) {
     const size_t n = q.n, k = q.k;
-    size_t b = DevicePool::size_class(4 * n * k) + DevicePool::size_class((n + 7) / 8) +
-               DevicePool::size_class(4 * n) + DevicePool::size_class(4 * n * (k + 1));
+    const size_t in = one_block(q) ? DevicePool::size_class(q.delta_bytes() + q.accept_bytes())
+                                   : DevicePool::size_class(4 * n * k) + DevicePool::size_class((n + 7) / 8);
+    size_t b = in + DevicePool::size_class(4 * n) + DevicePool::size_class(4 * n * (k + 1));
     if (q.opts.closure != DFAMIN_CLOSURE_OFF) {
       const size_t L = floor_log2_u32(q.n);
       b += DevicePool::size_class(4 * n * k * L) + DevicePool::size_class(4 * n * (k * (L + 1) + 1));
@@ -734,13 +792,7 @@ struct Serving::Impl {
       }
       r->up = free_events.back();
       free_events.pop_back();
-      if (hipMemcpyAsync(r->d_delta, r->req->delta(), r->sz_delta, hipMemcpyHostToDevice, ustream) !=
-              hipSuccess ||
-          hipMemcpyAsync(r->d_accept, r->req->accept(), r->req->accept_bytes(), hipMemcpyHostToDevice,
-                         ustream) != hipSuccess ||
-          hipEventRecord(r->up, ustream) != hipSuccess)
-        return DFAMIN_E_DEVICE;
-      r->uploaded = true;
+      if (!put_inputs(r, ustream) || hipEventRecord(r->up, ustream) != hipSuccess) return DFAMIN_E_DEVICE;
       staged.push_back(r);
     }
     return DFAMIN_OK;
@@ -770,12 +822,18 @@ struct Serving::Impl {
     jobs.assign(F, FusedJob{});
     fb.pos.assign(F, 0);
     uint32_t at = 0, start[kFusedClasses] = {};
+    uint32_t top = 0;
+    for (Resident* r : fb.fs) top = std::max(top, r->req->n);
+    // A batch that leaves CUs idle runs as one launch, in the tile of its
+    // largest: every request then starts at once, where a launch per class
+    // takes the classes' longest one after another.
+    auto class_of = [&](uint32_t n) { return fused_class(F <= ctx->cus ? top : n); };
     for (int cls = kFusedClasses - 1; cls >= 0; --cls) {
       start[cls] = at;
       for (size_t w = 0; w < F; ++w) {
         Resident* r = fb.fs[w];
         const Request& q = *r->req;
-        if (fused_class(q.n) != cls) continue;
+        if (class_of(q.n) != cls) continue;
         FusedJob& J = jobs[at];
         J.delta = reinterpret_cast<uint64_t>(r->d_delta);
         J.accept = reinterpret_cast<uint64_t>(r->d_accept);
@@ -795,18 +853,12 @@ struct Serving::Impl {
       if ((F > 1 && !grow(s_fjobs, F * sizeof(FusedJob))) || !grow_host(h_fres, F * sizeof(FusedRes)))
       return DFAMIN_E_NOMEM;
     for (Resident* r : fb.fs) {
-      if (r->uploaded) continue;
-      if (hipMemcpyAsync(r->d_delta, r->req->delta(), r->sz_delta, hipMemcpyHostToDevice, fstream) !=
-              hipSuccess ||
-          hipMemcpyAsync(r->d_accept, r->req->accept(), r->req->accept_bytes(), hipMemcpyHostToDevice,
-                         fstream) != hipSuccess)
-        return DFAMIN_E_DEVICE;
-      r->uploaded = true;
+      if (!r->uploaded && !put_inputs(r, fstream)) return DFAMIN_E_DEVICE;
     }
     // one job travels as a kernel argument
     FusedRes* res = static_cast<FusedRes*>(h_fres.dp);
     if (F == 1) {
-      launch_fused(nullptr, res, 1, fused_class(jobs[0].n), fstream, &jobs[0]);
+      launch_fused(nullptr, res, 1, class_of(jobs[0].n), fstream, &jobs[0]);
     } else {
       if (hipMemcpyAsync(s_fjobs.p, jobs.data(), F * sizeof(FusedJob), hipMemcpyHostToDevice, fstream) !=
           hipSuccess)
@@ -866,16 +918,177 @@ struct Serving::Impl {
     return DFAMIN_OK;
   }
 
+  // Requests above kFusedMaxStates states (closure OFF or AUTO) go one by one
+  // through the grid kernel, which runs all their rounds in one launch (a
+  // hundred to a few hundred microseconds), as soon as their inputs are on the
+  // device: in the resident set a round is half a dozen launches, a copy back
+  // and a wait, ~150 us whoever takes part, and joining another 140.  A lane
+  // is a stream, an event and a barrier; the kernel's arrays come from the
+  // pool.  A request joins the resident set where there is no room for them,
+  // where the kernel hands it back (it needs closure letters, or more than
+  // kLaneRounds rounds) or reports that its workgroups were not all resident.  (64 requests of 256 to 131,072
+  // states, submitted at once: 4.65 -> 2.65 ms, of which their submits take
+  // 1.4.)
+  bool grid_takes(const Request& q, uint32_t* items, uint32_t* wgs) const {
+    if (q.n <= kFusedMaxStates || q.k > kFusedMaxLetters || q.opts.method != DFAMIN_METHOD_SIGNATURE ||
+        (q.opts.closure != DFAMIN_CLOSURE_AUTO && q.opts.closure != DFAMIN_CLOSURE_OFF))
+      return false;
+    if (const char* e = std::getenv("DFAMIN_GRID_MAX_STATES"))  // testing: 0 turns the grid kernel off
+      if ((long)q.n > std::atol(e)) return false;
+    return grid_shape(q.n, std::min(kLaneWgs, ctx->cus), items, wgs);
+  }
+  bool any_lane() const {
+    for (const Lane& l : lanes)
+      if (l.r) return true;
+    return false;
+  }
+  void drain_lanes() {
+    for (Lane& l : lanes) {
+      if (!l.r) continue;
+      (void)hipStreamSynchronize(l.stream);
+      pool.free(l.scratch, l.sz_scratch);
+      l.r = nullptr;
+      l.lease.give();
+    }
+  }
+  // Launches r on lane l; false (nothing queued): no memory for it.
+  bool launch_lane(Lane& l, Resident* r, uint32_t items, uint32_t wgs, int* rc) {
+    const Request& q = *r->req;
+    const size_t n = q.n;
+    if (!l.stream) {
+      void* bar = dmalloc(sizeof(GridBar));
+      if (!bar) return false;
+      l.bar = bar;
+      if (hipStreamCreateWithFlags(&l.stream, hipStreamNonBlocking) != hipSuccess ||
+          hipEventCreateWithFlags(&l.ev, hipEventDisableTiming) != hipSuccess ||
+          hipMemsetAsync(bar, 0, sizeof(GridBar), l.stream) != hipSuccess) {
+        *rc = DFAMIN_E_DEVICE;
+        return false;
+      }
+    }
+    if (!grow_host(l.res, sizeof(GridRes))) return false;
+    uint32_t L = floor_log2_u32(q.n);
+    if (q.opts.max_levels && q.opts.max_levels < L) L = q.opts.max_levels;
+    const uint32_t S = (uint32_t)((4 * n + 7) & ~size_t(7));
+    const size_t n4 = (4 * n + 255) & ~size_t(255);
+    l.sz_scratch = 6 * n4 + 16ull * S + 8ull * wgs;
+    // (with the level storage a unary request would have in the resident set:
+    // without room for that it refines plainly there, and does so still)
+    if (pool.live() + DevicePool::size_class(l.sz_scratch) + 4ull * L * n > pool.budget()) return false;
+    l.scratch = pool.alloc(l.sz_scratch);
+    if (!l.scratch) return false;
+    if (!r->req->out.make(pinned, 4ull * n)) {
+      pool.free(l.scratch, l.sz_scratch);
+      return false;
+    }
+    char* at = static_cast<char*>(l.scratch);
+    GridJob J{};
+    J.delta = reinterpret_cast<uint64_t>(r->d_delta);
+    J.accept = reinterpret_cast<uint64_t>(r->d_accept);
+    J.out = reinterpret_cast<uint64_t>(r->d_out);
+    J.n = q.n;
+    J.k = q.k;
+    J.q0 = q.q0;
+    J.closure = q.opts.closure;
+    J.levels = L;
+    J.auto_rounds = q.opts.auto_rounds ? q.opts.auto_rounds : kDefaultAutoRounds;
+    J.max_rounds = kLaneRounds;
+    J.S = S;
+    J.table[0] = reinterpret_cast<unsigned long long*>(at);
+    J.table[1] = J.table[0] + S;
+    at += 16ull * S;
+    for (int i = 0; i < 2; ++i, at += n4) J.blk[i] = reinterpret_cast<uint32_t*>(at);
+    for (int i = 0; i < 2; ++i, at += 2 * n4) J.pr[i] = reinterpret_cast<uint2*>(at);
+    J.rank = reinterpret_cast<uint32_t*>(J.pr[0]);
+    J.wgw = reinterpret_cast<uint32_t*>(at);
+    J.rec = q.k > grid_letters_kept(items) ? static_cast<uint32_t*>(r->d_sig) : nullptr;
+    J.bar = static_cast<GridBar*>(l.bar);
+    J.res = static_cast<GridRes*>(l.res.dp);
+    J.salt = 0x5DEECE66Dull;
+    GridRes* h = l.res.as<GridRes>();
+    *h = GridRes{};
+    h->status = kGridAborted;
+    launch_grid(J, items, wgs, l.stream);
+    l.r = r;
+    if (hipGetLastError() != hipSuccess ||
+        hipMemcpyAsync(r->req->out.data(), r->d_out, 4ull * n, hipMemcpyDeviceToHost, l.stream) != hipSuccess ||
+        hipEventRecord(l.ev, l.stream) != hipSuccess)
+      *rc = DFAMIN_E_DEVICE;
+    return true;
+  }
+  // Publishes the lanes that are done; requests handed back go to `back`.
+  int collect_lanes(std::vector<Resident*>& back, bool wait) {
+    for (Lane& l : lanes) {
+      if (!l.r) continue;
+      const hipError_t e = wait ? hipEventSynchronize(l.ev) : hipEventQuery(l.ev);
+      wait = false;
+      if (e == hipErrorNotReady) continue;
+      if (e != hipSuccess) return DFAMIN_E_DEVICE;
+      Resident* r = l.r;
+      l.r = nullptr;
+      l.lease.give();
+      pool.free(l.scratch, l.sz_scratch);
+      const GridRes& f = *l.res.as<GridRes>();
+      auto req = r->req;
+      const uint32_t ar = req->opts.auto_rounds ? req->opts.auto_rounds : kDefaultAutoRounds;
+      // (a request whose states are all told apart by the very round after
+      // which AUTO's closure letters come takes them in the resident set)
+      const bool letters = req->opts.closure == DFAMIN_CLOSURE_AUTO && !f.doubling && f.rounds == ar;
+      if (f.aborted || (f.status != kFusedOk && f.status != kFusedBad) ||
+          (f.status == kFusedOk && letters && f.num_blocks == req->n)) {
+        back.push_back(r);
+        continue;
+      }
+      int st = DFAMIN_E_BAD_DFA;
+      if (f.status == kFusedOk) {
+        dfamin_result& o = req->result;
+        o.num_blocks = f.num_blocks;
+        o.initial_block = f.initial_block;
+        o.refine_rounds = f.refine_rounds;
+        o.rounds_executed = f.refine_rounds + 1;
+        o.closure_levels = f.doubling ? f.levels_used : 0;
+        o.closure_letters = f.doubling ? f.levels_used + 1 : 0;
+        o.status = st = DFAMIN_OK;
+      }
+      req->in.release();
+      if (st != DFAMIN_OK) req->out.release();
+      const bool cancelled = req->cancelled;
+      release_resident(r);
+      finish(req, cancelled && st == DFAMIN_OK ? DFAMIN_E_CANCELLED : st);
+    }
+    return DFAMIN_OK;
+  }
+  // Starts waiting requests on free lanes; those that cannot go to `back`.
+  int launch_lanes(std::vector<Resident*>& back) {
+    int rc = DFAMIN_OK;
+    while (rc == DFAMIN_OK && !gpend.empty()) {
+      Lane* l = nullptr;
+      for (Lane& x : lanes)
+        if (!x.r) {
+          l = &x;
+          break;
+        }
+      if (!l) break;
+      Resident* r = gpend.front();
+      uint32_t items = 0, wgs = 0;
+      (void)grid_takes(*r->req, &items, &wgs);
+      if (!l->lease.take(ctx->device, wgs, ctx->cus)) {
+        if (any_lane()) break;  // one of ours ends and makes room
+        back.push_back(r);      // other contexts hold the CUs
+      } else if (!launch_lane(*l, r, items, wgs, &rc)) {
+        l->lease.give();
+        if (rc == DFAMIN_OK) back.push_back(r);
+      }
+      gpend.pop_front();
+    }
+    return rc;
+  }
+
   // Bring newly admitted requests into the resident set.
   int join(std::vector<Resident*>& js) {
     // upload inputs
     for (Resident* r : js) {
-      if (r->uploaded) continue;
-      if (hipMemcpyAsync(r->d_delta, r->req->delta(), r->sz_delta, hipMemcpyHostToDevice, stream) !=
-              hipSuccess ||
-          hipMemcpyAsync(r->d_accept, r->req->accept(), r->req->accept_bytes(), hipMemcpyHostToDevice,
-                         stream) != hipSuccess)
-        return DFAMIN_E_DEVICE;
+      if (!r->uploaded && !put_inputs(r, stream)) return DFAMIN_E_DEVICE;
     }
     // validation and identity letters: one row job per (request, letter)
     std::vector<RowJob> jobs;
@@ -1163,8 +1376,10 @@ struct Serving::Impl {
   void fail_all(int rc) {
     if (ustream) (void)hipStreamSynchronize(ustream);  // uploads still reading host staging
     if (fstream) (void)hipStreamSynchronize(fstream);  // a fused batch still running
+    drain_lanes();
     staged.clear();
     fpend.clear();
+    gpend.clear();
     fb.fs.clear();
     fb.live = false;
     std::vector<std::shared_ptr<Request>> rs;
@@ -1229,12 +1444,14 @@ struct Serving::Impl {
           r->req = q;
           r->slot = slot;
           r->off = off;
-          r->sz_delta = 4ull * q->n * q->k;
-          r->sz_accept = (q->n + 7) / 8;
+          const bool whole = one_block(*q);
+          r->sz_delta = q->delta_bytes() + (whole ? q->accept_bytes() : 0);
+          r->sz_accept = whole ? 0 : q->accept_bytes();
           r->sz_out = 4ull * q->n;
           r->sz_sig = 4ull * q->n * (q->k + 1);
           r->d_delta = pool.alloc(r->sz_delta);
-          r->d_accept = pool.alloc(r->sz_accept);
+          r->d_accept = !whole ? pool.alloc(r->sz_accept)
+                               : (r->d_delta ? static_cast<char*>(r->d_delta) + q->delta_bytes() : nullptr);
           r->d_out = pool.alloc(r->sz_out);
           r->d_sig = pool.alloc(r->sz_sig);
           slots[slot] = r;
@@ -1257,7 +1474,8 @@ struct Serving::Impl {
       // requests whose inputs are on the device join, in admission order;
       // with nothing else to run, wait for the oldest upload
       if (rc == DFAMIN_OK && !staged.empty()) {
-        if (!any_joined() && hipEventSynchronize(staged.front()->up) != hipSuccess) rc = DFAMIN_E_DEVICE;
+        if (!any_joined() && !any_lane() && hipEventSynchronize(staged.front()->up) != hipSuccess)
+          rc = DFAMIN_E_DEVICE;
         size_t take = 0;
         while (rc == DFAMIN_OK && take < staged.size()) {
           const hipError_t e = hipEventQuery(staged[take]->up);
@@ -1273,12 +1491,23 @@ struct Serving::Impl {
       const auto t0 = std::chrono::steady_clock::now();
       if (!joining.empty()) {
         std::vector<Resident*> rest;
-        for (Resident* r : joining) (fusable(*r->req) ? fpend : rest).push_back(r);
+        uint32_t items, wgs;
+        for (Resident* r : joining) {
+          if (fusable(*r->req)) fpend.push_back(r);
+          else if (grid_takes(*r->req, &items, &wgs)) gpend.push_back(r);
+          else rest.push_back(r);
+        }
         joining.swap(rest);
       }
+      if (rc == DFAMIN_OK && any_lane()) {
+        // with nothing else to run, wait for a kernel in flight
+        const bool idle = !any_joined() && joining.empty() && staged.empty() && !fb.live && fpend.empty();
+        rc = collect_lanes(joining, idle);
+      }
+      if (rc == DFAMIN_OK && !gpend.empty()) rc = launch_lanes(joining);
       if (rc == DFAMIN_OK && fb.live) {
         // with nothing else to run, wait for the batch in flight
-        const bool idle = !any_joined() && joining.empty() && staged.empty();
+        const bool idle = !any_joined() && joining.empty() && staged.empty() && !any_lane();
         const hipError_t e = idle ? hipEventSynchronize(fev) : hipEventQuery(fev);
         if (e == hipSuccess) rc = collect_fused(joining);
         else if (e != hipErrorNotReady) rc = DFAMIN_E_DEVICE;
@@ -1292,6 +1521,7 @@ struct Serving::Impl {
       t_round += std::chrono::duration<double, std::micro>(t2 - t1).count();
       iters += 1;
       joined += joining.size();
+      if (any_lane() && !any_joined()) std::this_thread::yield();  // (polling for whichever ends first)
       if (rc != DFAMIN_OK) {
         fail_all(rc);
         m = 0;

@@ -282,3 +282,84 @@ def test_small_request_batches_beside_rounds(ctx):
     assert rc == dfamin.DFAMIN_E_BAD_DFA
     rc, out, res = dfamin.dfamin_wait(ctx, tl, long.n, timeout_us=60_000_000)
     assert rc == dfamin.DFAMIN_OK and np.array_equal(out, np.arange(long.n))
+
+
+def test_larger_requests_on_lanes(monkeypatch):
+    """Requests above 16,384 states run on the grid kernel, one per lane: the
+    results are those of the resident set (DFAMIN_GRID_MAX_STATES=0) and the
+    oracle's, for requests that finish there, that need closure letters, more
+    rounds than a lane runs, or a round count that takes AUTO's letters at the
+    end; invalid and cancelled ones are reported as ever."""
+    from paper_2410_22764_amd import dfamin
+    reqs = [(W.random_dfa(n, k, n), {"closure": c}) for n, k, c in
+            ((16385, 2, "auto"), (65536, 9, "auto"), (65537, 1, "auto"), (100003, 3, "off"), (262145, 2, "auto"),
+             (20000, 32, "auto"), (20000, 33, "auto"), (40000, 2, "on"))]
+    reqs += [(W.permuted_chain_dfa(n, k, n), {"closure": "auto"}) for n, k in ((16390, 2), (120000, 5))]
+    reqs += [(_double_step_chain(17000, 3), {"closure": "auto"}), (W.bitsplitter_dfa(15), {"closure": "auto"}),
+             (W.bitsplitter_dfa(15), {"closure": "off"}), (W.chain_dfa(16400, 1), {"closure": "auto", "max_levels": 3})]
+    reqs += [(W.random_dfa(50000, 2, 5), {"closure": "auto", "auto_rounds": r}) for r in (1, 2, 3, 4, 5)]
+    n = 17001  # more plain rounds than a lane runs, few enough for the resident set
+    ids = np.arange(n)
+    step = W.from_rows(np.minimum(ids + 100, n - 1).astype(np.uint32)[None], ids == n - 1, 7, "step chain")
+    reqs.append((step, {"closure": "off"}))
+    bad = W.random_dfa(30000, 2, 7)
+    bad.delta = bad.delta.copy()
+    bad.delta[12345] = bad.n
+    gone = W.random_dfa(60000, 3, 8)
+    ends = []
+    for off in (True, False):
+        if off:
+            monkeypatch.setenv("DFAMIN_GRID_MAX_STATES", "0")
+        else:
+            monkeypatch.delenv("DFAMIN_GRID_MAX_STATES")
+        print(f"[case] serving {len(reqs) + 2} larger requests, lanes {'off' if off else 'on'}", flush=True)
+        with dfamin.dfamin_create(0) as c:
+            tk = [dfamin.dfamin_submit(c, d, o) for d, o in reqs]
+            tb, tg = dfamin.dfamin_submit(c, bad, "auto"), dfamin.dfamin_submit(c, gone, "auto")
+            dfamin.dfamin_cancel(c, tg)
+            ends.append([dfamin.dfamin_wait(c, t, d.n, timeout_us=60_000_000) for t, (d, _) in zip(tk, reqs)])
+            assert dfamin.dfamin_wait(c, tb, bad.n, timeout_us=60_000_000)[0] == dfamin.DFAMIN_E_BAD_DFA
+            assert dfamin.dfamin_wait(c, tg, gone.n, timeout_us=60_000_000)[0] in (
+                dfamin.DFAMIN_OK, dfamin.DFAMIN_E_CANCELLED)
+    for (d, o), (r0, o0, s0), (r1, o1, s1) in zip(reqs, *ends):
+        assert r0 == r1 == dfamin.DFAMIN_OK, (d.name, o)
+        assert np.array_equal(o0, o1) and s0 == s1, (d.name, o, s0, s1)
+        want, nb = oracle.hopcroft(d.n, d.k, d.delta, d.accept)
+        assert s1["num_blocks"] == nb and np.array_equal(o1, want) and s1["initial_block"] == want[d.q0], (d.name, o)
+
+
+def test_lanes_of_several_contexts():
+    """Two serving contexts and a thread of single calls share the CUs."""
+    import threading
+    from paper_2410_22764_amd import dfamin
+    ds = [W.random_dfa(20000 + 9000 * i, 2 + i % 3, i) for i in range(12)]
+    want = [oracle.hopcroft(d.n, d.k, d.delta, d.accept)[0] for d in ds]
+    print("[case] two serving contexts and single calls", flush=True)
+    errs = []
+
+    def serve():
+        try:
+            with dfamin.dfamin_create(0) as c:
+                for _ in range(3):
+                    tk = [dfamin.dfamin_submit(c, d, "auto") for d in ds]
+                    for t, d, w in zip(tk, ds, want):
+                        rc, out, _ = dfamin.dfamin_wait(c, t, d.n, timeout_us=60_000_000)
+                        assert rc == dfamin.DFAMIN_OK and np.array_equal(out, w), d.name
+        except Exception as e:  # reported by the main thread
+            errs.append(repr(e))
+
+    def single():
+        try:
+            with dfamin.dfamin_create(0) as c:
+                for _ in range(3):
+                    for d, w in zip(ds, want):
+                        assert np.array_equal(dfamin.dfamin_minimize(c, d, "auto")[0], w), d.name
+        except Exception as e:
+            errs.append(repr(e))
+
+    ts = [threading.Thread(target=f) for f in (serve, serve, single)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not errs, errs
