@@ -296,6 +296,8 @@ class Engine {
   hipStream_t fused_stream_ = nullptr, big_stream_ = nullptr;
   hipEvent_t fused_ready_ = nullptr, fused_done_ = nullptr, big_done_ = nullptr;
   DevBuf d_fbig_;                     // their scratch
+  bool large_ok_ = false;             // this call may take the rounds of large.hip
+  DevBuf d_uniq_;                     // rounds by unique hashes: the sample's table, the bucket cursors
   std::vector<uint32_t> big_order_;   // longest first
   bool big_busy_ = false;             // d_fbig_ is in use by this call
   bool no_big_ = false;               // this call does without

@@ -19,6 +19,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <chrono>
+#include <cmath>
 #include <cstring>
 
 namespace dfamin {
@@ -44,6 +45,15 @@ inline uint64_t mix64(uint64_t z) {
 }
 
 constexpr uint32_t kDefaultAutoRounds = 8;
+// Single instances above the grid kernel's sizes (large.hip)
+constexpr uint64_t kLargeStates = (1ull << 20) + 1;
+// The sample for a round by unique hashes is taken after the second round by
+// labels, and from these sizes on after the first one (five letters or more)
+// and after the count table's round (three): it costs about 20 us, 2% of a call
+// of 2,500,000 states with copied ones (six letters, 1.20 ms) where a random
+// one gains 30% (0.60 -> 0.42 ms); with three letters a random one gains 10% at
+// that size and 20% at 4,100,000 (0.89 -> 0.73).
+constexpr uint64_t kSampleStates = 1ull << 21, kSampleStates3 = 1ull << 22;
 constexpr uint64_t kClearAheadSlots = 1ull << 22;  // 32 MiB: a few microseconds to clear
 // Larger instances of a batch take one workgroup each (launch_fused_big) when
 // together they have at least this many times the states of the largest: an
@@ -172,7 +182,7 @@ Engine::~Engine() {
                     &d_keep_, &d_rank_, &d_sig_, &d_table_, &d_status_, &d_changed_, &d_rb_,
                     &d_results_, &d_wgflags_, &d_part_, &d_dense_,
                     &d_djobs_, &d_visit_, &d_bfs_rows_, &d_min_delta_, &d_min_acc_,
-                    &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_fbig_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
+                    &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_fbig_, &d_uniq_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
   if (d_gbar_.p) (void)hipFree(d_gbar_.p);
   // device buffers of the fixed-region mode belong to the region
   if (!fixed()) {
@@ -193,7 +203,7 @@ uint64_t Engine::device_bytes() const {
                           &d_keep_, &d_rank_, &d_sig_, &d_table_, &d_status_, &d_changed_, &d_rb_,
                           &d_results_, &d_wgflags_, &d_part_, &d_dense_,
                           &d_djobs_, &d_visit_, &d_bfs_rows_, &d_min_delta_, &d_min_acc_,
-                          &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_fbig_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
+                          &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_fbig_, &d_uniq_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
   uint64_t t = d_gbar_.cap;
   for (const DevBuf* b : bufs) t += b->cap;
   for (const DevBuf& b : closure_bufs_) t += b.cap;
@@ -298,7 +308,7 @@ void Engine::reset_fixed_region() {
                     &d_results_, &d_wgflags_, &d_part_, &d_dense_,
                     &d_djobs_, &d_visit_, &d_bfs_rows_, &d_min_delta_, &d_min_acc_,
                     &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_ctrl_, &d_refine_, &d_counts_,
-                    &d_fjobs_, &d_fbig_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
+                    &d_fjobs_, &d_fbig_, &d_uniq_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
   for (DevBuf* b : bufs) *b = DevBuf{};
   closure_bufs_.clear();
   fixed_off_ = 0;
@@ -790,6 +800,45 @@ int Engine::signature_rounds(const dfamin_opts& opts, uint64_t max_rounds, hipSt
   uint32_t n_dirty = 0;
   auto now = [] { return std::chrono::steady_clock::now(); };
   auto us = [](auto a, auto b) { return std::chrono::duration<double, std::micro>(b - a).count(); };
+  // The early rounds of one large instance (large.hip): the round after the
+  // labels as a second round of labels, and a round that a sample says leaves
+  // nearly every state alone.  uniq: such a round is planned -- hashed letters
+  // (0: none), the source of its blocks -- and its sample has been queued;
+  // uniq_rest: the round under way does the rest of one.
+  const bool large = slots_ok && large_ok_;
+  uint32_t uniq = 0, uniq_bits = 0;
+  int uniq_width = 4;
+  bool uniq_rest = false;
+  const size_t nib_at = (N + 255) & ~uint64_t(255);  // where d_dense_ has the first round's nib
+  bool uncounted = false;  // a second round by labels whose blocks have not been counted
+  UniqTest uniq_test;
+  bool sampled = false;
+  auto plan_uniq = [&](double lb, double lb_before, uint32_t before, int width, const void* src) -> int {
+    // own block and t letters tell about lb + t * (lb - lb_before) bits; with
+    // six more than the states need, one in 64 of them still meets another
+    const double need = std::log2((double)N) + 6.0;
+    const uint32_t kp = desc_[0].kp;
+    uint32_t t = 1;
+    while (t <= kp && lb + t * (lb - lb_before) < need) ++t;
+    uniq_bits = ceil_log2_u64((N + kUniqBucket - 1) / kUniqBucket);
+    if (sampled || t > kp || (1u << uniq_bits) > kUniqBuckets) return DFAMIN_OK;
+    sampled = true;
+    // about half of kUniqSample states: one block and sel of the 2^lb / 2
+    // that its first letter may lead to, or one block in sel + 1
+    const double pairs = std::exp2(2.0 * lb - 1.0);
+    const uint32_t sel = width == 1 ? (uint32_t)std::ceil(pairs * (kUniqSample / 2) / N)
+                                    : (uint32_t)(1ull << ceil_log2_u64(N / (kUniqSample / 2))) - 1u;
+    const double frac = width == 1 ? sel / pairs : 1.0 / (sel + 1.0);
+    prof.begin(s, "uniq_sample", (double)width * N);
+    launch_uniq_sample(d_desc_.as<InstDesc>(), d_rows_.as<uint64_t>(), src, width, t, sel,
+                       d_uniq_.as<uint32_t>(), d_ctrl_.as<Ctrl>(), s);
+    prof.end(s);
+    uniq = t;
+    uniq_width = width;
+    uniq_test.expect = std::max<uint32_t>(256, (uint32_t)(frac * N / 4));
+    uniq_test.before = before;
+    return check_hip(hipGetLastError());
+  };
   auto tp0 = now();
   while (m > 0) {
     tp0 = now();
@@ -914,15 +963,18 @@ int Engine::signature_rounds(const dfamin_opts& opts, uint64_t max_rounds, hipSt
       prof.begin(s, "label", lb);
       // one-byte labels become the dense numbers in place; two-byte ones
       // are kept in the (here unused) new-id array
+      uint8_t* nib = large && desc_[0].kp == 4 ? d_dense_.as<uint8_t>() + nib_at : nullptr;
       launch_label(d_desc_.as<InstDesc>(), d_inst_off_.as<uint32_t>(), (uint32_t)I, init_wgs_,
                    d_rows_.as<uint64_t>(), label_bits_, lmin, rank, lw == 1 ? d_dense_.p : d_nb_.p,
                    d_dense_.as<uint8_t>(), d_counts_.as<uint32_t>(), d_changed_.as<uint32_t>(), d_ctrl_.as<Ctrl>(),
                    d_block_.as<uint32_t>(), 1u, (uint32_t)m, d_act_.as<uint32_t>(),
-                   batch ? d_inst_of_.as<uint32_t>() : nullptr, s);
+                   batch ? d_inst_of_.as<uint32_t>() : nullptr, s, nib);
       prof.end(s);
       launch_round_end((uint32_t)I, d_changed_.as<uint32_t>(), d_refine_.as<uint32_t>(), nullptr,
                        d_ctrl_.as<Ctrl>(), s);
       HIP(hipGetLastError());
+      if (large && N >= kSampleStates && desc_[0].kp >= 5 && label_bits_ <= 8 && !dbl[0])
+        TRY(plan_uniq(desc_[0].kp + 1.0, 1.0, 2, 1, d_dense_.p));
       // control block, refine counters and every instance's label count
       TRY(readback(h_rb_, d_rb_.p, sizeof(Ctrl) + 8 * I, s));
       // One instance's next round may group in a count table of at most
@@ -934,7 +986,7 @@ int Engine::signature_rounds(const dfamin_opts& opts, uint64_t max_rounds, hipSt
         if (!ev_rb_) HIP(hipEventCreateWithFlags(&ev_rb_, hipEventDisableTiming));
         HIP(hipEventRecord(ev_rb_, s));
         const uint32_t bits = (desc_[0].kp + 1u) * (desc_[0].kp + 1u);
-        if (!batch && slots_ok && !direct_off_ && !fixed() && bits <= kDirectMaxBits && bits >= 1 &&
+        if (!(large && desc_[0].kp == 4) && !batch && slots_ok && !direct_off_ && !fixed() && bits <= kDirectMaxBits && bits >= 1 &&
             (1ull << bits) <= 8ull * m) {
           TRY(ensure(d_dtab_, 4ull << bits));
           launch_clear_table(d_dtab_.as<Slot>(), 1ull << (bits - 1), d_ctrl_.as<Ctrl>(), s, 0, gcount);
@@ -957,6 +1009,7 @@ int Engine::signature_rounds(const dfamin_opts& opts, uint64_t max_rounds, hipSt
       const size_t before = alist.size();
       settle(h_refine);
       dense_from_labels = true;
+      if (!uniq_test.go(c.u_count, c.u_dup)) uniq = 0;
       if (I == 1) all_single_ = cnt[0] >= in_[0].n;
       if (!c.any_changed || alist.empty()) break;
       if (alist.size() < before) {
@@ -989,6 +1042,99 @@ int Engine::signature_rounds(const dfamin_opts& opts, uint64_t max_rounds, hipSt
       }
       continue;
     }
+    // The second round by labels (launch_label2): four letters, whose 2^21 keys
+    // are too many for the count table to be in any cache and few beside the
+    // states (2^24 states: 0.44 ms instead of 1.28; with three letters the
+    // count table's 2^16 words do as well, with five the keys are too long)
+    const bool one = large && m == N && alist.size() == 1 && !dbl[0] && !has_closure_[0];
+    if (one && rounds == 1 && dense_from_labels && cnt_ok[0] && desc_[0].ebits && desc_[0].kp == 4 &&
+        !would_scan(0)) {
+      TRY(ensure(d_table_, (1ull << ceil_log2_u64(2 * N)) * sizeof(Slot)));  // 32 MiB at least
+      prof.begin(s, "label2", (double)N * (0.125 + 4.5 * 4 + 0.5 + 4.0));
+      launch_label2(d_desc_.as<InstDesc>(), d_rows_.as<uint64_t>(), (uint32_t)N, d_dense_.as<uint8_t>() + nib_at,
+                    d_nb_.as<uint32_t>(), ctx_->cus, s);
+      prof.end(s);
+      TRY(plan_uniq(std::min((double)kLabel2Bits, std::log2((double)N)),
+                    std::log2((double)std::max<uint64_t>(cnt[0], 2)), (uint32_t)cnt[0], 4, d_nb_.p));
+      // (a unique-hash round has 3/4 of the states alone and needs no count of
+      // the blocks where the keys are fewer)
+      const bool lazy_count = uniq && (1ull << kLabel2Bits) < N - N / 4;
+      launch_label2_end((uint32_t)N, d_nb_.as<uint32_t>(), d_table_.as<uint32_t>(), (uint32_t)cnt[0], gcount,
+                        lazy_count ? uniq_test : UniqTest{}, d_changed_.as<uint32_t>(), d_ctrl_.as<Ctrl>(), s);
+      launch_round_end(1, d_changed_.as<uint32_t>(), d_refine_.as<uint32_t>(), nullptr, d_ctrl_.as<Ctrl>(), s);
+      HIP(hipGetLastError());
+      TRY(readback(h_rb_, d_rb_.p, sizeof(Ctrl) + 4, s));
+      spec_clear = 0;
+      if (!prof.enabled()) {
+        if (!ev_rb_) HIP(hipEventCreateWithFlags(&ev_rb_, hipEventDisableTiming));
+        HIP(hipEventRecord(ev_rb_, s));
+        if (!uniq) {  // the hash round's table, while the host plans
+          const uint64_t next = 1ull << ceil_log2_u64(2 * m);
+          TRY(ensure(d_table_, next * sizeof(Slot)));
+          launch_clear_table(d_table_.as<Slot>(), next, d_ctrl_.as<Ctrl>(), s, 0, gcount);
+          HIP(hipGetLastError());
+          spec_clear = next;
+        }
+        HIP(event_wait(ev_rb_));
+      } else {
+        HIP(stream_wait(s));
+      }
+      stage_flip();
+      prof.collect();
+      const Ctrl c = *h_rb_.as<Ctrl>();
+      if (c.fault) return DFAMIN_E_INTERNAL;
+      cnt_ok[0] = 0;
+      ++rounds;
+      settle(reinterpret_cast<const uint32_t*>(h_rb_.as<char>() + sizeof(Ctrl)));
+      dense_from_labels = false;
+      if (trace)
+        std::fprintf(stderr, "[dfamin] round 2 by labels: %u blocks (0: not counted), next round by unique hashes of %u letters: %u\n",
+                     c.prev_shared, uniq, (unsigned)uniq_test.go(c.u_count, c.u_dup));
+      if (!c.any_changed) break;  // (the ids in d_block_ stand)
+      std::swap(d_block_, d_nb_);
+      slot_prev = true;
+      if (!uniq_test.go(c.u_count, c.u_dup)) uniq = 0;
+      uncounted = lazy_count && uniq;
+      continue;
+    }
+    // A round by unique hashes (launch_uniq_round); what may share one stays
+    // for the ordinary round below.
+    if (one && uniq && rounds > 0 &&
+        ensure(d_table_, (1ull << std::max<uint32_t>(9, ceil_log2_u64(2 * N))) * sizeof(Slot)) == DFAMIN_OK) {
+      uint32_t* cursor = d_uniq_.as<uint32_t>() + kUniqTable;
+      const void* src = uniq_width == 1 ? d_dense_.p : d_block_.p;
+      prof.begin(s, "uniq", (double)N * (uniq_width * (1.0 + uniq) + 4.0 * uniq + 16.0));
+      launch_uniq_round(d_desc_.as<InstDesc>(), d_rows_.as<uint64_t>(), (uint32_t)N, src, uniq_width, uniq,
+                        d_table_.p, cursor, uniq_bits, nxt, d_ctrl_.as<Ctrl>(), s);
+      prof.end(s);
+      HIP(hipGetLastError());
+      TRY(readback(h_rb_, d_rb_.p, sizeof(Ctrl), s));
+      HIP(stream_wait(s));
+      stage_flip();
+      prof.collect();
+      const Ctrl c = *h_rb_.as<Ctrl>();
+      uniq = 0;
+      spec_clear = 0;
+      const uint64_t blocks = cnt_ok[0] ? cnt[0] : (uncounted ? 1ull << kLabel2Bits : c.prev_shared);
+      if (trace) std::fprintf(stderr, "[dfamin] %u states may share a signature, overflow %u\n", c.u_rest, c.u_over);
+      if (!c.u_over && c.u_rest <= N / 4 && N - c.u_rest > blocks) {
+        if (c.u_rest == 0) {
+          launch_uniq_apply((uint32_t)N, d_block_.as<uint32_t>(), d_changed_.as<uint32_t>(), d_ctrl_.as<Ctrl>(), s);
+          launch_round_end(1, d_changed_.as<uint32_t>(), d_refine_.as<uint32_t>(), nullptr, d_ctrl_.as<Ctrl>(), s);
+          HIP(hipGetLastError());
+          ++rounds;
+          all_single_ = true;
+          break;
+        }
+        std::swap(cur, nxt);
+        m = c.u_rest;
+        uniq_rest = true;
+      }
+    }
+    if (uncounted && !uniq_rest)
+      launch_label2_count((uint32_t)N, d_block_.as<uint32_t>(), d_table_.as<uint32_t>(), gcount,
+                          d_ctrl_.as<Ctrl>(), s);
+    uncounted = false;
     // Table: twice the number of groups this round can form, at most m.  An
     // exact-key instance forms at most 2^((kp+1) * ebits) groups.
     uint64_t groups = 0;
@@ -1244,6 +1390,8 @@ int Engine::signature_rounds(const dfamin_opts& opts, uint64_t max_rounds, hipSt
                      d_status_.as<unsigned long long>(), ntiles, s, 0,
                      tuned_now ? nullptr : d_notify_.as<uint8_t>(), slot_prev ? gcount : nullptr);
       prof.end(s);
+      if (uniq_rest)
+        launch_uniq_apply((uint32_t)N, d_block_.as<uint32_t>(), d_changed_.as<uint32_t>(), d_ctrl_.as<Ctrl>(), s);
       prof.begin(s, "compact", md * (4 + inst_b + 4 + 1 + 4));
       launch_compact(batch, cur, (uint32_t)m, d_inst_of_.as<uint32_t>(), d_nb_.as<uint32_t>(),
                      d_keep_.as<uint8_t>(), d_changed_.as<uint32_t>(), nullptr, d_block_.as<uint32_t>(),
@@ -1284,6 +1432,9 @@ int Engine::signature_rounds(const dfamin_opts& opts, uint64_t max_rounds, hipSt
       prof.end(s);
     }
     HIP(hipGetLastError());
+    if (one && slot_round && N >= kSampleStates3 && rounds == 1 && desc_[0].kp == 3)
+      TRY(plan_uniq(std::min(13.0, std::log2((double)N)), std::log2((double)std::max<uint64_t>(cnt[0], 2)),
+                    (uint32_t)cnt[0], 4, d_block_.p));
     // one copy: control block, refine counters, and the counts just scanned
     TRY(readback(h_rb_, d_rb_.p, sizeof(Ctrl) + 4 * I + 4 * (size_t)ns, s));
     // Work of the next round that needs none of this round's results is
@@ -1358,7 +1509,9 @@ int Engine::signature_rounds(const dfamin_opts& opts, uint64_t max_rounds, hipSt
     retries = 0;  // the bound is on redoing one round
     settle(h_refine);
     dense_from_labels = false;
+    uniq_rest = false;
     slot_prev = slot_round;
+    if (!uniq_test.go(c.u_count, c.u_dup)) uniq = 0;
     // one instance, and this round split blocks and kept no state (every
     // block is a singleton), or counted n blocks
     if (I == 1) all_single_ = (c.any_changed && c.m_next == 0) || (cnt_ok[0] && cnt[0] >= in_[0].n);
@@ -2355,6 +2508,12 @@ int Engine::run_path(const std::vector<InstInput>& in, const dfamin_opts& opts, 
   TRY(queue_fill(d_notify_.p, 0, N, s));
   TRY(queue_fill(d_refine_.p, 0, I * 4, s));
   TRY(queue_fill(d_ctrl_.p, 0, sizeof(Ctrl), s));
+  large_ok_ = labels_planned_ && !batch && !direct_off_ && !fixed() && N >= kLargeStates &&
+              ctx_->tuner.forced < 0 && cas_forced_ < 0;
+  if (large_ok_) {
+    TRY(ensure(d_uniq_, 4ull * (kUniqTable + kUniqBuckets)));
+    TRY(queue_fill(d_uniq_.p, 0, 4ull * (kUniqTable + kUniqBuckets), s));
+  }
   if (labels_planned_) {
     // the first round's least member per label: all ones (none yet); then
     // the labels' numbers, one or two bytes each

@@ -118,7 +118,11 @@ struct Ctrl {
   uint64_t salt;          // queued signature rounds: hash salt of the coming round
   uint64_t hash_mask;     // testing: nonzero keeps only these bits of a signature hash
   uint32_t prev_shared;   // shared groups of the last round that ended with slot labels
-  uint32_t pad0[19];
+  // rounds of nearly unique signatures (launch_uniq_sample / _round)
+  uint32_t u_count, u_dup;  // states sampled, repeats among their hashes
+  uint32_t u_rest;          // states that may share a signature
+  uint32_t u_over;          // a bucket overflowed: the round goes the ordinary way
+  uint32_t pad0[15];
   uint32_t tile_counter;  // dynamic tile ids for the look-back scans
   uint32_t pad1[31];
 };
@@ -388,6 +392,55 @@ void launch_compact(bool batch, const uint32_t* act, uint32_t m, const uint32_t*
 void launch_round_end(uint32_t ninst, uint32_t* changed_inst, uint32_t* refine_cnt, uint32_t* last,
                       Ctrl* ctrl, hipStream_t s, unsigned long long* clear_status = nullptr,
                       uint32_t clear_tiles = 0, int gmode = 0);
+// Whether a sample (launch_uniq_sample) says that the next round leaves nearly
+// every state a block of its own: few repeats, and not much smaller a sample
+// than blocks of about one size would give (expect: a quarter of that; else
+// large blocks are not in it).  More hashes than there were blocks before the
+// round that the sample is taken after (before) also say that that round
+// split: a stable partition has no more signatures than blocks.
+constexpr uint32_t kUniqSample = 16384, kUniqTable = 2 * kUniqSample;
+struct UniqTest {
+  uint32_t expect = 0xffffffffu, before = 0;  // (as they are: never)
+  __host__ __device__ bool go(uint32_t count, uint32_t dup) const {
+    return count >= expect && count <= kUniqSample && dup <= count / 32u && count - dup > before;
+  }
+};
+// The second round of one large instance with four letters, after a round by
+// labels that left the successors' accept bits in nib: label[q] = kSlotLabel |
+// exact key of q's signature, kLabel2Bits bits.  launch_label2_end, with
+// `before` blocks before the round, sets m_next = n and changed_inst[0] where
+// the round split, and prev_shared, the keys that occur; these are not counted
+// where lazy, from the sample taken, says that the round split (later, if
+// needed: launch_label2_count).  maps: kLabel2Maps * 128 KiB; part:
+// kGroupCounters words.
+constexpr uint32_t kLabel2Bits = 21, kLabel2Maps = 256;
+void launch_label2(const InstDesc* desc, const uint64_t* rows, uint32_t n, const uint8_t* nib, uint32_t* label,
+                   uint32_t cus, hipStream_t s);
+void launch_label2_count(uint32_t n, const uint32_t* label, uint32_t* maps, uint32_t* part, Ctrl* ctrl,
+                         hipStream_t s);
+void launch_label2_end(uint32_t n, const uint32_t* label, uint32_t* maps, uint32_t before, uint32_t* part,
+                       UniqTest lazy, uint32_t* changed_inst, Ctrl* ctrl, hipStream_t s);
+// A round in which nearly all states of one instance become blocks of their
+// own.  src: the blocks, as one-byte numbers (width 1) or words (width 4), of
+// which the own one and those of the first `letters` letters are hashed.
+// launch_uniq_sample looks at some of the states, all of a signature or none
+// (one-byte numbers: own 0 and the first letter's below sel; words: the blocks
+// whose hash has the bits of sel clear; table: kUniqTable words, all zero).
+// launch_uniq_round appends the states that may share a signature to list
+// (ctrl->u_rest of them, in no order); entries: 2^pbits * kUniqCap pairs, the
+// average bucket at most kUniqBucket; cursor: 2^pbits words, all zero.
+// launch_uniq_apply ends the round for the others, between the resolve and the
+// compaction step of the rest.  (One sample and one such round per call: the
+// words of Ctrl, the table and the cursors are cleared with the call's state.)
+constexpr uint32_t kUniqBucket = 16384, kUniqCap = 20480;
+constexpr uint32_t kUniqBuckets = 2048;  // at most
+constexpr uint64_t kUniqSeed = 0x452821E638D01377ull;
+void launch_uniq_sample(const InstDesc* desc, const uint64_t* rows, const void* src, int width, uint32_t letters,
+                        uint32_t sel, uint32_t* table, Ctrl* ctrl, hipStream_t s);
+void launch_uniq_round(const InstDesc* desc, const uint64_t* rows, uint32_t n, const void* src, int width,
+                       uint32_t letters, void* entries, uint32_t* cursor, uint32_t pbits, uint32_t* list, Ctrl* ctrl,
+                       hipStream_t s);
+void launch_uniq_apply(uint32_t n, uint32_t* block, uint32_t* changed_inst, const Ctrl* ctrl, hipStream_t s);
 // Queued signature rounds: start (stop, iterations and retries cleared,
 // m_cur and salt set) and the one-thread step that ends each round: after a
 // hash collision a new salt (the round is redone; too many set fault and
@@ -408,7 +461,7 @@ void launch_copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t s);
 // mapped for the device) to dst, src null sets `bytes` bytes of dst to fill.
 // For host-to-device staging only: a copy to host memory needs
 // launch_copy_bytes, which makes its stores visible to the host.
-constexpr uint32_t kMemSegs = 8;
+constexpr uint32_t kMemSegs = 10;
 struct MemSeg {
   void* dst;
   const void* src;
@@ -494,12 +547,15 @@ void launch_dense_jobs(const InstDesc* desc, const uint32_t* slot, const uint32_
 // blocks; dense may be label itself when labels are one byte), act[g] = g
 // and inst_of[g] = i (nullable): the initial partition need not be
 // computed first.  The round flags of ctrl are cleared, and with set_m
-// m_next is set to m (every state stays active).
+// m_next is set to m (every state stays active).  nib (nullable; one instance
+// of up to four letters): the accept bits of each state's successors, four
+// bits per state, the even one's below.
 constexpr uint32_t kMaxLabelLetters = 8;
 void launch_label(const InstDesc* desc, const uint32_t* job_wg_off, uint32_t ninst, uint32_t total_wgs,
                   const uint64_t* rows, uint32_t label_bits, uint32_t* lmin, void* rank, void* label,
                   uint8_t* dense, uint32_t* counts, uint32_t* changed_inst, Ctrl* ctrl, uint32_t* block,
-                  uint32_t set_m, uint32_t m, uint32_t* act, uint32_t* inst_of, hipStream_t s);
+                  uint32_t set_m, uint32_t m, uint32_t* act, uint32_t* inst_of, hipStream_t s,
+                  uint8_t* nib = nullptr);
 // One instance whose blocks are all singletons: out[q] = q and its results
 // (n blocks, initial block q0).
 void launch_identity_out(const InstDesc* desc, uint32_t n, const uint32_t* refine_cnt, ResultDev* res,

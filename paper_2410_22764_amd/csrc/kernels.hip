@@ -1587,8 +1587,10 @@ __global__ __launch_bounds__(NL) void k_label_rank(const uint32_t* __restrict__ 
 // g (every state in order: list position and state id agree) and
 // inst_of[g] = i where given.  With one-byte labels, dense may be label
 // itself (each thread reads its state's label before it writes there).
+// nib (nullable; one instance of up to four letters): the accept bits of each
+// state's successors, four bits per state, for launch_label2.
 // Algorithmic bytes per state: sizeof(LT) (label) + 1 (dense) + 4 (id) + 4
-// (act) [+4 inst_of].
+// (act) [+4 inst_of] [+ 1/2 nib].
 template <int NL, typename LT>
 __global__ __launch_bounds__(kBlock) void k_label_apply(const InstDesc* __restrict__ desc,
                                                         const uint32_t* __restrict__ job_wg_off,
@@ -1596,7 +1598,8 @@ __global__ __launch_bounds__(kBlock) void k_label_apply(const InstDesc* __restri
                                                         const LT* __restrict__ rank, const LT* label,
                                                         uint8_t* dense, uint32_t* __restrict__ block,
                                                         uint32_t* __restrict__ act,
-                                                        uint32_t* __restrict__ inst_of) {
+                                                        uint32_t* __restrict__ inst_of,
+                                                        uint8_t* __restrict__ nib) {
   __shared__ uint32_t s_job;
   const uint32_t i = find_job(job_wg_off, ninst, &s_job);
   const InstDesc D = desc[i];
@@ -1606,9 +1609,13 @@ __global__ __launch_bounds__(kBlock) void k_label_apply(const InstDesc* __restri
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const uint32_t q = base + e * kBlock + threadIdx.x;
-    if (q >= D.n) continue;
     const uint32_t g = D.state_off + q;
-    const uint32_t L = label[g];
+    const uint32_t L = q < D.n ? label[g] : 0u;
+    if (nib) {  // the lanes of a pair of states share a byte
+      const uint32_t mine = (L >> 1) & 15u, other = __shfl_xor(mine, 1, 64);
+      if (!(q & 1u) && q < D.n) nib[q >> 1] = (uint8_t)(mine | other << 4);
+    }
+    if (q >= D.n) continue;
     dense[g] = (uint8_t)rk[L];
     block[g] = lm[L];
     act[g] = g;
@@ -1942,27 +1949,27 @@ template <int NL, typename LT>
 void launch_label_t(const InstDesc* desc, const uint32_t* job_wg_off, uint32_t ninst, uint32_t total_wgs,
                     const uint64_t* rows, uint32_t* lmin, void* rank, void* label, uint8_t* dense,
                     uint32_t* counts, uint32_t* changed_inst, Ctrl* ctrl, uint32_t* block, uint32_t set_m,
-                    uint32_t m, uint32_t* act, uint32_t* inst_of, hipStream_t s) {
+                    uint32_t m, uint32_t* act, uint32_t* inst_of, uint8_t* nib, hipStream_t s) {
   hipLaunchKernelGGL((k_label<NL, LT>), dim3(total_wgs), dim3(kBlock), 0, s, desc, job_wg_off, ninst, rows, lmin,
                      static_cast<LT*>(label));
   hipLaunchKernelGGL((k_label_rank<NL, LT>), dim3(ninst), dim3(NL), 0, s, lmin, static_cast<LT*>(rank), counts,
                      changed_inst, ctrl, set_m, m);
   hipLaunchKernelGGL((k_label_apply<NL, LT>), dim3(total_wgs), dim3(kBlock), 0, s, desc, job_wg_off, ninst, lmin,
-                     static_cast<const LT*>(rank), static_cast<const LT*>(label), dense, block, act, inst_of);
+                     static_cast<const LT*>(rank), static_cast<const LT*>(label), dense, block, act, inst_of, nib);
 }
 }  // namespace
 
 void launch_label(const InstDesc* desc, const uint32_t* job_wg_off, uint32_t ninst, uint32_t total_wgs,
                   const uint64_t* rows, uint32_t label_bits, uint32_t* lmin, void* rank, void* label,
                   uint8_t* dense, uint32_t* counts, uint32_t* changed_inst, Ctrl* ctrl, uint32_t* block,
-                  uint32_t set_m, uint32_t m, uint32_t* act, uint32_t* inst_of, hipStream_t s) {
+                  uint32_t set_m, uint32_t m, uint32_t* act, uint32_t* inst_of, hipStream_t s, uint8_t* nib) {
   if (!total_wgs || !ninst) return;
   if (label_bits <= 8)
     launch_label_t<256, uint8_t>(desc, job_wg_off, ninst, total_wgs, rows, lmin, rank, label, dense, counts,
-                                 changed_inst, ctrl, block, set_m, m, act, inst_of, s);
+                                 changed_inst, ctrl, block, set_m, m, act, inst_of, nib, s);
   else
     launch_label_t<512, uint16_t>(desc, job_wg_off, ninst, total_wgs, rows, lmin, rank, label, dense, counts,
-                                  changed_inst, ctrl, block, set_m, m, act, inst_of, s);
+                                  changed_inst, ctrl, block, set_m, m, act, inst_of, nib, s);
 }
 
 void launch_identity_out(const InstDesc* desc, uint32_t n, const uint32_t* refine_cnt, ResultDev* res,
