@@ -20,10 +20,9 @@ struct ClosureSpec {
   uint32_t L = 0;                    // levels 1..L at most
 };
 
-// Scratch the builder may grow: ensure(buffer_index, bytes) returns the
-// device pointer (index 0: jobs, 1: job offsets, 2: flags, 3: per-workgroup
-// flags) or nullptr when memory runs out; host_flags(bytes) a pinned host
-// buffer.  level_storage(bytes) returns device memory for a batch of closure
+// Scratch the builder may grow: device(bytes) returns device memory for its
+// jobs, their offsets and flags, or nullptr when memory runs out;
+// host_flags(bytes) a pinned host buffer.  level_storage(bytes) returns device memory for a batch of closure
 // rows that must stay valid while the rows are used, or nullptr to stop
 // building (out of memory or over the caller's cap): the levels built so far
 // are kept, which is sound because any subset of closure letters preserves
@@ -33,7 +32,7 @@ struct ClosureSpec {
 // host_flags buffer, each returning false on failure; when unset, plain
 // hipMemcpyAsync copies are queued.
 struct ClosureScratch {
-  std::function<void*(int, size_t)> ensure;
+  std::function<void*(size_t)> device;
   std::function<void*(size_t)> host_flags;
   std::function<void*(size_t)> level_storage;
   std::function<bool(void*, const void*, size_t)> upload;

@@ -5,6 +5,7 @@
 #include <chrono>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 
 #include "../../include/dfamin.h"
 
@@ -81,28 +82,31 @@ int build_closure_levels(std::vector<ClosureSpec>& specs, const ClosureScratch& 
       max_wgs = std::max(max_wgs, wgs);
     }
     lvl_begin.push_back((uint32_t)jobs.size());
-    RowJob* d_jobs = static_cast<RowJob*>(scratch.ensure(0, jobs.size() * sizeof(RowJob)));
-    uint32_t* d_off = static_cast<uint32_t*>(scratch.ensure(1, joboff.size() * 4));
-    uint32_t* d_flags = static_cast<uint32_t*>(scratch.ensure(2, jobs.size() * 4));
-    uint32_t* d_wg = static_cast<uint32_t*>(scratch.ensure(3, (size_t)max_wgs * 4));
-    uint32_t* h_flags = static_cast<uint32_t*>(scratch.host_flags(jobs.size() * 4));
-    if (!d_jobs || !d_off || !d_flags || !d_wg || !h_flags) return DFAMIN_E_NOMEM;
-    auto up = [&](void* d, const void* h, size_t bytes) {
-      return scratch.upload ? scratch.upload(d, h, bytes)
-                            : hipMemcpyAsync(d, h, bytes, hipMemcpyHostToDevice, s) == hipSuccess;
-    };
-    if (!up(d_jobs, jobs.data(), jobs.size() * sizeof(RowJob)) || !up(d_off, joboff.data(), joboff.size() * 4))
+    // jobs, workgroup offsets and cleared flags, in one upload
+    const size_t jb = jobs.size() * sizeof(RowJob), ob = joboff.size() * 4, fb = jobs.size() * 4;
+    char* d_jobs = static_cast<char*>(scratch.device(jb + ob + fb + (size_t)max_wgs * 4));
+    uint32_t* d_wg = reinterpret_cast<uint32_t*>(d_jobs + jb + ob + fb);
+    uint32_t* h_flags = static_cast<uint32_t*>(scratch.host_flags(fb));
+    if (!d_jobs || !h_flags) return DFAMIN_E_NOMEM;
+    uint32_t* d_off = reinterpret_cast<uint32_t*>(d_jobs + jb);
+    uint32_t* d_flags = reinterpret_cast<uint32_t*>(d_jobs + jb + ob);
+    std::vector<char> up(jb + ob + fb);
+    std::memcpy(up.data(), jobs.data(), jb);
+    std::memcpy(up.data() + jb, joboff.data(), ob);
+    if (!(scratch.upload ? scratch.upload(d_jobs, up.data(), up.size())
+                         : hipMemcpyAsync(d_jobs, up.data(), up.size(), hipMemcpyHostToDevice, s) == hipSuccess))
       return DFAMIN_E_DEVICE;
     for (uint32_t b = 0; b < batch; ++b) {
       const uint32_t lb = lvl_begin[b], le = lvl_begin[b + 1];
       if (lb == le) continue;
-      launch_closure_level(d_jobs + lb, d_off + lb, le - lb, lvl_wgs[b], d_wg, d_flags + lb, s);
+      launch_closure_level(reinterpret_cast<RowJob*>(d_jobs) + lb, d_off + lb, le - lb, lvl_wgs[b], d_wg,
+                           d_flags + lb, s);
     }
     if (hipGetLastError() != hipSuccess) return DFAMIN_E_DEVICE;
     const auto t1 = now();
     const bool copied = scratch.flags_to_host
-                            ? scratch.flags_to_host(d_flags, jobs.size() * 4)
-                            : hipMemcpyAsync(h_flags, d_flags, jobs.size() * 4, hipMemcpyDeviceToHost, s) == hipSuccess;
+                            ? scratch.flags_to_host(d_flags, fb)
+                            : hipMemcpyAsync(h_flags, d_flags, fb, hipMemcpyDeviceToHost, s) == hipSuccess;
     if (!copied || stream_wait(s) != hipSuccess) return DFAMIN_E_DEVICE;
     if (trace)
       std::fprintf(stderr, "[dfamin] closure levels %u..%u: %zu jobs, %zu words, host %.0f us, device wait %.0f us\n",

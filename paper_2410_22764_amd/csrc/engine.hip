@@ -427,10 +427,7 @@ int Engine::build_closure(const std::vector<uint32_t>& which, const dfamin_opts&
   const uint64_t cap = closure_cap();
   uint64_t taken = 0;
   ClosureScratch scratch;
-  DevBuf* bufs[4] = {&d_jobs_, &d_joboff_, &d_flags_, &d_wgflags_};
-  scratch.ensure = [&](int b, size_t bytes) -> void* {
-    return ensure(*bufs[b], bytes) == DFAMIN_OK ? bufs[b]->p : nullptr;
-  };
+  scratch.device = [&](size_t bytes) -> void* { return ensure(d_jobs_, bytes) == DFAMIN_OK ? d_jobs_.p : nullptr; };
   scratch.host_flags = [&](size_t bytes) -> void* {
     return ensure_host(h_flags_, bytes) == DFAMIN_OK ? h_flags_.p : nullptr;
   };

@@ -275,7 +275,8 @@ __global__ __launch_bounds__(kBlock) void k_row_check(const RowJob* __restrict__
 __global__ __launch_bounds__(kBlock) void k_closure_level(const RowJob* __restrict__ jobs,
                                                           const uint32_t* __restrict__ job_wg_off,
                                                           uint32_t njobs,
-                                                          uint32_t* __restrict__ wg_flags) {
+                                                          uint32_t* __restrict__ wg_flags,
+                                                          uint32_t* __restrict__ flags) {
   __shared__ uint32_t s_job, s_or;
   const uint32_t wg = xcd_contiguous(blockIdx.x, gridDim.x);  // a row's tiles share one L2
   const uint32_t j = find_job(job_wg_off, njobs, &s_job, wg);
@@ -301,9 +302,13 @@ __global__ __launch_bounds__(kBlock) void k_closure_level(const RowJob* __restri
       if (s2 != q) bits |= kFlagNonId;
     }
   }
-  if (wg_flags) {  // the same for the whole grid
+  if (wg_flags || flags) {  // the same for the whole grid
     const uint32_t w = block_or(bits, &s_or);
-    if (threadIdx.x == 0) wg_flags[wg] = w;
+    if (threadIdx.x == 0) {
+      if (wg_flags) wg_flags[wg] = w;
+      // (a coherent read: an XCD's L2 would go on holding the zero)
+      else if (w & ~__hip_atomic_load(&flags[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicOr(&flags[j], w);
+    }
   }
 }
 
@@ -1662,12 +1667,17 @@ void launch_row_check(const RowJob* jobs, const uint32_t* job_wg_off, uint32_t n
                      wg_flags, flags);
 }
 
+// Small levels or their flags straight away; in large ones a thousand
+// workgroups would wait for one word, and a launch that reduces a word each
+// costs less (2^20 states, level by level: 14 us against 19; 3,000 states, all
+// levels: 0.76 against 0.82 ms of a call, 100,000: 0.88 against 0.94).
 void launch_closure_level(const RowJob* jobs, const uint32_t* job_wg_off, uint32_t njobs,
                           uint32_t total_wgs, uint32_t* wg_flags, uint32_t* flags, hipStream_t s) {
   if (!total_wgs) return;
+  const bool direct = total_wgs <= 256u;
   hipLaunchKernelGGL(k_closure_level, dim3(total_wgs), dim3(kBlock), 0, s, jobs, job_wg_off, njobs,
-                     flags ? wg_flags : nullptr);
-  if (flags)
+                     flags && !direct ? wg_flags : nullptr, direct ? flags : nullptr);
+  if (flags && !direct)
     hipLaunchKernelGGL(k_flags_reduce, dim3(njobs), dim3(kBlock), 0, s, job_wg_off, njobs, total_wgs,
                        wg_flags, flags);
 }

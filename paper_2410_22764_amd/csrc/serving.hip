@@ -359,7 +359,7 @@ struct Serving::Impl {
   size_t rows_cap = 0;
   uint64_t table_cap = 0;
   // scratch that grows
-  DevBuf s_jobs, s_off, s_flags, s_wg, s_part, s_slot, s_aux, s_fjobs;
+  DevBuf s_jobs, s_wg, s_part, s_slot, s_aux, s_fjobs;
   HostBuf h_flags, h_ctrl, h_results, h_fres;  // h_ctrl: a Ctrl, then the per-slot flags of d_last
   std::vector<char> job_stage;                 // host side of upload_jobs
   std::vector<uint32_t> join_list;             // host side of a join's job list
@@ -493,7 +493,7 @@ struct Serving::Impl {
     for (void** p : ps)
       if (*p) { (void)hipFree(*p); *p = nullptr; }
     d_last = nullptr;  // part of d_ctrl's allocation
-    DevBuf* db[] = {&s_jobs, &s_off, &s_flags, &s_wg, &s_part, &s_slot, &s_aux, &s_fjobs};
+    DevBuf* db[] = {&s_jobs, &s_wg, &s_part, &s_slot, &s_aux, &s_fjobs};
     for (DevBuf* b : db)
       if (b->p) { (void)hipFree(b->p); b->p = nullptr; b->cap = 0; }
     HostBuf* hb[] = {&h_flags, &h_ctrl, &h_results, &h_fres};
@@ -725,10 +725,7 @@ struct Serving::Impl {
 
   ClosureScratch scratch() {
     ClosureScratch sc;
-    sc.ensure = [this](int b, size_t bytes) -> void* {
-      DevBuf* bufs[4] = {&s_jobs, &s_off, &s_flags, &s_wg};
-      return grow(*bufs[b], bytes) ? bufs[b]->p : nullptr;
-    };
+    sc.device = [this](size_t bytes) -> void* { return grow(s_jobs, bytes) ? s_jobs.p : nullptr; };
     sc.host_flags = [this](size_t bytes) -> void* { return grow_host(h_flags, bytes) ? h_flags.p : nullptr; };
     return sc;
   }
