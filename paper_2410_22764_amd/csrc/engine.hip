@@ -57,9 +57,9 @@ constexpr uint64_t kSampleStates = 1ull << 21, kSampleStates3 = 1ull << 22;
 constexpr uint64_t kClearAheadSlots = 1ull << 22;  // 32 MiB: a few microseconds to clear
 // Larger instances of a batch take one workgroup each (launch_fused_big) when
 // together they have at least this many times the states of the largest: an
-// instance alone on its CU takes longer (65,536 states, two letters: 1.1 ms)
-// than a few of them in the round engine (16: 0.6 ms; 64: 1.3 against 1.2 ms;
-// 256: 4.0 against 2.2 ms; 30,000 states: even at 16, 0.74 against 0.47 ms at
+// instance alone on its CU takes longer (65,536 states, two letters: 1.0 ms)
+// than a few of them in the round engine (16: 0.6 ms; 64: 1.3 against 1.15 ms;
+// 256: 4.0 against 1.8 ms; 30,000 states: even at 16, 0.74 against 0.46 ms at
 // 64).
 constexpr uint64_t kBigMinRatio = 48;
 constexpr uint32_t kQueueRounds = 8;               // queued signature rounds per graph (even)

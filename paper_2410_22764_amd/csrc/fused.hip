@@ -559,14 +559,15 @@ __global__ void __launch_bounds__(NT, 4) k_fused(const FusedJob* __restrict__ jo
 // throw left.  Bound: LDS operations and the row reads of each round, on as
 // many CUs as there are instances; a round of the round engine moves the same
 // states through device atomics (27 G/s) and a dozen launches instead.  A
-// random instance of 65,536 states and two letters takes 1.1 ms (six rounds
-// of 40 us hashing and, in three, 150 us of throws), 256 of them 2.2 ms
-// (round engine: 4.0), 512 chains of that size 6.2 ms (22.9); a batch of 1,272
-// instances up to 65,536 states went from 10.2 to 3.6 ms.
+// random instance of 65,536 states and two letters takes 1.0 ms (six rounds
+// of 40 us hashing and, in three, 150 us of throws), 256 of them 1.8 ms
+// (round engine: 4.0), 512 chains of that size 5.5 ms (22.9); a batch of 4,096
+// instances up to 65,536 states went from 10.2 to 3.4 ms.  New ids take the old
+// ones' place as groups form (written to scratch and copied at the round's end:
+// 2.2 and 6.2 ms).
 constexpr uint32_t kBigThreads = 1024, kBigWaves = kBigThreads / 64;
 constexpr uint32_t kBigLds = 40960 - 64;  // 32-bit words
 constexpr uint32_t kSlices = 16;
-constexpr uint32_t kAlone = 0x10000u;     // new-id word: a block of one state
 constexpr int kBigChunk = 8;              // states of a thread whose loads go out together
 
 __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __restrict__ jobs,
@@ -586,7 +587,8 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __
   const uint32_t S = kBigLds - (64 + kBigWaves * kSlices + 32) - blkw;  // below 2^15
   const uint32_t* __restrict__ delta = reinterpret_cast<const uint32_t*>(J.delta);
   const uint8_t* __restrict__ acc = reinterpret_cast<const uint8_t*>(J.accept);
-  // scratch: hash and new id per state, the sorted list, two leftover lists
+  // scratch: hash per state, the emission's ids (in a round: a byte per state
+  // that a list throw found alone), the sorted list, two leftover lists
   // ((hash, state) pairs), two levels, the signatures
   const uint32_t n4 = (n + 3u) & ~3u;
   uint32_t* H = reinterpret_cast<uint32_t*>(J.scratch);
@@ -673,9 +675,11 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __
   uint32_t rounds = 0, refine = 0, used = 0, l = 0, alive = n;
   uint64_t jlen = 0;
   int32_t status = kFusedOk;
+  uint8_t* const AB = reinterpret_cast<uint8_t*>(NB);
   __syncthreads();
 
-  while (true) {
+  // (no letter but identities: {F, Q\F} is stable)
+  while (knon) {
     if (autom && !dbl && knon >= 2 && rounds == J.auto_rounds) {
       status = kFusedHandOff;
       break;
@@ -703,11 +707,6 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __
       frag = min(y >> 17, 0x7FFEu);
       pos = ((y & 0x1FFFFu) * S) >> 17;
     };
-    auto hash_one = [&](uint32_t q, uint32_t seed) {  // (a rehash: rare)
-      uint32_t h = mix_step(seed, blk[q]);
-      for (uint32_t mm = mask; mm; mm &= mm - 1u) h = mix_step(h, blk[ld(delta + (size_t)(__ffs(mm) - 1) * n, q)]);
-      return mix_final(h);
-    };
     if (P > 1 && tid < kBigWaves * kSlices) hist[tid] = 0;
     if (P == 1)
       for (uint32_t x = tid; x < S; x += kBigThreads) slot[x] = kEmpty;
@@ -717,6 +716,12 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __
     // its exact 32-bit key, which the hash only permutes.  With one slice the
     // first throw happens right here.
     const uint32_t recs = (knon + 8u) / 8u;  // records per signature
+    auto hash_one = [&](uint32_t q, uint32_t seed) {  // (a rehash, from the records: rare)
+      const uint32_t* r = reinterpret_cast<const uint32_t*>(REC) + (size_t)q * (4u * recs);
+      uint32_t h = seed;
+      for (uint32_t a = 0; a <= knon; ++a) h = mix_step(h, (r[a >> 1] >> (16u * (a & 1u))) & 0xFFFFu);
+      return mix_final(h);
+    };
     auto throw_at = [&](uint32_t h, uint32_t q, uint32_t mul) {
       uint32_t pos = h, frag = 0;
       if (!direct) aim_at(h, mul, pos, frag);
@@ -810,7 +815,11 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __
       __syncthreads();
     }
     // ---- throws
+    // A state that has its group takes its new id at once: the signatures are
+    // in the records (doubling: in the hashes), the old ids no longer needed.
     uint32_t next = 0, left = 0, lo = 0, idle = 0, rehash = 0;  // next: slices thrown so far
+    uint32_t leaders = 0, alone = 0;
+    bool lists = false;  // some throw took its states from a list
     while (next < P || left) {
       // entries of this throw: what is left, then the next slice (or, with
       // one slice, every live state in order)
@@ -837,8 +846,12 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __
           aim_at(h, mul, pos, frag);
         }
       };
-      if (!order)
+      if (!order) {
         for (uint32_t x = tid; x < S; x += kBigThreads) slot[x] = kEmpty;
+        if (!lists)
+          for (uint32_t x = tid; x < n4 / 4u; x += kBigThreads) NB[x] = 0u;
+        lists = true;
+      }
       if (tid == 0) sh[6 + (lo ^ 1u)] = 0;
       __syncthreads();
       const uint32_t its = (total + kBigThreads - 1) / kBigThreads;
@@ -891,10 +904,6 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __
 #pragma unroll
             for (int i = 0; i < U; ++i)
               if (a[i] != e[i].x) cand &= ~(1u << i);
-          } else if (!knon) {
-#pragma unroll
-            for (int i = 0; i < U; ++i)
-              if (((cand >> i) & 1u) && blk[rep[i]] != blk[e[i].y]) cand &= ~(1u << i);
           } else {
             for (uint32_t r = 0; r < recs; ++r) {
               uint4 a[U], b[U];
@@ -923,7 +932,7 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __
           uint32_t pos, frag;
           aim(e[i].x, pos, frag);
           if (!(slot[pos] & 1u)) atomicOr(&slot[pos], 1u);
-          NB[e[i].y] = rep[i];
+          blk[e[i].y] = (uint16_t)rep[i];
         }
         todo &= ~cand;
         // what is left joins the next throw's list
@@ -943,7 +952,12 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __
         const uint2 e = entry(tid + (uint32_t)__builtin_ctzll(b) * kBigThreads);
         uint32_t pos, frag;
         aim(e.x, pos, frag);
-        NB[e.y] = e.y | ((slot[pos] & 1u) ? 0u : kAlone);
+        blk[e.y] = (uint16_t)e.y;
+        ++leaders;
+        if (slot[pos] & 1u) continue;
+        ++alone;
+        if (order) live &= ~(b & (0ull - b));
+        else AB[e.y] = 1;
       }
       left = uniform(sh[6 + (lo ^ 1u)]);
       lo ^= 1u;
@@ -965,36 +979,27 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __
       }
     }
     if (status != kFusedOk) break;
-    // ---- new ids; groups counted
-    uint32_t leaders = 0, stay = 0;
-    for (uint32_t i0 = 0; i0 < iters; i0 += kBigChunk) {
-      uint32_t v[kBigChunk];
+    // ---- groups counted (a state alone before this round is one); the owners
+    // of states found alone from a list drop them
+    if (lists)
+      for (uint32_t i0 = 0; i0 < iters; i0 += kBigChunk) {
+        uint8_t v[kBigChunk];
 #pragma unroll
-      for (int i = 0; i < kBigChunk; ++i)
-        v[i] = ((live >> (i0 + i)) & 1ull) ? NB[tid + (i0 + i) * kBigThreads] : kNone;
+        for (int i = 0; i < kBigChunk; ++i)
+          v[i] = ((live >> (i0 + i)) & 1ull) ? AB[tid + (i0 + i) * kBigThreads] : 0;
 #pragma unroll
-      for (int i = 0; i < kBigChunk; ++i) {
-        const uint32_t q = tid + (i0 + i) * kBigThreads;
-        if (q >= n) continue;
-        if (v[i] == kNone) {  // alone before this round
-          ++leaders;
-          continue;
-        }
-        blk[q] = (uint16_t)v[i];
-        leaders += (uint32_t)((v[i] & 0xFFFFu) == q);
-        if (v[i] & kAlone) live &= ~(1ull << (i0 + i));
-        else ++stay;
+        for (int i = 0; i < kBigChunk; ++i)
+          if (v[i]) live &= ~(1ull << (i0 + i));
       }
-    }
     leaders = wave_sum(leaders);
-    stay = wave_sum(stay);
+    alone = wave_sum(alone);
     if (lane == 0) {
       atomicAdd(&sh[4], leaders);
-      atomicAdd(&sh[5], stay);
+      atomicAdd(&sh[5], alone);
     }
     __syncthreads();
-    const uint32_t cnew = uniform(sh[4]);
-    alive = uniform(sh[5]);
+    const uint32_t cnew = uniform(sh[4]) + (n - alive);
+    alive -= uniform(sh[5]);
     __syncthreads();
     if (tid < 2) sh[4 + tid] = 0;
     ++rounds;
