@@ -561,8 +561,8 @@ __global__ void __launch_bounds__(NT, 4) k_fused(const FusedJob* __restrict__ jo
 // states through device atomics (27 G/s) and a dozen launches instead.  A
 // random instance of 65,536 states and two letters takes 1.0 ms (six rounds
 // of 40 us hashing and, in three, 150 us of throws), 256 of them 1.8 ms
-// (round engine: 4.0), 512 chains of that size 5.5 ms (22.9); a batch of 4,096
-// instances up to 65,536 states went from 10.2 to 3.4 ms.  New ids take the old
+// (round engine: 4.0), 512 chains of that size 5.3 ms (22.9); a batch of 4,096
+// instances up to 65,536 states went from 10.2 to 3.3 ms.  New ids take the old
 // ones' place as groups form (written to scratch and copied at the round's end:
 // 2.2 and 6.2 ms).
 constexpr uint32_t kBigThreads = 1024, kBigWaves = kBigThreads / 64;
@@ -678,9 +678,12 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __
   uint8_t* const AB = reinterpret_cast<uint8_t*>(NB);
   __syncthreads();
 
-  // (no letter but identities: {F, Q\F} is stable)
+  // (a copy of the loop for doubling instances: less to keep in registers
+  // than in one loop for both; no letter but identities: {F, Q\F} is stable)
+  auto run = [&](auto dblc) {
+  constexpr bool DBL = decltype(dblc)::value;
   while (knon) {
-    if (autom && !dbl && knon >= 2 && rounds == J.auto_rounds) {
+    if (autom && !DBL && knon >= 2 && rounds == J.auto_rounds) {
       status = kFusedHandOff;
       break;
     }
@@ -690,13 +693,13 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __
     }
     const uint16_t* lv = LV[l & 1u];
     uint16_t* lvn = nullptr;  // the next round's level, squared beside this round's hashes
-    if (dbl && l < J.levels && (1ull << (l + 1)) <= jlen + (1ull << l) + 1ull) lvn = LV[(l + 1u) & 1u];
+    if (DBL && l < J.levels && (1ull << (l + 1)) <= jlen + (1ull << l) + 1ull) lvn = LV[(l + 1u) & 1u];
     // the first round's signatures (accept bits) index the table themselves
-    const bool direct = !dbl && rounds == 0 && knon + 1u <= 31u - (uint32_t)__clz(S);
+    const bool direct = !DBL && rounds == 0 && knon + 1u <= 31u - (uint32_t)__clz(S);
     // groups this round may form: as many as states left to place, but a
     // doubling round at most about squares its blocks, and from few blocks
     // forms far fewer (a guess: too low costs throws, nothing else)
-    const uint32_t est = direct ? 1u : (dbl ? (uint32_t)min((uint64_t)alive, 4ull * count) : alive);
+    const uint32_t est = direct ? 1u : (DBL ? (uint32_t)min((uint64_t)alive, 4ull * count) : alive);
     const uint32_t P = est <= S + S / 2u ? 1u : min(kSlices, (uint32_t)((10ull * est + 7ull * S - 1) / (7ull * S)));
     const bool read_first = count * 8u < n;
     const uint32_t seed0 = 0x6A09E667u;
@@ -731,7 +734,7 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __
     for (uint32_t i0 = 0; i0 < iters; i0 += kBigChunk) {
       uint32_t h[kBigChunk], s[kBigChunk];
       const uint32_t bits = (uint32_t)(live >> i0) & ((1u << kBigChunk) - 1u);
-      if (dbl) {
+      if (DBL) {
         uint32_t nx[kBigChunk];
 #pragma unroll
         for (int i = 0; i < kBigChunk; ++i) {
@@ -780,7 +783,7 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __
 #pragma unroll
       for (int i = 0; i < kBigChunk; ++i) {
         if (!((bits >> i) & 1u)) continue;
-        if (!direct && !dbl) h[i] = mix_final(h[i]);
+        if (!direct && !DBL) h[i] = mix_final(h[i]);
         H[tid + (i0 + i) * kBigThreads] = h[i];
         if (P > 1) atomicAdd(&hist[wave * kSlices + slice(h[i])], 1u);
         else throw_at(h[i], tid + (i0 + i) * kBigThreads, 0x9E3779B1u);
@@ -855,7 +858,7 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __
       if (tid == 0) sh[6 + (lo ^ 1u)] = 0;
       __syncthreads();
       const uint32_t its = (total + kBigThreads - 1) / kBigThreads;
-      constexpr int UT = 8, U = 4;
+      constexpr int UT = 8, U = DBL ? 8 : 4;
       if (!order) {
         for (uint32_t i0 = 0; i0 < its; i0 += UT) {
           uint2 e[UT];
@@ -897,7 +900,7 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __
           }
         }
         if (!direct && __any(cand != 0u)) {
-          if (dbl) {  // the hash is the signature
+          if (DBL) {  // the hash is the signature
             uint32_t a[U];
 #pragma unroll
             for (int i = 0; i < U; ++i) a[i] = ((cand >> i) & 1u) ? H[rep[i]] : e[i].x;
@@ -968,7 +971,7 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __
         status = kFusedFault;
         break;
       }
-      if (!dbl && left && next >= P && (idle & 7u) == 7u) {
+      if (!DBL && left && next >= P && (idle & 7u) == 7u) {
         // signatures that share a whole hash: another one separates them
         ++rehash;
         for (uint32_t x = tid; x < left; x += kBigThreads) {
@@ -1007,10 +1010,13 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_fused_big(const FusedJob* __
     ++refine;
     used = max(used, l);
     count = cnew;
-    jlen += dbl ? (1ull << l) : 1ull;
+    jlen += DBL ? (1ull << l) : 1ull;
     if (lvn) ++l;
     if (count == n) break;
   }
+  };
+  if (dbl) run(std::true_type{});
+  else run(std::false_type{});
   if (status != kFusedOk) {
     if (tid == 0) {
       R.status = status;
