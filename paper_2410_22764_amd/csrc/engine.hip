@@ -2051,8 +2051,8 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
     // records of signatures too long for registers, while they fit
     const uint32_t letters = J.rows ? J.nrows : x.k;
     J.rec = nullptr;
-    if (!fixed() && letters > grid_letters_kept(items) && ensure(d_sig_, (size_t)letters * n * 4) == DFAMIN_OK)
-      J.rec = d_sig_.as<uint32_t>();
+    if (!fixed() && letters > grid_letters_kept(items) && ensure(d_sig_, (size_t)grid_records(letters) * n * 8) == DFAMIN_OK)
+      J.rec = d_sig_.as<uint2>();
     *h = GridRes{};
     h->status = kGridAborted;
     prof.begin(s, "grid", 4.0 * x.n * x.k + x.n / 8.0 + 4.0 * x.n);

@@ -30,8 +30,8 @@
 // rounds (the one-workgroup kernel up to 16,384 states): Fib_20 (17,711
 // states, 15 rounds) 932 -> 184 us; a permuted chain of 300,007 states (19
 // rounds) 1,240 -> 490 us; random, n = 16,384, two letters, 140 -> 81 us; the
-// 2^20-state bit-splitter 5.14 -> 1.95 ms, half of it reading rows and
-// records at 6-8 TB/s from the caches.
+// 2^20-state bit-splitter 5.14 -> 1.61 ms, much of it reading rows and
+// records at 6-8 TB/s from the caches (records of four bytes an id: 1.95).
 #include "../../include/dfamin.h"
 #include "internal.h"
 
@@ -240,6 +240,11 @@ __device__ __forceinline__ uint2 at64(const uint2* p, uint32_t i) {
   return *reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(p) + (i << 3));
 }
 
+// Three block ids (below 2^21, see grid_shape) in a record of 8 bytes.
+__device__ __forceinline__ uint2 pack3(uint32_t a, uint32_t b, uint32_t c) {
+  return make_uint2(a | b << 21, b >> 11 | c << 10);
+}
+
 // ITEMS states per thread.  A workgroup owns the kT*ITEMS states from
 // base on, item e of thread t being base + e*kT + t, so workgroup order is
 // state order (the numbering at the end is a prefix over workgroups).  A
@@ -249,7 +254,11 @@ __device__ __forceinline__ uint2 at64(const uint2* p, uint32_t i) {
 template <int ITEMS>
 __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
   constexpr int CH = 8 / ITEMS;                           // letters kept in registers
-  constexpr int CL = 8 / ITEMS;  // letters per chunk of longer signatures
+  // Letters per chunk of longer signatures: one record's.  (Longer chunks for
+  // fewer states per thread, 9 at one and 6 at two, load more past the last
+  // letter and hold more registers: 2^19 states, 18 letters, 1.04 against 0.83
+  // ms, 32,768 states and 14 letters 0.35 against 0.32.)
+  constexpr int CL = 3;
   // states are grouped in LDS kPass items at a time, in twice as many slots
   constexpr int kPass = ITEMS < 4 ? ITEMS : 4;
   constexpr uint32_t kLds = 2u * kPass * kT;
@@ -590,7 +599,7 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
     }
     // longer signatures: the blocks gathered in the group step are kept for
     // the comparison in the resolve step
-    uint32_t* rec = fit ? nullptr : J.rec;
+    uint2* rec = fit ? nullptr : J.rec;
     while (true) {
       if (!list && autom && knon >= 2 && rounds == J.auto_rounds) {
         status = kFusedHandOff;  // still splitting: the host builds its closure letters
@@ -625,7 +634,7 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
         uint32_t s[CL][ITEMS];
 #pragma unroll
         for (int c = 0; c < CL; ++c) {
-          const uint32_t* rp = row((uint32_t)c);
+          const uint32_t* rp = row(min((uint32_t)c, kp - 1u));
 #pragma unroll
           for (int e = 0; e < ITEMS; ++e) s[c][e] = (own[e] & kSingleBit) ? 0u : at32(rp, state(e));
         }
@@ -647,11 +656,15 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
           for (int c = 0; c < CL; ++c)
             if (t0 + c < kp) {
 #pragma unroll
-              for (int e = 0; e < ITEMS; ++e) {
-                h[e] = mix(h[e], v[c][e]);
-                if (rec && !(own[e] & kSingleBit)) rec[(size_t)(t0 + c) * n + state(e)] = v[c][e];
-              }
+              for (int e = 0; e < ITEMS; ++e) h[e] = mix(h[e], v[c][e]);
             }
+          // (letters past the last one repeat it: the same in every record)
+          if (rec) {
+            uint2* rp = rec + (size_t)(t0 / 3u) * n;
+#pragma unroll
+            for (int e = 0; e < ITEMS; ++e)
+              if (!(own[e] & kSingleBit)) rp[state(e)] = pack3(v[0][e], v[1][e], v[2][e]);
+          }
 #pragma unroll
           for (int c = 0; c < CL; ++c)
 #pragma unroll
@@ -690,21 +703,16 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
               if (chk[e]) coll |= (uint32_t)((at32(bc, o[c][e]) & kIdBits) != b[c][e]);
           }
       } else if (rec) {
-        for (uint32_t t0 = 0; t0 < kp; t0 += CL) {
-          uint32_t x[CL][ITEMS], y[CL][ITEMS];
+        for (uint32_t t = 0; t < grid_records(kp); ++t) {
+          const uint2* rp = rec + (size_t)t * n;
+          uint2 x[ITEMS], y[ITEMS];
 #pragma unroll
-          for (int c = 0; c < CL; ++c) {
-            const uint32_t* rp = rec + (size_t)min(t0 + c, kp - 1u) * n;
-#pragma unroll
-            for (int e = 0; e < ITEMS; ++e) {
-              x[c][e] = chk[e] ? at32(rp, state(e)) : 0u;
-              y[c][e] = chk[e] ? at32(rp, r[e]) : 0u;
-            }
+          for (int e = 0; e < ITEMS; ++e) {
+            x[e] = chk[e] ? at64(rp, state(e)) : make_uint2(0, 0);
+            y[e] = chk[e] ? at64(rp, r[e]) : make_uint2(0, 0);
           }
 #pragma unroll
-          for (int c = 0; c < CL; ++c)
-#pragma unroll
-            for (int e = 0; e < ITEMS; ++e) coll |= (uint32_t)(x[c][e] != y[c][e]);
+          for (int e = 0; e < ITEMS; ++e) coll |= (uint32_t)(x[e].x != y[e].x || x[e].y != y[e].y);
         }
       } else {  // no room for records: both signatures gathered again
         for (uint32_t t = 0; t < kp; ++t) {
@@ -900,7 +908,7 @@ __global__ __launch_bounds__(kT) void k_bfs_grid(BfsJob B) {
 bool grid_shape(uint32_t n, uint32_t cus, uint32_t* items, uint32_t* wgs) {
   uint32_t it = 1;
   while (it <= kGridMaxItems && (uint64_t)it * kGridThreads * cus < n) it *= 2;
-  if (it > kGridMaxItems) return false;
+  if (it > kGridMaxItems || n > 1u << 21) return false;  // (records hold 21-bit ids)
   *items = it;
   *wgs = (n + it * kGridThreads - 1) / (it * kGridThreads);
   return true;

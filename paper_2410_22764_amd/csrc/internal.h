@@ -257,7 +257,7 @@ struct GridJob {
   uint2* pr[2];                  // n (block id, successor) pairs each: doubling rounds
   uint32_t* rank;                // n words, written once the rounds are over (may be pr[0])
   unsigned long long* table[2];  // S slots each, table[1] right behind table[0]
-  uint32_t* rec;                 // signature letters x n words, or null
+  uint2* rec;                    // grid_records(letters) x n records of three ids, or null
   uint32_t* wgw;                 // two words per workgroup
   GridBar* bar;
   GridRes* res;  // mapped page-locked host memory
@@ -273,6 +273,7 @@ struct GridJob {
 // Signature letters whose blocks a thread keeps in registers between the
 // steps of a round; records (GridJob::rec) serve longer signatures.
 inline uint32_t grid_letters_kept(uint32_t items) { return 8u / items; }
+__host__ __device__ inline uint32_t grid_records(uint32_t letters) { return (letters + 2u) / 3u; }
 // States per thread and workgroups for n states on a device of `cus` CUs;
 // false if that is more than the kernel takes.
 bool grid_shape(uint32_t n, uint32_t cus, uint32_t* items, uint32_t* wgs);

@@ -998,7 +998,8 @@ struct Serving::Impl {
     for (int i = 0; i < 2; ++i, at += 2 * n4) J.pr[i] = reinterpret_cast<uint2*>(at);
     J.rank = reinterpret_cast<uint32_t*>(J.pr[0]);
     J.wgw = reinterpret_cast<uint32_t*>(at);
-    J.rec = q.k > grid_letters_kept(items) ? static_cast<uint32_t*>(r->d_sig) : nullptr;
+    // (8 * ceil(k/3) bytes a state are no more than d_sig's 4 * (k + 1))
+    J.rec = q.k > grid_letters_kept(items) ? static_cast<uint2*>(r->d_sig) : nullptr;
     J.bar = static_cast<GridBar*>(l.bar);
     J.res = static_cast<GridRes*>(l.res.dp);
     J.salt = 0x5DEECE66Dull;
