@@ -2050,9 +2050,12 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
   while (true) {
     // records of signatures too long for registers, while they fit
     const uint32_t letters = J.rows ? J.nrows : x.k;
-    J.rec = nullptr;
-    if (!fixed() && letters > grid_letters_kept(items) && ensure(d_sig_, (size_t)grid_records(letters) * n * 8) == DFAMIN_OK)
-      J.rec = d_sig_.as<uint2>();
+    J.rec = J.rows3 = nullptr;
+    const size_t recs = (size_t)grid_records(letters) * n;
+    if (!fixed() && letters > grid_letters_kept(items)) {
+      if (items == 1 && ensure(d_sig_, 2 * recs * 8) == DFAMIN_OK) J.rows3 = d_sig_.as<uint2>() + recs;
+      if (J.rows3 || ensure(d_sig_, recs * 8) == DFAMIN_OK) J.rec = d_sig_.as<uint2>();
+    }
     *h = GridRes{};
     h->status = kGridAborted;
     prof.begin(s, "grid", 4.0 * x.n * x.k + x.n / 8.0 + 4.0 * x.n);

@@ -600,6 +600,8 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
     // longer signatures: the blocks gathered in the group step are kept for
     // the comparison in the resolve step
     uint2* rec = fit ? nullptr : J.rec;
+    [[maybe_unused]] uint2* rows3 = fit ? nullptr : J.rows3;
+    [[maybe_unused]] bool packed = false;  // rows3 is written
     while (true) {
       if (!list && autom && knon >= 2 && rounds == J.auto_rounds) {
         status = kFusedHandOff;  // still splitting: the host builds its closure letters
@@ -630,45 +632,68 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
           }
       } else {
         // chunks of CL letters; the next chunk's row entries go out before
-        // this chunk's gathers
-        uint32_t s[CL][ITEMS];
+        // this chunk's gathers.  At one state per thread they come as records,
+        // too, from the second round on (rows3), as the first one wrote them:
+        // a third of the loads and two thirds of the bytes.
+        auto load = [&](uint32_t t0, uint32_t (&x)[CL][ITEMS], auto packedc) {
+          if constexpr (decltype(packedc)::value) {
+            const uint2* rp = rows3 + (size_t)(min(t0, kp - 1u) / 3u) * n;
 #pragma unroll
-        for (int c = 0; c < CL; ++c) {
-          const uint32_t* rp = row(min((uint32_t)c, kp - 1u));
-#pragma unroll
-          for (int e = 0; e < ITEMS; ++e) s[c][e] = (own[e] & kSingleBit) ? 0u : at32(rp, state(e));
-        }
-        clear_lds();
-        clear_old();
-        for (uint32_t t0 = 0; t0 < kp; t0 += CL) {
-          uint32_t sn[CL][ITEMS], v[CL][ITEMS];
-#pragma unroll
-          for (int c = 0; c < CL; ++c) {
-            const uint32_t* rp = row(min(t0 + CL + c, kp - 1u));
-#pragma unroll
-            for (int e = 0; e < ITEMS; ++e) sn[c][e] = (own[e] & kSingleBit) ? 0u : at32(rp, state(e));
-          }
-#pragma unroll
-          for (int c = 0; c < CL; ++c)
-#pragma unroll
-            for (int e = 0; e < ITEMS; ++e) v[c][e] = (own[e] & kSingleBit) ? 0u : at32(bc, s[c][e]) & kIdBits;
-#pragma unroll
-          for (int c = 0; c < CL; ++c)
-            if (t0 + c < kp) {
-#pragma unroll
-              for (int e = 0; e < ITEMS; ++e) h[e] = mix(h[e], v[c][e]);
+            for (int e = 0; e < ITEMS; ++e) {
+              const uint2 w = (own[e] & kSingleBit) ? make_uint2(0, 0) : at64(rp, state(e));
+              x[0][e] = w.x & 0x1fffffu;
+              x[1][e] = (w.x >> 21 | w.y << 11) & 0x1fffffu;
+              x[2][e] = w.y >> 10;
             }
-          // (letters past the last one repeat it: the same in every record)
-          if (rec) {
-            uint2* rp = rec + (size_t)(t0 / 3u) * n;
+          } else {
 #pragma unroll
-            for (int e = 0; e < ITEMS; ++e)
-              if (!(own[e] & kSingleBit)) rp[state(e)] = pack3(v[0][e], v[1][e], v[2][e]);
+            for (int c = 0; c < CL; ++c) {
+              const uint32_t* rp = row(min(t0 + c, kp - 1u));
+#pragma unroll
+              for (int e = 0; e < ITEMS; ++e) x[c][e] = (own[e] & kSingleBit) ? 0u : at32(rp, state(e));
+            }
           }
+        };
+        auto gather = [&](auto packedc) {
+          uint32_t s[CL][ITEMS];
+          load(0u, s, packedc);
+          clear_lds();
+          clear_old();
+          for (uint32_t t0 = 0; t0 < kp; t0 += CL) {
+            uint32_t sn[CL][ITEMS], v[CL][ITEMS];
+            load(t0 + CL, sn, packedc);
 #pragma unroll
-          for (int c = 0; c < CL; ++c)
+            for (int c = 0; c < CL; ++c)
 #pragma unroll
-            for (int e = 0; e < ITEMS; ++e) s[c][e] = sn[c][e];
+              for (int e = 0; e < ITEMS; ++e) v[c][e] = (own[e] & kSingleBit) ? 0u : at32(bc, s[c][e]) & kIdBits;
+            if constexpr (ITEMS == 1 && !decltype(packedc)::value)
+              if (rows3 && !(own[0] & kSingleBit))
+                rows3[(size_t)(t0 / 3u) * n + state(0)] = pack3(s[0][0], s[1][0], s[2][0]);
+#pragma unroll
+            for (int c = 0; c < CL; ++c)
+              if (t0 + c < kp) {
+#pragma unroll
+                for (int e = 0; e < ITEMS; ++e) h[e] = mix(h[e], v[c][e]);
+              }
+            // (letters past the last one repeat it: the same in every record)
+            if (rec) {
+              uint2* rp = rec + (size_t)(t0 / 3u) * n;
+#pragma unroll
+              for (int e = 0; e < ITEMS; ++e)
+                if (!(own[e] & kSingleBit)) rp[state(e)] = pack3(v[0][e], v[1][e], v[2][e]);
+            }
+#pragma unroll
+            for (int c = 0; c < CL; ++c)
+#pragma unroll
+              for (int e = 0; e < ITEMS; ++e) s[c][e] = sn[c][e];
+          }
+        };
+        if constexpr (ITEMS == 1) {
+          if (packed) gather(std::true_type{});
+          else gather(std::false_type{});
+          packed = rows3 != nullptr;
+        } else {
+          gather(std::false_type{});
         }
       }
       group(h);

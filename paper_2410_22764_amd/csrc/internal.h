@@ -258,6 +258,8 @@ struct GridJob {
   uint32_t* rank;                // n words, written once the rounds are over (may be pr[0])
   unsigned long long* table[2];  // S slots each, table[1] right behind table[0]
   uint2* rec;                    // grid_records(letters) x n records of three ids, or null
+  uint2* rows3;                  // as many for the rows, three entries to a record, or null
+                                 // (used at one state per thread)
   uint32_t* wgw;                 // two words per workgroup
   GridBar* bar;
   GridRes* res;  // mapped page-locked host memory
