@@ -660,8 +660,8 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
           clear_lds();
           clear_old();
           for (uint32_t t0 = 0; t0 < kp; t0 += CL) {
-            uint32_t sn[CL][ITEMS], v[CL][ITEMS];
-            load(t0 + CL, sn, packedc);
+            uint32_t sn[CL][ITEMS] = {}, v[CL][ITEMS];
+            if (t0 + CL < kp) load(t0 + CL, sn, packedc);
 #pragma unroll
             for (int c = 0; c < CL; ++c)
 #pragma unroll
