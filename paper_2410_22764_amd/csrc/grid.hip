@@ -29,7 +29,7 @@
 // single one costs 28 ns per workgroup).  Per call, against the host-planned
 // rounds (the one-workgroup kernel up to 16,384 states): Fib_20 (17,711
 // states, 15 rounds) 932 -> 184 us; a permuted chain of 300,007 states (19
-// rounds) 1,240 -> 490 us; random, n = 16,384, two letters, 140 -> 81 us; the
+// rounds) 1,240 -> 400 us; random, n = 16,384, two letters, 140 -> 81 us; the
 // 2^20-state bit-splitter 5.14 -> 1.61 ms, much of it reading rows and
 // records at 6-8 TB/s from the caches (records of four bytes an id: 1.95).
 #include "../../include/dfamin.h"
