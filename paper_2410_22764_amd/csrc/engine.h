@@ -163,6 +163,9 @@ class Engine {
   // remaining budget, or a third of what is left of the fixed region (the
   // signature records of the levels need about as much again).
   uint64_t closure_cap() const;
+  uint64_t fixed_handoff_cap(const InstInput& x) const;
+  uint64_t closure_limit_ = ~0ull;  // build_closure takes no more level storage than this
+  bool closure_denied_ = false;     // its last request for storage was refused
   void reset_fixed_region();
   int build_closure(const std::vector<uint32_t>& which, const dfamin_opts& opts, hipStream_t s);
   // Closure levels of unary doubling instances, computed round by round.

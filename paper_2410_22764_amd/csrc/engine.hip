@@ -321,6 +321,16 @@ uint64_t Engine::closure_cap() const {
   return ctx_->budget > used ? (ctx_->budget - used) / 2 : 0;
 }
 
+// Closure storage that the round engine has at least, in the fixed region,
+// when an AUTO instance of several letters comes to its closure after
+// auto_rounds rounds: a third of what its arrays leave (62 bytes a state with
+// the largest table, once more that table for the smaller ones before it, the
+// signature records, lists).
+uint64_t Engine::fixed_handoff_cap(const InstInput& x) const {
+  const uint64_t own = (uint64_t)x.n * (96 + 4ull * (x.k + 1)) + (1ull << 20);
+  return fixed_cap_ > own ? (fixed_cap_ - own) / 3 : 0;
+}
+
 int Engine::upload(void* dst, const void* src, size_t bytes, hipStream_t s) {
   if (!bytes) return DFAMIN_OK;
   TRY(flush_segs(s));  // queued copies first, in the order they were asked for
@@ -424,7 +434,7 @@ int Engine::build_closure(const std::vector<uint32_t>& which, const dfamin_opts&
     specs[w].letters = nonid_[i];
     specs[w].L = l;
   }
-  const uint64_t cap = closure_cap();
+  const uint64_t cap = std::min(closure_cap(), closure_limit_);
   uint64_t taken = 0;
   ClosureScratch scratch;
   scratch.device = [&](size_t bytes) -> void* { return ensure(d_jobs_, bytes) == DFAMIN_OK ? d_jobs_.p : nullptr; };
@@ -436,10 +446,12 @@ int Engine::build_closure(const std::vector<uint32_t>& which, const dfamin_opts&
     return readback(h_flags_, d, bytes, s) == DFAMIN_OK;
   };
   scratch.level_storage = [&](size_t bytes) -> void* {
+    closure_denied_ = true;
     if (taken + bytes > cap) return nullptr;
     if (closure_cursor_ == closure_bufs_.size()) closure_bufs_.emplace_back();
     DevBuf& b = closure_bufs_[closure_cursor_];
     if (ensure(b, bytes) != DFAMIN_OK) return nullptr;
+    closure_denied_ = false;
     ++closure_cursor_;
     taken += bytes;
     return b.p;
@@ -1969,12 +1981,6 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
   const size_t n = x.n;
   const uint32_t S = (uint32_t)((4 * n + 7) & ~size_t(7));  // (a quarter full: few home slots are taken)
   TRY(ensure_gbar());
-  TRY(ensure(d_block_, n * 4));
-  TRY(ensure(d_nb_, n * 4));
-  TRY(ensure(d_act_, n * 8));
-  TRY(ensure(d_act2_, n * 8));
-  TRY(ensure(d_table_, (size_t)S * 16));
-  TRY(ensure(d_wgflags_, (size_t)wgs * 8));
   TRY(ensure_host(h_gres_, sizeof(GridRes)));
   in_ = in;
   res.assign(1, InstOutcome{});
@@ -1991,19 +1997,27 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
       inst_rows_[0].push_back(reinterpret_cast<uint64_t>(x.delta) + 4ull * a * x.n);
   };
   GridJob J{};
-  auto closure_rows = [&]() -> int {
-    TRY(build_closure({0u}, opts, s));
+  auto upload_rows = [&]() -> int {
     TRY(ensure(d_rows_, std::max<size_t>(inst_rows_[0].size(), 1) * 8));
     TRY(upload(d_rows_.p, inst_rows_[0].data(), inst_rows_[0].size() * 8, s));
     J.rows = d_rows_.as<uint64_t>();
     J.nrows = (uint32_t)inst_rows_[0].size();
     return DFAMIN_OK;
   };
+  // (the closure before the kernel's arrays, as the round engine has it before
+  // its own: its storage is a share of what is left, and as many levels fit)
   if (x.closure == DFAMIN_CLOSURE_ON) {
     TRY(validate(s, res));
     letter_rows();
-    TRY(closure_rows());
+    TRY(build_closure({0u}, opts, s));
+    TRY(upload_rows());
   }
+  TRY(ensure(d_block_, n * 4));
+  TRY(ensure(d_nb_, n * 4));
+  TRY(ensure(d_act_, n * 8));
+  TRY(ensure(d_act2_, n * 8));
+  TRY(ensure(d_table_, (size_t)S * 16));
+  TRY(ensure(d_wgflags_, (size_t)wgs * 8));
   if (no_fused) {  // the minimal DFA's buffers, as the round engine leaves them
     TRY(ensure(d_slot_of_, n * 4));
     TRY(ensure(d_keep_, n));
@@ -2065,7 +2079,7 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
     HIP(stream_wait(s));
     prof.collect();
     if (h->aborted || h->status == kGridAborted) return DFAMIN_OK;  // not all resident: the round engine takes it
-    if (h->status != kFusedHandOff || J.resume || h->doubling || fixed()) break;
+    if (h->status != kFusedHandOff || J.resume || h->doubling) break;
     // AUTO, still splitting after auto_rounds rounds: the closure's letters
     // join and the kernel goes on from its partition
     nonid_[0].clear();
@@ -2076,7 +2090,15 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
     J.count0 = h->num_blocks;
     J.rounds0 = h->rounds;
     J.refine0 = h->refine_rounds;
-    TRY(closure_rows());
+    // (in the fixed region the round engine takes it where the storage that
+    // it is certain to have there does not hold every level)
+    closure_denied_ = false;
+    closure_limit_ = fixed() ? fixed_handoff_cap(x) : ~0ull;
+    const int rc = build_closure({0u}, opts, s);
+    closure_limit_ = ~0ull;
+    if (rc != DFAMIN_OK) return rc;
+    if (fixed() && closure_denied_) return DFAMIN_OK;
+    TRY(upload_rows());
   }
   InstOutcome& o = res[0];
   switch (h->status) {

@@ -156,3 +156,35 @@ def test_concurrent_calls(monkeypatch):
     for t in ts:
         t.join()
     assert not bad
+
+
+def _shifts(n, steps, seed):
+    """Letters q -> min(q + s, n - 1), one accepting state, ids shuffled:
+    deep, with several letters that move."""
+    q = np.arange(n)
+    rows = np.stack([np.minimum(q + s, n - 1) for s in steps]).astype(np.uint32)
+    return W.permute_dfa(W.from_rows(rows, q == n - 1), W.random_permutation(n, seed), f"shifts({n},{steps})")
+
+
+@pytest.mark.parametrize("closure", ["on", "auto"])
+@pytest.mark.parametrize("n,steps", [(120000, [1, 3, 5]), (60000, [1, 2, 3, 4]), (7000, [1, 7])])
+def test_noalloc_holds_the_same_levels(ctx, n, steps, closure, monkeypatch):
+    """In the fixed region the closure keeps as many levels with the grid
+    kernel as with the round engine's rounds, and the results say so."""
+    import torch
+    d = _shifts(n, steps, n)
+    delta = torch.from_numpy(d.delta.view(np.int32)).cuda()
+    acc = torch.from_numpy(d.accept).cuda()
+    got = []
+    for grid in (True, False):
+        if not grid:
+            monkeypatch.setenv("DFAMIN_GRID_MAX_STATES", "0")
+        print(f"[case] noalloc {d.name} {closure} grid={grid}", flush=True)
+        out = torch.empty(n, dtype=torch.int32, device="cuda")
+        r = dfamin.dfamin_minimize_device_noalloc(ctx, d.n, d.k, delta.data_ptr(), acc.data_ptr(), d.q0, out.data_ptr(),
+                                                  opts=closure, stream=torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        got.append((r, out.cpu().numpy()))
+    assert got[0][0] == got[1][0]
+    assert np.array_equal(got[0][1], got[1][1])
+    assert np.array_equal(got[0][1], oracle.hopcroft(d.n, d.k, d.delta, d.accept)[0])
