@@ -122,12 +122,12 @@ int ensure(Context& c, dfamin::DevBuf& b, size_t bytes) {
   size_t want = (bytes + bytes / 8 + 4095) & ~size_t(4095);
   if (c.used + want > c.budget) {
     want = (bytes + 4095) & ~size_t(4095);
-    if (c.used + want > c.budget) return c.engine.release_big() ? ensure(c, b, bytes) : DFAMIN_E_NOMEM;
+    if (c.used + want > c.budget) return c.engine.release_spare() ? ensure(c, b, bytes) : DFAMIN_E_NOMEM;
   }
   if (hipMalloc(&b.p, want) != hipSuccess) {
     b.p = nullptr;
     (void)hipGetLastError();
-    if (c.engine.release_big()) return ensure(c, b, bytes);
+    if (c.engine.release_spare()) return ensure(c, b, bytes);
     return DFAMIN_E_NOMEM;
   }
   b.cap = want;
@@ -219,6 +219,7 @@ int run_host_batch(Context& c, uint32_t count, const dfamin_dfa* dfas, const dfa
     out_bytes = align16(out_bytes + 4ull * dfas[i].n);
   }
   int rc;
+  c.engine.begin_call();
   if ((rc = ensure_host(c.h_in, in_bytes)) != DFAMIN_OK) return rc;
   if ((rc = ensure_host(c.h_out, out_bytes)) != DFAMIN_OK) return rc;
   if ((rc = ensure(c, c.in_delta, in_bytes)) != DFAMIN_OK) return rc;

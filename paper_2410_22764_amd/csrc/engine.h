@@ -164,7 +164,8 @@ class Engine {
   // signature records of the levels need about as much again).
   uint64_t closure_cap() const;
   uint64_t fixed_handoff_cap(const InstInput& x) const;
-  uint64_t closure_limit_ = ~0ull;  // build_closure takes no more level storage than this
+  uint64_t closure_limit_ = ~0ull;  // level storage is no more than this
+  uint64_t closure_taken_ = 0;      // the most that this call has taken
   bool closure_denied_ = false;     // its last request for storage was refused
   void reset_fixed_region();
   int build_closure(const std::vector<uint32_t>& which, const dfamin_opts& opts, hipStream_t s);
@@ -286,8 +287,8 @@ class Engine {
   DevBuf d_fjobs_;
   HostBuf h_fjobs_, h_fres_;
   // grid kernel: its barrier words (zero between launches; never part of the
-  // fixed region) and its mapped result
-  DevBuf d_gbar_;
+  // fixed region) and its mapped result (arrays: d_grid_)
+  GridBar* gbar_ = nullptr;
   HostBuf h_gres_;
   std::vector<uint32_t> fused_pos_;  // per entry of `which`: index in the job array
   // A batch's fused kernels run on their own stream beside the round
@@ -304,8 +305,14 @@ class Engine {
   std::vector<uint32_t> big_order_;   // longest first
   bool big_busy_ = false;             // d_fbig_ is in use by this call
   bool no_big_ = false;               // this call does without
+  // The grid kernel's tables and pairs, and its records of long signatures
+  DevBuf d_grid_, d_grec_;
+  bool grid_busy_ = false;            // they are in use by this call
+  uint64_t used_bytes() const;
  public:
-  bool release_big();  // true: d_fbig_ was given back
+  bool release_spare();  // true: some memory was given back
+  // A new call is about to take memory (its level buffers are all free).
+  void begin_call() { closure_cursor_ = 0; }
   // Set by callers that read the round engine's buffers after run() (the
   // minimal DFA): every instance then goes through the round engine.
   bool no_fused = false;

@@ -182,8 +182,8 @@ Engine::~Engine() {
                     &d_keep_, &d_rank_, &d_sig_, &d_table_, &d_status_, &d_changed_, &d_rb_,
                     &d_results_, &d_wgflags_, &d_part_, &d_dense_,
                     &d_djobs_, &d_visit_, &d_bfs_rows_, &d_min_delta_, &d_min_acc_,
-                    &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_fbig_, &d_uniq_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
-  if (d_gbar_.p) (void)hipFree(d_gbar_.p);
+                    &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_fbig_, &d_grid_, &d_grec_, &d_uniq_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
+  if (gbar_) (void)hipFree(gbar_);
   // device buffers of the fixed-region mode belong to the region
   if (!fixed()) {
     for (DevBuf* b : bufs)
@@ -203,8 +203,8 @@ uint64_t Engine::device_bytes() const {
                           &d_keep_, &d_rank_, &d_sig_, &d_table_, &d_status_, &d_changed_, &d_rb_,
                           &d_results_, &d_wgflags_, &d_part_, &d_dense_,
                           &d_djobs_, &d_visit_, &d_bfs_rows_, &d_min_delta_, &d_min_acc_,
-                          &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_fbig_, &d_uniq_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
-  uint64_t t = d_gbar_.cap;
+                          &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_fbig_, &d_grid_, &d_grec_, &d_uniq_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
+  uint64_t t = 0;
   for (const DevBuf* b : bufs) t += b->cap;
   for (const DevBuf& b : closure_bufs_) t += b.cap;
   return t;
@@ -240,13 +240,13 @@ int Engine::ensure(DevBuf& b, size_t bytes) {
   }
   if (ctx_->used + want > ctx_->budget) {
     want = (bytes + 4095) & ~size_t(4095);
-    if (ctx_->used + want > ctx_->budget) return &b != &d_fbig_ && release_big() ? ensure(b, bytes) : DFAMIN_E_NOMEM;
+    if (ctx_->used + want > ctx_->budget) return release_spare() ? ensure(b, bytes) : DFAMIN_E_NOMEM;
   }
   hipError_t e = hipMalloc(&b.p, want);
   if (e != hipSuccess) {
     b.p = nullptr;
     (void)hipGetLastError();
-    if (e == hipErrorOutOfMemory && &b != &d_fbig_ && release_big()) return ensure(b, bytes);
+    if (e == hipErrorOutOfMemory && release_spare()) return ensure(b, bytes);
     return e == hipErrorOutOfMemory ? DFAMIN_E_NOMEM : check_hip(e);
   }
   b.cap = want;
@@ -254,14 +254,33 @@ int Engine::ensure(DevBuf& b, size_t bytes) {
   return DFAMIN_OK;
 }
 
-// Gives back the scratch of a batch's larger instances, which is kept from
-// call to call only while nothing else needs the budget.
-bool Engine::release_big() {
-  if (big_busy_ || fixed() || !d_fbig_.p) return false;
-  (void)hipFree(d_fbig_.p);
-  ctx_->used -= d_fbig_.cap;
-  d_fbig_ = DevBuf{};
-  return true;
+// Gives back what is kept from call to call only while nothing else needs the
+// budget: the arrays of the grid kernel and of a batch's larger instances, and
+// level buffers that this call has not taken.  (Their kernels have ended:
+// hipFree waits for the device.)
+bool Engine::release_spare() {
+  if (fixed()) return false;
+  bool any = false;
+  auto drop = [&](DevBuf& b) {
+    if (!b.p) return;
+    (void)hipFree(b.p);
+    ctx_->used -= b.cap;
+    b = DevBuf{};
+    any = true;
+  };
+  if (!big_busy_) drop(d_fbig_);
+  if (!grid_busy_) drop(d_grid_);
+  drop(d_grec_);  // (sized right before each launch, which is waited for)
+  for (size_t i = closure_cursor_; i < closure_bufs_.size(); ++i) drop(closure_bufs_[i]);
+  return any;
+}
+
+// The context's bytes, without what release_spare would give back (what this
+// call uses of it counts).
+uint64_t Engine::used_bytes() const {
+  uint64_t u = ctx_->used - (big_busy_ ? 0 : d_fbig_.cap) - (grid_busy_ ? 0 : d_grid_.cap) - d_grec_.cap;
+  for (size_t i = closure_cursor_; i < closure_bufs_.size(); ++i) u -= closure_bufs_[i].cap;
+  return u;
 }
 
 int Engine::ensure_host(HostBuf& b, size_t bytes) {
@@ -308,17 +327,18 @@ void Engine::reset_fixed_region() {
                     &d_results_, &d_wgflags_, &d_part_, &d_dense_,
                     &d_djobs_, &d_visit_, &d_bfs_rows_, &d_min_delta_, &d_min_acc_,
                     &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_ctrl_, &d_refine_, &d_counts_,
-                    &d_fjobs_, &d_fbig_, &d_uniq_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
+                    &d_fjobs_, &d_fbig_, &d_grid_, &d_grec_, &d_uniq_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
   for (DevBuf* b : bufs) *b = DevBuf{};
   closure_bufs_.clear();
   fixed_off_ = 0;
 }
 
 uint64_t Engine::closure_cap() const {
-  if (fixed()) return fixed_cap_ > fixed_off_ ? (fixed_cap_ - fixed_off_) / 3 : 0;
-  // (d_fbig_ is given up before anything else fails for it)
-  const uint64_t used = ctx_->used - d_fbig_.cap;
-  return ctx_->budget > used ? (ctx_->budget - used) / 2 : 0;
+  if (fixed()) return std::min(closure_limit_, fixed_cap_ > fixed_off_ ? (uint64_t)(fixed_cap_ - fixed_off_) / 3 : 0);
+  // (an AUTO closure that the grid kernel waits for: its arrays do not count,
+  // being less than what grid_applies left free and the round engine would hold)
+  const uint64_t used = used_bytes() - (grid_busy_ ? d_grid_.cap : 0);
+  return std::min(closure_limit_, ctx_->budget > used ? (ctx_->budget - used) / 2 : 0);
 }
 
 // Closure storage that the round engine has at least, in the fixed region,
@@ -434,7 +454,7 @@ int Engine::build_closure(const std::vector<uint32_t>& which, const dfamin_opts&
     specs[w].letters = nonid_[i];
     specs[w].L = l;
   }
-  const uint64_t cap = std::min(closure_cap(), closure_limit_);
+  const uint64_t cap = closure_cap();
   uint64_t taken = 0;
   ClosureScratch scratch;
   scratch.device = [&](size_t bytes) -> void* { return ensure(d_jobs_, bytes) == DFAMIN_OK ? d_jobs_.p : nullptr; };
@@ -454,6 +474,7 @@ int Engine::build_closure(const std::vector<uint32_t>& which, const dfamin_opts&
     closure_denied_ = false;
     ++closure_cursor_;
     taken += bytes;
+    closure_taken_ = std::max(closure_taken_, taken);
     return b.p;
   };
   std::vector<std::vector<uint64_t>> rows;
@@ -512,6 +533,7 @@ int Engine::lazy_levels(const std::vector<uint32_t>& which, const dfamin_opts& o
       return DFAMIN_OK;
     }
     ++closure_cursor_;
+    closure_taken_ = std::max(closure_taken_, words * 4);
     base = static_cast<char*>(b.p);
   }
   uint64_t off = 0;
@@ -1057,8 +1079,7 @@ int Engine::signature_rounds(const dfamin_opts& opts, uint64_t max_rounds, hipSt
     // count table's 2^16 words do as well, with five the keys are too long)
     const bool one = large && m == N && alist.size() == 1 && !dbl[0] && !has_closure_[0];
     if (one && rounds == 1 && dense_from_labels && cnt_ok[0] && desc_[0].ebits && desc_[0].kp == 4 &&
-        !would_scan(0)) {
-      TRY(ensure(d_table_, (1ull << ceil_log2_u64(2 * N)) * sizeof(Slot)));  // 32 MiB at least
+        !would_scan(0) && ensure(d_table_, (1ull << ceil_log2_u64(2 * N)) * sizeof(Slot)) == DFAMIN_OK) {  // 32 MiB at least
       prof.begin(s, "label2", (double)N * (0.125 + 4.5 * 4 + 0.5 + 4.0));
       launch_label2(d_desc_.as<InstDesc>(), d_rows_.as<uint64_t>(), (uint32_t)N, d_dense_.as<uint8_t>() + nib_at,
                     d_nb_.as<uint32_t>(), ctx_->cus, s);
@@ -1695,8 +1716,8 @@ int Engine::minimal_dfa(const dfamin_opts& opts, hipStream_t s, uint32_t nb, uin
     const uint32_t wgs = std::min<uint32_t>({128u, ctx_->cus, (n + kGridThreads - 1) / kGridThreads});
     GridLease lease;
     const char* knob = std::getenv("DFAMIN_GRID_MAX_STATES");
-    if (wgs && !(knob && std::atol(knob) <= 0) && lease.take(ctx_->device, wgs, ctx_->cus)) {
-      TRY(ensure_gbar());
+    if (wgs && !(knob && std::atol(knob) <= 0) && ensure_gbar() == DFAMIN_OK &&
+        lease.take(ctx_->device, wgs, ctx_->cus)) {
       TRY(ensure_host(h_gres_, sizeof(GridRes)));
       TRY(ensure(d_qdbl_, 256));
       BfsJob B{};
@@ -1707,7 +1728,7 @@ int Engine::minimal_dfa(const dfamin_opts& opts, hipStream_t s, uint32_t nb, uin
       B.list[1] = next;
       B.visited = visited;
       B.counter = d_qdbl_.as<uint32_t>();
-      B.bar = d_gbar_.as<GridBar>();
+      B.bar = gbar_;
       B.res = static_cast<GridRes*>(h_gres_.dp);
       B.fcount = B.reached = 1;
       GridRes* h = h_gres_.as<GridRes>();
@@ -1957,16 +1978,21 @@ bool Engine::grid_applies(const InstInput& x, const dfamin_opts& opts, uint32_t*
   if (fixed()) {
     const uint64_t own = 27ull * n + (64ull << 10);  // the engine's buffers carved before the levels
     if (own > fixed_cap_ || 4 * L * n > (fixed_cap_ - own) / 3) return false;
-  } else if (ctx_->used - d_fbig_.cap + 2 * 4 * L * n + (256ull + 8ull * x.k) * n > ctx_->budget) {
+  } else if (used_bytes() + 2 * 4 * L * n + (256ull + 8ull * x.k) * n > ctx_->budget) {
     return false;
   }
   return grid_shape(x.n, ctx_->cus, items, wgs);
 }
 
+// (a few KiB, held until the context goes and not the budget's)
 int Engine::ensure_gbar() {
-  if (d_gbar_.p) return DFAMIN_OK;
-  TRY(ensure(d_gbar_, sizeof(GridBar)));
-  HIP(hipMemset(d_gbar_.p, 0, sizeof(GridBar)));
+  if (gbar_) return DFAMIN_OK;
+  void* p = nullptr;
+  const hipError_t e = hipMalloc(&p, sizeof(GridBar));
+  if (e != hipSuccess) (void)hipGetLastError();
+  HIP(e);
+  gbar_ = static_cast<GridBar*>(p);
+  HIP(hipMemset(p, 0, sizeof(GridBar)));
   return check_hip(hipDeviceSynchronize());  // (set-up, once per engine: calls come on any stream)
 }
 
@@ -1980,7 +2006,10 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
   if (!lease.take(ctx_->device, wgs, ctx_->cus)) return DFAMIN_OK;
   const size_t n = x.n;
   const uint32_t S = (uint32_t)((4 * n + 7) & ~size_t(7));  // (a quarter full: few home slots are taken)
-  TRY(ensure_gbar());
+  {
+    const int rc = ensure_gbar();
+    if (rc != DFAMIN_OK) return rc == DFAMIN_E_NOMEM ? DFAMIN_OK : rc;
+  }
   TRY(ensure_host(h_gres_, sizeof(GridRes)));
   in_ = in;
   res.assign(1, InstOutcome{});
@@ -1995,6 +2024,11 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
   auto letter_rows = [&]() {
     for (uint32_t a : nonid_[0])
       inst_rows_[0].push_back(reinterpret_cast<uint64_t>(x.delta) + 4ull * a * x.n);
+  };
+  auto leave = [&]() -> int {  // to the round engine, which builds its own levels
+    closure_cursor_ = 0;
+    if (has_closure_[0]) (void)release_spare();
+    return DFAMIN_OK;
   };
   GridJob J{};
   auto upload_rows = [&]() -> int {
@@ -2012,13 +2046,25 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
     TRY(build_closure({0u}, opts, s));
     TRY(upload_rows());
   }
-  TRY(ensure(d_block_, n * 4));
-  TRY(ensure(d_nb_, n * 4));
-  TRY(ensure(d_act_, n * 8));
-  TRY(ensure(d_act2_, n * 8));
-  TRY(ensure(d_table_, (size_t)S * 16));
-  TRY(ensure(d_wgflags_, (size_t)wgs * 8));
+  // From here on the kernel's arrays are this call's: the tables, the pairs of
+  // doubling rounds, two words per workgroup.
+  struct Busy {
+    bool& b;
+    explicit Busy(bool& x) : b(x) { b = true; }
+    ~Busy() { b = false; }
+  } busy(grid_busy_);
+  const size_t tab = 16 * (size_t)S, pairs = (8 * n + 255) & ~size_t(255);
+  {
+    int rc = ensure(d_block_, n * 4);
+    if (rc == DFAMIN_OK) rc = ensure(d_nb_, n * 4);
+    if (rc == DFAMIN_OK) rc = ensure(d_grid_, tab + 2 * pairs + 8 * (size_t)wgs);
+    if (rc == DFAMIN_E_NOMEM) return leave();  // the round engine may need less
+    TRY(rc);
+  }
+  char* const mem = d_grid_.as<char>();
   if (no_fused) {  // the minimal DFA's buffers, as the round engine leaves them
+    TRY(ensure(d_act_, n * 4));
+    TRY(ensure(d_act2_, n * 4));
     TRY(ensure(d_slot_of_, n * 4));
     TRY(ensure(d_keep_, n));
     TRY(ensure(d_rank_, (n + 1) * 4));
@@ -2045,13 +2091,13 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
   J.S = S;
   J.blk[0] = d_block_.as<uint32_t>();
   J.blk[1] = d_nb_.as<uint32_t>();
-  J.pr[0] = d_act_.as<uint2>();
-  J.pr[1] = d_act2_.as<uint2>();
-  J.rank = d_act_.as<uint32_t>();
-  J.table[0] = d_table_.as<unsigned long long>();
+  J.table[0] = reinterpret_cast<unsigned long long*>(mem);
   J.table[1] = J.table[0] + S;
-  J.wgw = d_wgflags_.as<uint32_t>();
-  J.bar = d_gbar_.as<GridBar>();
+  J.pr[0] = reinterpret_cast<uint2*>(mem + tab);
+  J.pr[1] = reinterpret_cast<uint2*>(mem + tab + pairs);
+  J.rank = reinterpret_cast<uint32_t*>(J.pr[0]);
+  J.wgw = reinterpret_cast<uint32_t*>(mem + tab + 2 * pairs);
+  J.bar = gbar_;
   J.res = static_cast<GridRes*>(h_gres_.dp);
   J.no_doubling = J.want_ids = no_fused ? 1u : 0u;
   J.salt = 0x5DEECE66Dull;
@@ -2067,8 +2113,8 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
     J.rec = J.rows3 = nullptr;
     const size_t recs = (size_t)grid_records(letters) * n;
     if (!fixed() && letters > grid_letters_kept(items)) {
-      if (items == 1 && ensure(d_sig_, 2 * recs * 8) == DFAMIN_OK) J.rows3 = d_sig_.as<uint2>() + recs;
-      if (J.rows3 || ensure(d_sig_, recs * 8) == DFAMIN_OK) J.rec = d_sig_.as<uint2>();
+      if (items == 1 && ensure(d_grec_, 2 * recs * 8) == DFAMIN_OK) J.rows3 = d_grec_.as<uint2>() + recs;
+      if (J.rows3 || ensure(d_grec_, recs * 8) == DFAMIN_OK) J.rec = d_grec_.as<uint2>();
     }
     *h = GridRes{};
     h->status = kGridAborted;
@@ -2078,7 +2124,7 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
     HIP(hipGetLastError());
     HIP(stream_wait(s));
     prof.collect();
-    if (h->aborted || h->status == kGridAborted) return DFAMIN_OK;  // not all resident: the round engine takes it
+    if (h->aborted || h->status == kGridAborted) return leave();  // a wait ran out: the round engine takes it
     if (h->status != kFusedHandOff || J.resume || h->doubling) break;
     // AUTO, still splitting after auto_rounds rounds: the closure's letters
     // join and the kernel goes on from its partition
@@ -2097,13 +2143,13 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
     const int rc = build_closure({0u}, opts, s);
     closure_limit_ = ~0ull;
     if (rc != DFAMIN_OK) return rc;
-    if (fixed() && closure_denied_) return DFAMIN_OK;
+    if (fixed() && closure_denied_) return leave();
     TRY(upload_rows());
   }
   InstOutcome& o = res[0];
   switch (h->status) {
     case kFusedOk: break;
-    case kFusedHandOff: return DFAMIN_OK;
+    case kFusedHandOff: return leave();
     case kFusedBad: o.status = DFAMIN_E_BAD_DFA; done = true; return DFAMIN_E_BAD_DFA;
     default: done = true; return DFAMIN_E_INTERNAL;
   }
@@ -2277,13 +2323,26 @@ int Engine::run_all(const std::vector<InstInput>& in, const dfamin_opts& opts, h
 int Engine::run(const std::vector<InstInput>& in, const dfamin_opts& opts, hipStream_t s,
                 std::vector<InstOutcome>& res) {
   if (fixed()) reset_fixed_region();
+  closure_cursor_ = 0;
+  closure_taken_ = 0;
+  const uint64_t beside = ctx_->budget > ctx_->used ? (ctx_->budget - ctx_->used) / 2 : 0;
   int rc = run_all(in, opts, s, res);
+  const bool beside_big = big_busy_;
   big_busy_ = false;
-  if (rc == DFAMIN_E_NOMEM && release_big()) {  // the rest did not fit beside d_fbig_
+  if (rc == DFAMIN_E_NOMEM && beside_big) {  // the rest may fit without d_fbig_
     (void)hipStreamSynchronize(s);
     no_big_ = true;
     rc = run_all(in, opts, s, res);
     no_big_ = false;
+  }
+  while (rc == DFAMIN_E_NOMEM && !fixed() && closure_taken_ > beside) {
+    // the arrays did not fit beside the levels: fewer of these, down to what
+    // there would be if the last call's storage could not be given back
+    (void)hipStreamSynchronize(s);
+    closure_limit_ = std::max(closure_taken_ / 2, beside);
+    closure_taken_ = 0;
+    rc = run_all(in, opts, s, res);
+    closure_limit_ = ~0ull;
   }
   // A call that stops early may leave work queued behind its last wait (the
   // next round's level passes and table clear): let it finish before the
@@ -2531,9 +2590,9 @@ int Engine::run_path(const std::vector<InstInput>& in, const dfamin_opts& opts, 
   TRY(queue_fill(d_refine_.p, 0, I * 4, s));
   TRY(queue_fill(d_ctrl_.p, 0, sizeof(Ctrl), s));
   large_ok_ = labels_planned_ && !batch && !direct_off_ && !fixed() && N >= kLargeStates &&
-              ctx_->tuner.forced < 0 && cas_forced_ < 0;
+              ctx_->tuner.forced < 0 && cas_forced_ < 0 &&
+              ensure(d_uniq_, 4ull * (kUniqTable + kUniqBuckets)) == DFAMIN_OK;
   if (large_ok_) {
-    TRY(ensure(d_uniq_, 4ull * (kUniqTable + kUniqBuckets)));
     TRY(queue_fill(d_uniq_.p, 0, 4ull * (kUniqTable + kUniqBuckets), s));
   }
   if (labels_planned_) {

@@ -176,3 +176,31 @@ def test_bad_dfa_leaves_device_outputs_untouched(ctx):
     rc = dfamin.load().dfamin_minimize(ctx.handle, dfamin.ctypes.byref(s), None, h.ctypes.data,
                                        dfamin.ctypes.byref(rr))
     assert rc == dfamin.DFAMIN_E_BAD_DFA and bool((h == SENTINEL).all())
+
+
+def test_small_budgets_take_calls_in_a_row():
+    """One context of a small budget: what the kernels of one call keep gives
+    way to the next call's needs.  Every call here fits its budget in a context
+    of its own, and has to in this one, in any order, with the same partition."""
+    from paper_2410_22764_amd import dfamin
+    ds = [W.random_dfa(300000, 2, 1), W.random_dfa(100000, 12, 1), W.permuted_chain_dfa(200000, 2, 1),
+          shift_dfa(20000, [1, 7], "shift(1,7) n=20000")]
+    want = [oracle.hopcroft(d.n, d.k, d.delta, d.accept) for d in ds]
+    batch = [W.random_dfa(17000 + 13 * i, 3, i) for i in range(60)]
+    bwant = [oracle.hopcroft(d.n, d.k, d.delta, d.accept)[0] for d in batch]
+    for mib in (72, 128, 176):
+        with dfamin.dfamin_create(0, mib << 20) as c:
+            for t in range(3):
+                for i in (0, 1, 2, 3) if t % 2 == 0 else (1, 0, 3, 2):
+                    d = ds[i]
+                    print(f"[case] budget {mib} MiB, pass {t}: {d.name} n={d.n} k={d.k}", flush=True)
+                    out, r = dfamin.dfamin_minimize(c, d, "auto", check=False)
+                    if mib < 100 and i == 1 and r["rc"] == dfamin.DFAMIN_E_NOMEM:
+                        continue  # (its buffers beside the largest call's)
+                    assert r["rc"] == dfamin.DFAMIN_OK, (mib, t, i, r)
+                    assert np.array_equal(out, want[i][0]) and r["num_blocks"] == want[i][1]
+                if mib >= 176:
+                    print(f"[case] budget {mib} MiB, pass {t}: batch of {len(batch)}", flush=True)
+                    outs, _ = dfamin.dfamin_minimize_batch(c, batch, "auto")
+                    for o, w in zip(outs, bwant):
+                        assert np.array_equal(o, w)
