@@ -363,3 +363,44 @@ def test_lanes_of_several_contexts():
     for t in ts:
         t.join()
     assert not errs, errs
+
+
+def _copied_chain(n, length, seed, k=1):
+    """Every state copies one of a chain of `length` states: `length` rounds of
+    n active states."""
+    r = np.random.RandomState(seed)
+    cls = r.permutation(np.concatenate([np.arange(length)] * 2 + [r.randint(0, length, n - 2 * length)]))
+    order = np.argsort(cls, kind="stable")
+    size = np.bincount(cls, minlength=length)
+    nxt = np.minimum(cls + 1, length - 1)
+    pick = (r.rand(n) * size[nxt]).astype(np.int64)
+    row = order[(np.cumsum(size) - size)[nxt] + pick].astype(np.uint32)
+    rows = np.concatenate([row[None], np.tile(np.arange(n, dtype=np.uint32), (k - 1, 1))])
+    return W.from_rows(rows, cls == length - 1, 0, f"copied chain({n},{length})"), cls
+
+def test_many_requests_beside_a_long_one(ctx):
+    """A large request is resident for thirty rounds; three hundred smaller
+    ones must not wait for a lane each round of it, but share its rounds (or
+    lanes seen to during them), and be done about when it is."""
+    from paper_2410_22764_amd import dfamin
+    length = 30
+    long, cls = _copied_chain(1 << 22, length, 1)
+    first = np.unique(cls, return_index=True)[1]
+    rank = np.empty(length, np.int64)
+    rank[np.argsort(first)] = np.arange(length)
+    ds = [W.random_dfa(17000 + 10 * i, 2, i) for i in range(10)]
+    want = [oracle.hopcroft(d.n, d.k, d.delta, d.accept)[0] for d in ds]
+    for _ in range(2):  # (the first pass fills the pools)
+        print("[case] serving: 300 requests beside a long one", flush=True)
+        tl = dfamin.dfamin_submit(ctx, long, {"closure": "off"})
+        tk = [dfamin.dfamin_submit(ctx, ds[i % 10], "auto") for i in range(300)]
+        rc, out, res = dfamin.dfamin_wait(ctx, tl, long.n, timeout_us=60_000_000)
+        ends = [dfamin.dfamin_wait(ctx, t, ds[i % 10].n, timeout_us=0) for i, t in enumerate(tk)]
+        late = [i for i, e in enumerate(ends) if e[0] == dfamin.DFAMIN_E_TIMEOUT]
+        for i in late:
+            ends[i] = dfamin.dfamin_wait(ctx, tk[i], ds[i % 10].n, timeout_us=60_000_000)
+        for i, (r, o, _) in enumerate(ends):
+            assert r == dfamin.DFAMIN_OK and np.array_equal(o, want[i % 10]), i
+        assert rc == dfamin.DFAMIN_OK and res["num_blocks"] == length and res["refine_rounds"] == length - 2
+        assert np.array_equal(out, rank[cls])
+    assert len(late) <= 60, len(late)
