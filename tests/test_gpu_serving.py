@@ -404,3 +404,24 @@ def test_many_requests_beside_a_long_one(ctx):
         assert rc == dfamin.DFAMIN_OK and res["num_blocks"] == length and res["refine_rounds"] == length - 2
         assert np.array_equal(out, rank[cls])
     assert len(late) <= 60, len(late)
+
+
+def test_cancelled_while_waiting_for_a_lane(ctx):
+    """A cancelled request that waits for a lane ends as cancelled without
+    being looked at: these are invalid, and would otherwise say so."""
+    from paper_2410_22764_amd import dfamin
+    good = _copied_chain(20000, 60, 1)[0]
+    bad = W.random_dfa(20000, 1, 2)
+    bad.delta = bad.delta.copy()
+    bad.delta[777] = bad.n
+    print("[case] serving: 300 requests for lanes, the last 10 cancelled", flush=True)
+    tk = [dfamin.dfamin_submit(ctx, good, {"closure": "off"}) for _ in range(290)]
+    tb = [dfamin.dfamin_submit(ctx, bad, {"closure": "off"}) for _ in range(10)]
+    time.sleep(0.005)  # admitted, their inputs on the device
+    for t in tb:
+        dfamin.dfamin_cancel(ctx, t)
+    for t in tb:
+        assert dfamin.dfamin_wait(ctx, t, bad.n, timeout_us=60_000_000)[0] == dfamin.DFAMIN_E_CANCELLED
+    for t in tk:
+        rc, _, res = dfamin.dfamin_wait(ctx, t, good.n, timeout_us=60_000_000)
+        assert rc == dfamin.DFAMIN_OK and res["num_blocks"] == 60
