@@ -62,6 +62,14 @@ constexpr uint64_t kClearAheadSlots = 1ull << 22;  // 32 MiB: a few microseconds
 // 256: 4.0 against 1.8 ms; 30,000 states: even at 16, 0.74 against 0.46 ms at
 // 64).
 constexpr uint64_t kBigMinRatio = 48;
+// A reachability frontier above this many states is followed by k_bfs_level on
+// all CUs, below by the grid kernel's 128 (whose levels cost no launch, copy
+// and wait of 20 us).  Kernel time and call, random, four letters: 2^24 states
+// 2.89 ms (the grid throughout 3.85, level by level 2.81) and 45.2 (46.3, 48.2);
+// 2^20 0.48 (0.61, 0.42) and 2.86 (2.91, 3.10); at 2^18 no frontier is as wide.
+// Half or twice the width: the same within 3%.  Levels this narrow also stay
+// far below the time that a barrier waits.
+constexpr uint32_t kBfsGridFrontier = 1u << 17;
 constexpr uint32_t kQueueRounds = 8;               // queued signature rounds per graph (even)
 
 }  // namespace
@@ -1700,83 +1708,88 @@ int Engine::minimal_dfa(const dfamin_opts& opts, hipStream_t s, uint32_t nb, uin
   TRY(upload_rows());
   uint32_t fcount = 1, reached = 1, levels = 0;
   // a long path: closure letters (words over Sigma) shorten it
+  std::vector<uint64_t> closure_rows;
   auto join_closure = [&]() -> int {
-    TRY(build_closure({0u}, opts, s));
-    rows = inst_rows_[0];
+    if (closure_rows.empty()) {
+      TRY(build_closure({0u}, opts, s));
+      closure_rows = inst_rows_[0];
+    }
+    rows = closure_rows;
     closure_used = true;
     return upload_rows();
   };
   const bool may_join = !closure_used && !nonid_[0].empty();
-  bool by_grid = false;
-  {
-    // Levels on the device (k_bfs_grid), in one launch, or two where the
-    // closure's rows join in between.  128 workgroups: a frontier of a
-    // quarter million states still has two per thread, and a barrier of
-    // twice as many costs 3 us more a level.
-    const uint32_t wgs = std::min<uint32_t>({128u, ctx_->cus, (n + kGridThreads - 1) / kGridThreads});
-    GridLease lease;
-    const char* knob = std::getenv("DFAMIN_GRID_MAX_STATES");
-    if (wgs && !(knob && std::atol(knob) <= 0) && ensure_gbar() == DFAMIN_OK &&
-        lease.take(ctx_->device, wgs, ctx_->cus)) {
-      TRY(ensure_host(h_gres_, sizeof(GridRes)));
-      TRY(ensure(d_qdbl_, 256));
+  // Narrow levels run on the device (k_bfs_grid), many to a launch; a frontier
+  // of more than kBfsGridFrontier states goes level by level, on all CUs.  (128
+  // workgroups: a barrier of twice as many costs 3 us more a level.)
+  const uint32_t wgs = std::min<uint32_t>({128u, ctx_->cus, (n + kGridThreads - 1) / kGridThreads});
+  GridLease lease;
+  const char* knob = std::getenv("DFAMIN_GRID_MAX_STATES");
+  bool grid = wgs && !(knob && std::atol(knob) <= 0) && ensure_gbar() == DFAMIN_OK &&
+              lease.take(ctx_->device, wgs, ctx_->cus);
+  bool seeded = false;  // visited and the first frontier are set
+  uint32_t* list[2] = {frontier, next};
+  uint32_t cur = 0;
+  if (grid) {
+    TRY(ensure_host(h_gres_, sizeof(GridRes)));
+    TRY(ensure(d_qdbl_, 256));
+  }
+  while (fcount) {
+    if (levels == kBfsLevelsBeforeClosure && !closure_used && may_join) TRY(join_closure());
+    if (grid && fcount <= kBfsGridFrontier) {
       BfsJob B{};
-      B.seed = 1;
+      B.rows = d_bfs_rows_.as<uint64_t>();
+      B.nrows = (uint32_t)rows.size();
+      B.fcount = fcount;
+      B.levels = levels;
+      B.reached = reached;
+      B.cur = cur;
+      B.max_levels = may_join && !closure_used ? kBfsLevelsBeforeClosure : 0xffffffffu;
+      B.max_frontier = kBfsGridFrontier;
+      B.seed = !seeded;
       B.q0 = x.q0;
       B.words = words;
-      B.list[0] = frontier;
-      B.list[1] = next;
+      B.list[0] = list[0];
+      B.list[1] = list[1];
       B.visited = visited;
       B.counter = d_qdbl_.as<uint32_t>();
       B.bar = gbar_;
       B.res = static_cast<GridRes*>(h_gres_.dp);
-      B.fcount = B.reached = 1;
       GridRes* h = h_gres_.as<GridRes>();
-      while (true) {
-        B.rows = d_bfs_rows_.as<uint64_t>();
-        B.nrows = (uint32_t)rows.size();
-        B.max_levels = may_join && !closure_used ? kBfsLevelsBeforeClosure : 0xffffffffu;
-        *h = GridRes{};
-        h->status = kGridAborted;
-        prof.begin(s, "bfs_level", 4.0 * n * (1.0 + 3.0 * rows.size()));
-        launch_bfs_grid(B, wgs, s);
-        prof.end(s);
-        HIP(hipGetLastError());
-        HIP(stream_wait(s));
-        stage_idle();
-        prof.collect();
-        by_grid = !h->aborted && h->status == kFusedOk;
-        if (!by_grid || !h->num_blocks) break;
-        B.fcount = h->num_blocks;
-        B.levels = h->rounds;
-        B.reached = h->refine_rounds;
-        B.cur = h->cur;
-        B.seed = 0;
-        TRY(join_closure());
+      *h = GridRes{};
+      h->status = kGridAborted;
+      prof.begin(s, "bfs_level", 4.0 * fcount * (1.0 + 3.0 * rows.size()));
+      launch_bfs_grid(B, wgs, s);
+      prof.end(s);
+      HIP(hipGetLastError());
+      HIP(stream_wait(s));
+      stage_idle();
+      prof.collect();
+      if (!h->aborted && h->status == kFusedOk) {
+        seeded = true;
+        fcount = h->num_blocks;
+        levels = h->rounds;
+        reached = h->refine_rounds;
+        cur = h->cur;
+      } else {  // a wait ran out: from the start, level by level
+        grid = seeded = false;
+        fcount = reached = 1;
+        levels = cur = 0;
+        if (closure_used && may_join) {
+          rows.clear();
+          for (uint32_t a : nonid_[0]) rows.push_back(reinterpret_cast<uint64_t>(x.delta) + 4ull * a * n);
+          closure_used = false;
+          TRY(upload_rows());
+        }
       }
-      reached = h->refine_rounds;
-      levels = h->rounds;
+      continue;
     }
-  }
-  if (!by_grid) {
-    if (levels || reached != 1) {  // gave up: from the start, level by level
-      levels = 0;
-      reached = 1;
-      if (closure_used && may_join) {
-        rows.clear();
-        for (uint32_t a : nonid_[0]) rows.push_back(reinterpret_cast<uint64_t>(x.delta) + 4ull * a * n);
-        closure_used = false;
-        TRY(upload_rows());
-      }
-    }
-    TRY(start());
-  }
-  while (!by_grid && fcount) {
-    if (levels == kBfsLevelsBeforeClosure && !closure_used && !nonid_[0].empty()) TRY(join_closure());
+    if (!seeded) TRY(start());
+    seeded = true;
     TRY(queue_fill(counter, 0, 4, s));
     TRY(flush_segs(s));
     prof.begin(s, "bfs_level", 4.0 * fcount * (1.0 + 3.0 * rows.size()));
-    launch_bfs_level(d_bfs_rows_.as<uint64_t>(), (uint32_t)rows.size(), frontier, fcount, visited, next,
+    launch_bfs_level(d_bfs_rows_.as<uint64_t>(), (uint32_t)rows.size(), list[cur], fcount, visited, list[cur ^ 1u],
                      counter, s);
     prof.end(s);
     HIP(hipGetLastError());
@@ -1787,7 +1800,7 @@ int Engine::minimal_dfa(const dfamin_opts& opts, hipStream_t s, uint32_t nb, uin
     fcount = hj[2];
     reached += fcount;
     ++levels;
-    std::swap(frontier, next);
+    cur ^= 1u;
   }
   // quotient of the reachable classes
   uint32_t* sel = d_nb_.as<uint32_t>();

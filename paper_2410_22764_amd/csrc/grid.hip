@@ -840,7 +840,8 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
 
 // Breadth-first levels from a frontier, one barrier per level instead of one
 // launch, readback and host decision (whole minimal-DFA calls, four letters:
-// 30,000 states 740 -> 370 us, 262,144 states 1,558 -> 1,177 us).  Each workgroup
+// 30,000 states 740 -> 370 us, 262,144 states 1,558 -> 1,177 us), until the
+// frontier is wide enough for a launch per level.  Each workgroup
 // stages the states it visits first in LDS and appends them with one atomic
 // per chunk of rows, as k_bfs_level does; the barrier's sum is the next
 // frontier's size, so no counter is read.  Bound: the latency of a level's
@@ -863,7 +864,7 @@ __global__ __launch_bounds__(kT) void k_bfs_grid(BfsJob B) {
     unsigned long long sum = 0;
     ok = sync.wait(0, sum);
   }
-  while (ok && f && levels < B.max_levels) {
+  while (ok && f && f <= B.max_frontier && levels < B.max_levels) {
     const uint32_t* frontier = B.list[cur];
     uint32_t* next = B.list[cur ^ 1u];
     uint32_t* counter = B.counter + (levels & 1u) * 32u;  // zero: reset a level ago, or by the host

@@ -281,14 +281,15 @@ __host__ __device__ inline uint32_t grid_records(uint32_t letters) { return (let
 bool grid_shape(uint32_t n, uint32_t cus, uint32_t* items, uint32_t* wgs);
 void launch_grid(const GridJob& J, uint32_t items, uint32_t wgs, hipStream_t s);
 // Breadth-first levels by the grid kernel's barrier: from the fcount states
-// in list[cur] until no new state is found or max_levels levels have run.
+// in list[cur] until no new state is found, the frontier is larger than
+// max_frontier or max_levels levels have run.
 // counter: two words 128 bytes apart, zero before the launch (or cleared by
 // it, with seed).  The result's
 // num_blocks is the frontier left, rounds the levels, refine_rounds the
 // states reached, cur the list that holds the frontier.
 struct BfsJob {
   const uint64_t* rows;
-  uint32_t nrows, fcount, levels, reached, cur, max_levels;
+  uint32_t nrows, fcount, levels, reached, cur, max_levels, max_frontier;
   uint32_t seed, q0;  // seed: first clear visited (words) and the counters and start from {q0}
   uint64_t words;
   uint32_t* list[2];

@@ -188,3 +188,25 @@ def test_noalloc_holds_the_same_levels(ctx, n, steps, closure, monkeypatch):
     assert got[0][0] == got[1][0]
     assert np.array_equal(got[0][1], got[1][1])
     assert np.array_equal(got[0][1], oracle.hopcroft(d.n, d.k, d.delta, d.accept)[0])
+
+
+@pytest.mark.parametrize("n,k,tail", [(1 << 19, 4, 0), (400003, 3, 90)])
+def test_wide_frontiers_leave_the_grid(ctx, n, k, tail, monkeypatch):
+    """Reachability: wide levels run one launch each on all CUs, narrow ones
+    (before, between and after them; a path long enough for closure rows)
+    many to a launch; the same minimal DFA and level count as level by level."""
+    r = np.random.RandomState(n)
+    rows = r.randint(tail, n, (k, n)).astype(np.uint32)
+    rows[:, :tail] = np.arange(1, tail + 1)  # a path into the wide part
+    d = W.from_rows(rows, r.rand(n) < 0.5, 0, f"wide({n},{k},{tail})")
+    print(f"[case] minimal {d.name}", flush=True)
+    a = dfamin.dfamin_minimal_dfa(ctx, d)
+    dfamin.dfamin_set_profiling(ctx, True)
+    dfamin.dfamin_minimal_dfa(ctx, d)
+    launches = {s["name"]: s["launches"] for s in dfamin.dfamin_get_kernel_stats(ctx)}["bfs_level"]
+    dfamin.dfamin_set_profiling(ctx, False)
+    monkeypatch.setenv("DFAMIN_GRID_MAX_STATES", "0")
+    b = dfamin.dfamin_minimal_dfa(ctx, d)
+    assert a[0] == b[0] and a[3] == b[3]
+    assert all(np.array_equal(a[i], b[i]) for i in (1, 2, 4))
+    assert 3 <= launches < a[3]["bfs_levels"]
