@@ -32,6 +32,26 @@ struct GridLease {
   ~GridLease() { give(); }
 };
 
+// After a grid kernel whose waits ran out (another process holds CUs, say) the
+// next calls take the other path at once, twice as many each time up to 1,024:
+// a wait costs 20 ms.
+struct GridBackoff {
+  uint32_t skip = 0, last = 0;
+  bool pass() {
+    if (!skip) return true;
+    --skip;
+    return false;
+  }
+  void ended(bool ran_out) {
+    last = ran_out ? (last ? (last < 1024u ? 2u * last : last) : 1u) : 0u;
+    skip = last;
+  }
+};
+// Testing: DFAMIN_GRID_ABORT=m, bit i of m set: the i-th grid launch of a call
+// (of a lane: every one, bit 0) finds its abort word set and a barrier that is
+// never full, and gives up there at once.
+void test_abort(GridBar* bar, uint32_t launch, hipStream_t s);
+
 // A device buffer that only grows; its bytes count against the context budget.
 struct DevBuf {
   void* p = nullptr;
@@ -289,6 +309,8 @@ class Engine {
   // grid kernel: its barrier words (zero between launches; never part of the
   // fixed region) and its mapped result (arrays: d_grid_)
   GridBar* gbar_ = nullptr;
+  GridBackoff backoff_;
+  uint32_t grid_launches_ = 0;  // of this call
   HostBuf h_gres_;
   std::vector<uint32_t> fused_pos_;  // per entry of `which`: index in the job array
   // A batch's fused kernels run on their own stream beside the round

@@ -93,6 +93,13 @@ bool GridLease::take(int device, uint32_t want, uint32_t cus) {
   return true;
 }
 
+void test_abort(GridBar* bar, uint32_t launch, hipStream_t s) {
+  const char* e = std::getenv("DFAMIN_GRID_ABORT");
+  if (!e || launch >= 32 || !((std::strtoul(e, nullptr, 10) >> launch) & 1u)) return;
+  launch_store_u64(reinterpret_cast<uint64_t*>(&bar->root[0].v), 1ull << 63, s);  // a count no launch arrives at
+  launch_store_u64(reinterpret_cast<uint64_t*>(&bar->abort), 1ull, s);            // (and padding behind the word)
+}
+
 // ------------------------------------------------------------------ Profiler
 Profiler::~Profiler() {
   for (auto& p : pending_) { (void)hipEventDestroy(p.a); (void)hipEventDestroy(p.b); }
@@ -1725,7 +1732,7 @@ int Engine::minimal_dfa(const dfamin_opts& opts, hipStream_t s, uint32_t nb, uin
   const uint32_t wgs = std::min<uint32_t>({128u, ctx_->cus, (n + kGridThreads - 1) / kGridThreads});
   GridLease lease;
   const char* knob = std::getenv("DFAMIN_GRID_MAX_STATES");
-  bool grid = wgs && !(knob && std::atol(knob) <= 0) && ensure_gbar() == DFAMIN_OK &&
+  bool grid = wgs && !(knob && std::atol(knob) <= 0) && backoff_.pass() && ensure_gbar() == DFAMIN_OK &&
               lease.take(ctx_->device, wgs, ctx_->cus);
   bool seeded = false;  // visited and the first frontier are set
   uint32_t* list[2] = {frontier, next};
@@ -1759,13 +1766,16 @@ int Engine::minimal_dfa(const dfamin_opts& opts, hipStream_t s, uint32_t nb, uin
       *h = GridRes{};
       h->status = kGridAborted;
       prof.begin(s, "bfs_level", 4.0 * fcount * (1.0 + 3.0 * rows.size()));
+      test_abort(gbar_, grid_launches_++, s);
       launch_bfs_grid(B, wgs, s);
       prof.end(s);
       HIP(hipGetLastError());
       HIP(stream_wait(s));
       stage_idle();
       prof.collect();
-      if (!h->aborted && h->status == kFusedOk) {
+      const bool ran_out = h->aborted || h->status != kFusedOk;
+      backoff_.ended(ran_out);
+      if (!ran_out) {
         seeded = true;
         fcount = h->num_blocks;
         levels = h->rounds;
@@ -2014,7 +2024,7 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
   done = false;
   const InstInput& x = in[0];
   uint32_t items = 0, wgs = 0;
-  if (!grid_applies(x, opts, &items, &wgs)) return DFAMIN_OK;
+  if (!grid_applies(x, opts, &items, &wgs) || !backoff_.pass()) return DFAMIN_OK;
   GridLease lease;
   if (!lease.take(ctx_->device, wgs, ctx_->cus)) return DFAMIN_OK;
   const size_t n = x.n;
@@ -2132,12 +2142,15 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
     *h = GridRes{};
     h->status = kGridAborted;
     prof.begin(s, "grid", 4.0 * x.n * x.k + x.n / 8.0 + 4.0 * x.n);
+    test_abort(gbar_, grid_launches_++, s);
     launch_grid(J, items, wgs, s);
     prof.end(s);
     HIP(hipGetLastError());
     HIP(stream_wait(s));
     prof.collect();
-    if (h->aborted || h->status == kGridAborted) return leave();  // a wait ran out: the round engine takes it
+    const bool ran_out = h->aborted || h->status == kGridAborted;
+    backoff_.ended(ran_out);
+    if (ran_out) return leave();  // the round engine takes it
     if (h->status != kFusedHandOff || J.resume || h->doubling) break;
     // AUTO, still splitting after auto_rounds rounds: the closure's letters
     // join and the kernel goes on from its partition
@@ -2338,6 +2351,7 @@ int Engine::run(const std::vector<InstInput>& in, const dfamin_opts& opts, hipSt
   if (fixed()) reset_fixed_region();
   closure_cursor_ = 0;
   closure_taken_ = 0;
+  grid_launches_ = 0;
   const uint64_t beside = ctx_->budget > ctx_->used ? (ctx_->budget - ctx_->used) / 2 : 0;
   int rc = run_all(in, opts, s, res);
   const bool beside_big = big_busy_;

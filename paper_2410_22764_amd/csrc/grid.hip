@@ -84,9 +84,10 @@ __device__ __forceinline__ void store_agent(T* p, T v) {
 // Grid barrier that also sums a payload over the workgroups.  Four words
 // rotate; workgroup 0 resets the one used two barriers ago, which no
 // workgroup can still be reading.  Returns false (for the whole workgroup)
-// when a wait ran out -- some workgroup is not resident -- or another
-// workgroup gave up: the caller leaves at once and the host takes another
-// path.  What was written before the barrier is visible after it.
+// when a wait ran out -- some workgroup is not resident, or its step took
+// longer than 20 ms -- or another workgroup gave up: the caller leaves at once
+// and the host takes another path.  What was written before the barrier is
+// visible after it.
 struct GridSync {
   GridBar* bar;
   uint32_t G, wg, gen;

@@ -384,6 +384,7 @@ struct Serving::Impl {
     size_t sz_scratch = 0;
   };
   Lane lanes[kLanes];
+  GridBackoff backoff;
   std::deque<Resident*> gpend;  // requests waiting for a lane
   std::vector<Resident*> back_;  // handed back during a round: to join before the next
   uint32_t* h_last() { return reinterpret_cast<uint32_t*>(static_cast<char*>(h_ctrl.p) + sizeof(Ctrl)); }
@@ -1008,6 +1009,7 @@ struct Serving::Impl {
     GridRes* h = l.res.as<GridRes>();
     *h = GridRes{};
     h->status = kGridAborted;
+    test_abort(J.bar, 0, l.stream);
     launch_grid(J, items, wgs, l.stream);
     l.r = r;
     if (hipGetLastError() != hipSuccess ||
@@ -1029,6 +1031,7 @@ struct Serving::Impl {
       l.lease.give();
       pool.free(l.scratch, l.sz_scratch);
       const GridRes& f = *l.res.as<GridRes>();
+      backoff.ended(f.aborted || f.status == kGridAborted);
       auto req = r->req;
       const uint32_t ar = req->opts.auto_rounds ? req->opts.auto_rounds : kDefaultAutoRounds;
       // (a request whose states are all told apart by the very round after
@@ -1546,7 +1549,7 @@ struct Serving::Impl {
         uint32_t items, wgs;
         for (Resident* r : joining) {
           if (fusable(*r->req)) fpend.push_back(r);
-          else if (grid_takes(*r->req, &items, &wgs)) gpend.push_back(r);
+          else if (grid_takes(*r->req, &items, &wgs) && backoff.pass()) gpend.push_back(r);
           else rest.push_back(r);
         }
         joining.swap(rest);

@@ -210,3 +210,95 @@ def test_wide_frontiers_leave_the_grid(ctx, n, k, tail, monkeypatch):
     assert a[0] == b[0] and a[3] == b[3]
     assert all(np.array_equal(a[i], b[i]) for i in (1, 2, 4))
     assert 3 <= launches < a[3]["bfs_levels"]
+
+
+def _grid_launches(ctx, call, name="grid"):
+    dfamin.dfamin_set_profiling(ctx, True)
+    got = call()
+    n = sum(s["launches"] for s in dfamin.dfamin_get_kernel_stats(ctx) if s["name"] == name)
+    dfamin.dfamin_set_profiling(ctx, False)
+    return got, n
+
+
+@pytest.mark.parametrize("mask", [1, 2, 3])
+@pytest.mark.parametrize("d,closure", [(W.random_dfa(40001, 3, 1), "off"), (W.random_dfa(300007, 2, 2), "auto"),
+                                       (W.permuted_chain_dfa(30001, 2, 3), "auto"), (W.bitsplitter_dfa(14), "auto"),
+                                       (W.bitsplitter_dfa(13), "on")], ids=lambda x: getattr(x, "name", x))
+def test_given_up_launches(d, closure, mask, monkeypatch):
+    """A launch whose waits run out (the first, the one after the closure was
+    built): the call ends as ever through the round engine, also in the fixed
+    region, and the next launch finds its barrier in order."""
+    import torch
+    want, nb = oracle.hopcroft(d.n, d.k, d.delta, d.accept)
+    delta = torch.from_numpy(d.delta.view(np.int32)).cuda()
+    acc = torch.from_numpy(d.accept).cuda()
+    with dfamin.dfamin_create(0) as c:
+        for fn in (dfamin.dfamin_minimize_device, dfamin.dfamin_minimize_device_noalloc):
+            def call():
+                out = torch.full((d.n,), -1, dtype=torch.int32, device="cuda")
+                r = fn(c, d.n, d.k, delta.data_ptr(), acc.data_ptr(), d.q0, out.data_ptr(), opts=closure,
+                       stream=torch.cuda.current_stream().cuda_stream)
+                torch.cuda.synchronize()
+                return r, out.cpu().numpy()
+            plain = call()
+            monkeypatch.setenv("DFAMIN_GRID_ABORT", str(mask))
+            print(f"[case] {fn.__name__} {d.name} {closure} launches {mask:b} given up", flush=True)
+            given_up = call()
+            monkeypatch.delenv("DFAMIN_GRID_ABORT")
+            for r, out in (plain, given_up, call(), call(), call()):
+                assert r == plain[0] and r["num_blocks"] == nb and np.array_equal(out, want)
+
+
+def test_given_up_calls_are_remembered(monkeypatch):
+    """After a call whose launch gave up, the next takes the round engine at
+    once, after a second one in a row the next two, and so on; a launch that
+    ends well puts that back."""
+    d = W.random_dfa(40001, 3, 1)
+    want = oracle.hopcroft(d.n, d.k, d.delta, d.accept)[0]
+    launches = []
+    with dfamin.dfamin_create(0) as c:
+        for i in range(12):
+            if i == 0:
+                monkeypatch.setenv("DFAMIN_GRID_ABORT", "1")
+            if i == 5:
+                monkeypatch.delenv("DFAMIN_GRID_ABORT")
+            (out, _), n = _grid_launches(c, lambda: dfamin.dfamin_minimize(c, d))
+            assert np.array_equal(out, want)
+            launches.append(n)
+    assert launches == [1, 0, 1, 0, 0, 1, 1, 1, 1, 1, 1, 1]
+
+
+@pytest.mark.parametrize("mask", [2, 4, 6])
+def test_given_up_reachability(mask, monkeypatch):
+    """The reachability kernel gives up in its first launch, and in the one
+    after closure rows have joined: level by level from the start."""
+    n = 20001
+    q = np.arange(n)
+    rows = np.stack([np.minimum(q + 1, n - 1), np.minimum(q + 2, n - 1)]).astype(np.uint32)
+    for d in (W.random_dfa(30001, 3, 2), W.from_rows(rows, np.random.RandomState(1).rand(n) < 0.5, 0, "path")):
+        with dfamin.dfamin_create(0) as c:
+            a = dfamin.dfamin_minimal_dfa(c, d)
+            monkeypatch.setenv("DFAMIN_GRID_ABORT", str(mask))
+            print(f"[case] minimal {d.name}, launches {mask:b} given up", flush=True)
+            b = dfamin.dfamin_minimal_dfa(c, d)
+            monkeypatch.delenv("DFAMIN_GRID_ABORT")
+            for x in (b, dfamin.dfamin_minimal_dfa(c, d), dfamin.dfamin_minimal_dfa(c, d)):
+                assert a[0] == x[0] and a[3] == x[3]
+                assert all(np.array_equal(a[i], x[i]) for i in (1, 2, 4))
+
+
+def test_given_up_lanes(monkeypatch):
+    """Requests whose lane gives up join the resident set."""
+    ds = [W.random_dfa(20000 + 5000 * i, 2 + i % 3, i) for i in range(8)] + [W.permuted_chain_dfa(30000, 2, 9)]
+    want = [oracle.hopcroft(d.n, d.k, d.delta, d.accept) for d in ds]
+    with dfamin.dfamin_create(0) as c:
+        for i in range(4):
+            if i == 1:
+                monkeypatch.setenv("DFAMIN_GRID_ABORT", "1")
+            if i == 2:
+                monkeypatch.delenv("DFAMIN_GRID_ABORT")
+            print(f"[case] serving, lanes {'given up' if i == 1 else 'as ever'}", flush=True)
+            tk = [dfamin.dfamin_submit(c, d, "auto") for d in ds]
+            for t, d, (w, nb) in zip(tk, ds, want):
+                rc, out, res = dfamin.dfamin_wait(c, t, d.n, timeout_us=60_000_000)
+                assert rc == dfamin.DFAMIN_OK and res["num_blocks"] == nb and np.array_equal(out, w)
