@@ -197,7 +197,8 @@ Engine::~Engine() {
                     &d_keep_, &d_rank_, &d_sig_, &d_table_, &d_status_, &d_changed_, &d_rb_,
                     &d_results_, &d_wgflags_, &d_part_, &d_dense_,
                     &d_djobs_, &d_visit_, &d_bfs_rows_, &d_min_delta_, &d_min_acc_,
-                    &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_fbig_, &d_grid_, &d_grec_, &d_uniq_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
+                    &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_fbig_, &d_grid_, &d_grec_,
+                    &d_uniq_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
   if (gbar_) (void)hipFree(gbar_);
   // device buffers of the fixed-region mode belong to the region
   if (!fixed()) {
@@ -218,7 +219,8 @@ uint64_t Engine::device_bytes() const {
                           &d_keep_, &d_rank_, &d_sig_, &d_table_, &d_status_, &d_changed_, &d_rb_,
                           &d_results_, &d_wgflags_, &d_part_, &d_dense_,
                           &d_djobs_, &d_visit_, &d_bfs_rows_, &d_min_delta_, &d_min_acc_,
-                          &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_fbig_, &d_grid_, &d_grec_, &d_uniq_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
+                          &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_fbig_, &d_grid_, &d_grec_,
+                    &d_uniq_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
   uint64_t t = 0;
   for (const DevBuf* b : bufs) t += b->cap;
   for (const DevBuf& b : closure_bufs_) t += b.cap;
@@ -1032,8 +1034,8 @@ int Engine::signature_rounds(const dfamin_opts& opts, uint64_t max_rounds, hipSt
         if (!ev_rb_) HIP(hipEventCreateWithFlags(&ev_rb_, hipEventDisableTiming));
         HIP(hipEventRecord(ev_rb_, s));
         const uint32_t bits = (desc_[0].kp + 1u) * (desc_[0].kp + 1u);
-        if (!(large && desc_[0].kp == 4) && !batch && slots_ok && !direct_off_ && !fixed() && bits <= kDirectMaxBits && bits >= 1 &&
-            (1ull << bits) <= 8ull * m) {
+        if (!(large && desc_[0].kp == 4) && !batch && slots_ok && !direct_off_ && !fixed() &&
+            bits <= kDirectMaxBits && bits >= 1 && (1ull << bits) <= 8ull * m) {
           TRY(ensure(d_dtab_, 4ull << bits));
           launch_clear_table(d_dtab_.as<Slot>(), 1ull << (bits - 1), d_ctrl_.as<Ctrl>(), s, 0, gcount);
           HIP(hipGetLastError());

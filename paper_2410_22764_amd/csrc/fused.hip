@@ -362,7 +362,8 @@ __global__ void __launch_bounds__(NT, 4) k_fused(const FusedJob* __restrict__ jo
         // this throw's slot and fragment
         // (the multiplier is made opaque in each of the three steps: the
         // compiler would otherwise keep every state's slot and fragment from
-        // one step to the next, and spill)
+        // one step to the next, and spill; at 16 states per thread 23
+        // registers still do)
         uint32_t mul = 0x9E3779B1u + 0x3C6EF372u * t;  // odd: a bijection of h
         asm volatile("" : "+s"(mul));
         auto aim = [&](uint32_t h, uint32_t& pos, uint32_t& frag) {
@@ -552,11 +553,11 @@ __global__ void __launch_bounds__(NT, 4) k_fused(const FusedJob* __restrict__ jo
 // Larger instances of a batch (16,384 < n <= 65,536), one workgroup each: the
 // same rounds and the same grouping by minimum, with the block ids (16-bit)
 // and the table sharing the LDS -- 30,000 slots at 20,000 states, 7,700 at
-// 65,536 -- and hashes, new ids and lists in global scratch that stays in the
-// caches.  Where a round may form more groups than the table takes, its
-// states are first sorted into slices of the hash (all members of a group
-// share one), and each throw takes one more slice along with what the last
-// throw left.  Bound: LDS operations and the row reads of each round, on as
+// 65,536 -- and hashes, lists and signatures in global scratch (796 instances
+// at once move 3.3 GB into and 2.8 GB out of L2 a launch for it).  Where a
+// round may form more groups than the table takes, its states are first sorted
+// into slices of the hash (all members of a group share one), and each throw
+// takes one more slice along with what the last throw left.  Bound: LDS operations and the row reads of each round, on as
 // many CUs as there are instances; a round of the round engine moves the same
 // states through device atomics (27 G/s) and a dozen launches instead.  A
 // random instance of 65,536 states and two letters takes 1.0 ms (six rounds

@@ -30,8 +30,8 @@
 // rounds (the one-workgroup kernel up to 16,384 states): Fib_20 (17,711
 // states, 15 rounds) 932 -> 184 us; a permuted chain of 300,007 states (19
 // rounds) 1,240 -> 400 us; random, n = 16,384, two letters, 140 -> 81 us; the
-// 2^20-state bit-splitter 5.14 -> 1.61 ms, much of it reading rows and
-// records at 6-8 TB/s from the caches (records of four bytes an id: 1.95).
+// 2^20-state bit-splitter 5.14 -> 1.60 ms, much of it reading rows and
+// records (with records of four bytes an id 1.95).
 #include "../../include/dfamin.h"
 #include "internal.h"
 
@@ -260,9 +260,7 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
   // letter and hold more registers: 2^19 states, 18 letters, 1.04 against 0.83
   // ms, 32,768 states and 14 letters 0.35 against 0.32.)
   constexpr int CL = 3;
-  // states are grouped in LDS kPass items at a time, in twice as many slots
-  constexpr int kPass = ITEMS < 4 ? ITEMS : 4;
-  constexpr uint32_t kLds = 2u * kPass * kT;
+  constexpr uint32_t kLds = 2u * ITEMS * kT;  // slots for grouping the workgroup's states
   __shared__ unsigned long long lkey[kLds];
   __shared__ uint32_t lmin[kLds], lval[kLds];  // least state; member count, then the slot
   __shared__ unsigned long long s_val[2], s_rows[kFusedMaxLetters];
@@ -386,15 +384,9 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
     // and the shared bit, and a read then saves the atomic
     const bool read_first = (uint64_t)count * 64u < n;
     uint32_t lp[ITEMS];
+    __syncthreads();
 #pragma unroll
     for (int e = 0; e < ITEMS; ++e) {
-      if (e % kPass == 0) {
-        if (e) {
-          __syncthreads();
-          clear_lds();
-        }
-        __syncthreads();
-      }
       const bool act = !(own[e] & kSingleBit);
       uint64_t hh = mix_end(h[e]);
       if (J.hash_mask) hh = mix_end(hh & J.hash_mask);
@@ -422,19 +414,17 @@ __global__ __launch_bounds__(kT) void k_grid(GridJob J) {
       }
       const uint32_t fp = __shfl(lp[e], f, 64);
       if (like) lp[e] = fp;
-      if (e % kPass == kPass - 1) {
-        __syncthreads();
-        // one insert per local group, by its least member (the only one to
-        // read the group's count, which the slot then replaces)
-#pragma unroll
-        for (int i = e - kPass + 1; i <= e; ++i)
-          if (!(own[i] & kSingleBit) && lmin[lp[i]] == state(i))
-            lval[lp[i]] = grid_insert(table, S, h[i], state(i), lval[lp[i]] > 1u, read_first, &s_fault);
-        __syncthreads();
-#pragma unroll
-        for (int i = e - kPass + 1; i <= e; ++i) slot[i] = (own[i] & kSingleBit) ? kNoSlot : lval[lp[i]];
-      }
     }
+    __syncthreads();
+    // one insert per local group, by its least member (the only one to read
+    // the group's count, which the slot then replaces)
+#pragma unroll
+    for (int e = 0; e < ITEMS; ++e)
+      if (!(own[e] & kSingleBit) && lmin[lp[e]] == state(e))
+        lval[lp[e]] = grid_insert(table, S, h[e], state(e), lval[lp[e]] > 1u, read_first, &s_fault);
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < ITEMS; ++e) slot[e] = (own[e] & kSingleBit) ? kNoSlot : lval[lp[e]];
   };
   // Ends the resolve step: new ids (nid) are known; counts leaders, and
   // after the barrier decides what comes next.  True: another round.
@@ -927,11 +917,12 @@ __global__ __launch_bounds__(kT) void k_bfs_grid(BfsJob B) {
 // 1,024 threads and the fewest states per thread that fit the CUs: more
 // workgroups with fewer states each beat fewer barrier arrivals (n = 150,000
 // chain: 314 us with 147 workgroups of one state per thread, 399 with 74 of
-// two), while 512 or 256 threads for small n changed nothing.  Above four
-// states per thread the registers spill, whose dirty lines every barrier has
-// to write back, and the gathers no longer fit the caches: random DFAs of
-// 2^21 states took 790 us against the round engine's 600 (at 2^20: 332
-// against 415), so larger instances stay with the round engine.
+// two), while 512 or 256 threads for small n changed nothing.  At four states
+// per thread the kernel uses 64 bytes of scratch a thread; at eight many
+// registers spill, whose dirty lines every barrier has to write back, and the
+// gathers no longer fit the caches: random DFAs of 2^21 states took 790 us
+// against the round engine's 600 (at 2^20: 332 against 415), so larger
+// instances stay with the round engine.
 bool grid_shape(uint32_t n, uint32_t cus, uint32_t* items, uint32_t* wgs) {
   uint32_t it = 1;
   while (it <= kGridMaxItems && (uint64_t)it * kGridThreads * cus < n) it *= 2;

@@ -207,8 +207,6 @@ constexpr uint32_t kFusedMaxLetters = 32;
 // of LDS)
 constexpr int kFusedClasses = 4;
 inline int fused_class(uint32_t n) { return n <= 512 ? 0 : (n <= 2048 ? 1 : (n <= 8192 ? 2 : 3)); }
-// one (nullable): a single job passed by value (jobs is then ignored and
-// njobs taken as 1).  res may be mapped page-locked host memory.
 // Instances of a batch above kFusedMaxStates and up to kFusedBigStates
 // states, one workgroup each (the other conditions as above).
 constexpr uint32_t kFusedBigStates = 65536;
@@ -216,6 +214,8 @@ inline uint64_t fused_big_scratch(uint32_t n, uint32_t k) {
   return (((uint64_t)n + 3) & ~3ull) * (36 + 16 * (((uint64_t)k + 8) / 8)) + 64;
 }
 void launch_fused_big(const FusedJob* jobs, FusedRes* res, uint32_t njobs, hipStream_t s);
+// one (nullable): a single job passed by value (jobs is then ignored and
+// njobs taken as 1).  res may be mapped page-locked host memory.
 void launch_fused(const FusedJob* jobs, FusedRes* res, uint32_t njobs, int cls, hipStream_t s,
                   const FusedJob* one = nullptr);
 

@@ -13,8 +13,9 @@
 //      of its states only (segmented scan), copy-out, buffers released.
 // Requests of up to 524,288 states (closure OFF or AUTO) seldom get that far:
 // up to 16,384 states they run as batches of the fused kernel, above that one
-// by one on the grid kernel, both on streams of their own beside the resident
-// set, which takes what those kernels hand back.
+// by one on the grid kernel while nothing is resident, both on streams of
+// their own; the resident set takes what those kernels hand back, and the
+// larger ones while it has a request of its own.
 // Instances never interact: block ids are global state ids, so a request's
 // result is the same alone and in any mix.
 #include "serving.h"

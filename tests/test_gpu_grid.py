@@ -302,3 +302,9 @@ def test_given_up_lanes(monkeypatch):
             for t, d, (w, nb) in zip(tk, ds, want):
                 rc, out, res = dfamin.dfamin_wait(c, t, d.n, timeout_us=60_000_000)
                 assert rc == dfamin.DFAMIN_OK and res["num_blocks"] == nb and np.array_equal(out, w)
+
+
+def test_largest_size(ctx, monkeypatch):
+    """1,048,576 states on 256 CUs, the last size of the grid kernel."""
+    _check(ctx, W.random_dfa(1048576, 2, 1), monkeypatch)
+    _check(ctx, W.permuted_chain_dfa(1048576, 2, 2), monkeypatch)
