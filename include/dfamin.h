@@ -136,7 +136,8 @@ typedef struct {
 
 /* ---- context ----------------------------------------------------------- */
 /* Create a context on HIP device `hip_device`.  hbm_budget_bytes caps the
- * device memory the context may hold (0 = 90% of the device's free memory).
+ * device memory the context may hold (0 = 90% of the device's free memory);
+ * a few KiB of barrier words, held from the start, are beside it.
  * Returns DFAMIN_E_DEVICE if the device cannot be used. */
 int dfamin_create(int hip_device, uint64_t hbm_budget_bytes, dfamin_ctx **out);
 
@@ -168,7 +169,8 @@ int dfamin_minimize_device(dfamin_ctx *ctx, const dfamin_dfa *dev_dfa, const dfa
  * signature records, closure levels, scan status, control block) is carved
  * from one static device array of DFAMIN_NOALLOC_SCRATCH_BYTES bytes, which
  * the library holds on each device it runs on until the process ends; the
- * host-side staging it uses was set up by dfamin_create.  The caller still
+ * host-side staging and the barrier words it uses were set up by
+ * dfamin_create.  The caller still
  * passes delta, accept and dev_out in device memory.
  *   - Size limit: n * (66 + 16 * (k + 1)) + 2^20 must not exceed
  *     DFAMIN_NOALLOC_SCRATCH_BYTES (about 579,000 states at k = 2);

@@ -372,7 +372,8 @@ int dfamin_minimal_dfa(dfamin_ctx* ctx, const dfamin_dfa* host_dfa, const dfamin
   dfamin_result r{};
   const dfamin_opts o = opts_or_default(opts);
   // the reachability search and the quotient read the round engine's
-  // buffers (block ids, closure rows): this instance goes through it
+  // buffers (block ids, closure rows): this instance goes through it, or
+  // through the grid kernel, which leaves them as it does
   ctx->c.engine.no_fused = true;
   rc = run_host_batch(ctx->c, 1, host_dfa, o, outs, &r);
   ctx->c.engine.no_fused = false;

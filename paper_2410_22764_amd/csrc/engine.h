@@ -336,7 +336,7 @@ class Engine {
   // A new call is about to take memory (its level buffers are all free).
   void begin_call() { closure_cursor_ = 0; }
   // Set by callers that read the round engine's buffers after run() (the
-  // minimal DFA): every instance then goes through the round engine.
+  // minimal DFA): the fused kernels, which have none, are then left out.
   bool no_fused = false;
  private:
   // fixed-region mode (set_fixed_region)

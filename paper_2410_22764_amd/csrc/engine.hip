@@ -220,7 +220,7 @@ uint64_t Engine::device_bytes() const {
                           &d_results_, &d_wgflags_, &d_part_, &d_dense_,
                           &d_djobs_, &d_visit_, &d_bfs_rows_, &d_min_delta_, &d_min_acc_,
                           &d_lvl_, &d_lvl_wg_, &d_lvl_flags_, &d_qdbl_, &d_fjobs_, &d_fbig_, &d_grid_, &d_grec_,
-                    &d_uniq_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
+                          &d_uniq_, &d_notify_, &d_lbl_, &d_gcount_, &d_dtab_};
   uint64_t t = 0;
   for (const DevBuf* b : bufs) t += b->cap;
   for (const DevBuf& b : closure_bufs_) t += b.cap;
@@ -1096,7 +1096,8 @@ int Engine::signature_rounds(const dfamin_opts& opts, uint64_t max_rounds, hipSt
     // count table's 2^16 words do as well, with five the keys are too long)
     const bool one = large && m == N && alist.size() == 1 && !dbl[0] && !has_closure_[0];
     if (one && rounds == 1 && dense_from_labels && cnt_ok[0] && desc_[0].ebits && desc_[0].kp == 4 &&
-        !would_scan(0) && ensure(d_table_, (1ull << ceil_log2_u64(2 * N)) * sizeof(Slot)) == DFAMIN_OK) {  // 32 MiB at least
+        !would_scan(0) &&
+        ensure(d_table_, (1ull << ceil_log2_u64(2 * N)) * sizeof(Slot)) == DFAMIN_OK) {  // (the maps: 32 MiB at least)
       prof.begin(s, "label2", (double)N * (0.125 + 4.5 * 4 + 0.5 + 4.0));
       launch_label2(d_desc_.as<InstDesc>(), d_rows_.as<uint64_t>(), (uint32_t)N, d_dense_.as<uint8_t>() + nib_at,
                     d_nb_.as<uint32_t>(), ctx_->cus, s);
@@ -1814,6 +1815,7 @@ int Engine::minimal_dfa(const dfamin_opts& opts, hipStream_t s, uint32_t nb, uin
     ++levels;
     cur ^= 1u;
   }
+  lease.give();
   // quotient of the reachable classes
   uint32_t* sel = d_nb_.as<uint32_t>();
   uint32_t* rid = d_rank_.as<uint32_t>();
@@ -2167,9 +2169,10 @@ int Engine::grid_run(const std::vector<InstInput>& in, const dfamin_opts& opts, 
     // (in the fixed region the round engine takes it where the storage that
     // it is certain to have there does not hold every level)
     closure_denied_ = false;
-    closure_limit_ = fixed() ? fixed_handoff_cap(x) : ~0ull;
+    const uint64_t limit = closure_limit_;
+    if (fixed()) closure_limit_ = fixed_handoff_cap(x);
     const int rc = build_closure({0u}, opts, s);
-    closure_limit_ = ~0ull;
+    closure_limit_ = limit;
     if (rc != DFAMIN_OK) return rc;
     if (fixed() && closure_denied_) return leave();
     TRY(upload_rows());
