@@ -1074,9 +1074,9 @@ struct Serving::Impl {
                 gpend.end());
     // While the resident set has a request of its own, its rounds take the
     // others along: lanes beside them hold the CUs that the rounds wait for
-    // (2^8 to 2^22 states at 1,400 requests a second: 99% within 16.6 ms, with
-    // lanes at all times 17 to 25; requests above 524,288 states 20 and 21 to
-    // 52).
+    // (2^8 to 2^22 states at 1,400 requests a second: 99% within 16.3 to 17.7
+    // ms, with lanes at all times 16.6 to 25; requests above 524,288 states 19
+    // to 22 and 20 to 52).
     if (any_joined()) {
       back.insert(back.end(), gpend.begin(), gpend.end());
       gpend.clear();
