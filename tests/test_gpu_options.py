@@ -204,3 +204,40 @@ def test_small_budgets_take_calls_in_a_row():
                     outs, _ = dfamin.dfamin_minimize_batch(c, batch, "auto")
                     for o, w in zip(outs, bwant):
                         assert np.array_equal(o, w)
+
+
+def test_small_budget_after_calls_that_did_not_fit():
+    """64 MiB: a chain of 200,000 states has room after other calls, some of
+    which may have been refused."""
+    from paper_2410_22764_amd import dfamin
+    ds = [(W.random_dfa(100000, 12, 1), True), (shift_dfa(60000, [1, 7], "shift(1,7) n=60000"), True),
+          (W.random_dfa(300000, 2, 1), False), (W.permuted_chain_dfa(200000, 2, 1), True)]
+    with dfamin.dfamin_create(0, 64 << 20) as c:
+        for d, fits in ds:
+            want, nb = oracle.hopcroft(d.n, d.k, d.delta, d.accept)
+            for closure in ("auto", "on"):
+                print(f"[case] budget 64 MiB: {d.name} closure {closure}", flush=True)
+                out, r = dfamin.dfamin_minimize(c, d, closure, check=False)
+                assert r["rc"] == dfamin.DFAMIN_OK or (not fits and r["rc"] == dfamin.DFAMIN_E_NOMEM), (d.name, closure, r)
+                if r["rc"] == dfamin.DFAMIN_OK:
+                    assert np.array_equal(out, want) and r["num_blocks"] == nb
+
+
+@pytest.mark.parametrize("mib", [22, 24.66, 30, 40])
+def test_small_budget_keeps_the_levels_of_the_round_engine(mib, monkeypatch):
+    """A deep instance of sixteen letters under AUTO: no fewer closure levels
+    with the grid kernel than with the round engine's rounds."""
+    from paper_2410_22764_amd import dfamin
+    d = shift_dfa(40000, list(range(1, 17)), "shift(1..16) n=40000")
+    want, nb = _hop(d)
+    levels = []
+    for grid in (True, False):
+        if not grid:
+            monkeypatch.setenv("DFAMIN_GRID_MAX_STATES", "0")
+        print(f"[case] {d.name}, budget {mib} MiB, grid {grid}", flush=True)
+        with dfamin.dfamin_create(0, int(mib * (1 << 20))) as c:
+            out, r = dfamin.dfamin_minimize(c, d, "auto", check=False)
+        assert r["rc"] == dfamin.DFAMIN_OK
+        assert np.array_equal(out, want) and r["num_blocks"] == nb
+        levels.append(r["closure_levels"])
+    assert levels[0] >= levels[1], levels
