@@ -2346,6 +2346,7 @@ int Engine::run_all(const std::vector<InstInput>& in, const dfamin_opts& opts, h
   if (fs != s) HIP(event_wait(fused_done_));
   if (bs != s) HIP(event_wait(big_done_));
   ctx_->prof.collect();
+  big_busy_ = false;  // (their scratch may give way to the closures of those handed back)
   TRY(fused_collect(in, small, res, handoff));
   if (!handoff.empty()) TRY(run_subset(handoff, nonid_all));
   return DFAMIN_OK;

@@ -241,3 +241,20 @@ def test_small_budget_keeps_the_levels_of_the_round_engine(mib, monkeypatch):
         assert np.array_equal(out, want) and r["num_blocks"] == nb
         levels.append(r["closure_levels"])
     assert levels[0] >= levels[1], levels
+
+
+def test_handed_back_instances_have_the_scratch_of_the_others():
+    """A batch of larger instances, most done in a workgroup each, some handed
+    back for their closure: the scratch of the others gives way to its levels."""
+    from paper_2410_22764_amd import dfamin
+    ds = [W.random_dfa(17000 + 13 * i, 3, i) for i in range(60)]
+    ds += [shift_dfa(17500, [1, 2, 3, 4], "shift(1,2,3,4) n=17500")] * 3
+    want, nb = _hop(ds[-1])
+    levels = {}
+    for mib in (90, 400):
+        print(f"[case] batch of {len(ds)}, budget {mib} MiB", flush=True)
+        with dfamin.dfamin_create(0, mib << 20) as c:
+            outs, res = dfamin.dfamin_minimize_batch(c, ds, "auto")
+        assert np.array_equal(outs[-1], want) and res[-1]["num_blocks"] == nb
+        levels[mib] = [r["closure_levels"] for r in res[-3:]]
+    assert levels[90] == levels[400], levels
